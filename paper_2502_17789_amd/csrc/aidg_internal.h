@@ -1,6 +1,8 @@
 // Internal declarations shared by the host plan code and the HIP kernels.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -36,7 +38,8 @@ struct alignas(16) SubgridDev {
   double w0;                   // layer w, wavelengths
   int32_t fold;                // 1: visibilities enter and leave conjugate-transposed
   int32_t kind;                // degridder form: kDegridRecur, kDegridDirect or kDegridPerVis
-  int32_t pad2, pad3;
+  int32_t order;               // matrix kernels: terms of the w series (0 .. kMaxWOrder)
+  float wmid;                  // matrix kernels: middle of the w range, wavelengths from w0
 };
 // Degridder forms, chosen per subgrid by the plan (degrid_form).
 constexpr int32_t kDegridRecur = 0;   // lanes own pixels; phasors step along each row's channels
@@ -52,6 +55,18 @@ struct Geometry {
   double dl, fov, du, beta, w_step;
   int64_t workspace;
 };
+
+// Tables of the matrix kernels.  The w-term n1(l, m) splits into n1(l, 0) + n1(0, m) + c(l, m)
+// and c = -b(l) b(m) to the given residual; peak[j] is the largest taper-weighted |c|^j.
+constexpr int kMaxWOrder = 3;
+struct WSeries {
+  std::vector<double> axis_n1, b, cross;  // [L], [L], [L][L]
+  double peak[kMaxWOrder + 2] = {0}, residual = 0;
+};
+void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out);
+// Terms of the series in (w - wmid) c that a subgrid with |w - wmid| <= dw needs, or -1
+// where the matrix kernels do not apply.
+int w_series_order(const WSeries& ws, double dw);
 
 // Host-side partition (library's own algorithm); table entries are aidg_subgrid.
 struct PartitionResult {
@@ -91,6 +106,11 @@ struct KernelArgs {
   const void* ainvh;        // device (A^-1)^H planes of the inverse A-term mode, else null
   const void* taper;        // device [L][L] taper times (-1)^(x+y)
   const void* twiddle;      // device [L] exp(-2 pi i k / L)
+  // matrix kernels (FP32 plans): n1(l, 0) along the lattice axis; the factor b of the
+  // cross term, 64 b as an FP16 pair; taper (as above) and cross term per pixel
+  const double* axis_n1;    // device [L]
+  const uint32_t* axis_b;   // device [L]
+  const float2* taper_cross;  // device [L][L]
   const int64_t* grp_begin; // device [n_groups + 1]: first subgrid of each (layer, centre) group
   int nt_total, nc_total, N;
   int npol;                 // grid planes: 4 (XX, XY, YX, YY) or 1 (Stokes I)
@@ -118,7 +138,8 @@ struct JobRef {
   int32_t pad;
 };
 struct Group {
-  int32_t n, pad;
+  int32_t n;
+  int32_t matrix;           // 1: the matrix kernels take the launch's DFTs
   int64_t total_sg;         // per-subgrid slots in the launch
   int64_t total_grp;        // per-group slots (scratch images) in the launch
   void* scratch;            // [total_grp][4][L][L] subgrid images
@@ -142,6 +163,9 @@ int32_t degrid_form(const Geometry& g, int nt, int nc, bool uniform);
 // Launch one kernel class over a group (kernels.hip).  max_nv: the largest
 // sub-table of the group (degridder LDS).  Returns a hipError_t as int.
 int launch_group(KernelClass k, int L, int precision, const Group& g, void* stream, int max_nv);
+// The DFT classes (kGridDft, kDegridDft) of an FP32 group on the matrix cores
+// (subgrid_matrix.hip), for plans whose subgrids all qualify (w_series_order).
+int launch_matrix(KernelClass k, int L, const Group& g, void* stream);
 int launch_zero_vis(int precision, const int64_t* idx, int64_t n, void* vis, void* stream);
 
 // Image level (image.hip).  A row of N complex values is transformed in LDS: N must

@@ -78,6 +78,10 @@ struct aidg_plan {
   int64_t* d_excl = nullptr;
   int64_t* d_grp = nullptr;
   KernelArgs* d_args = nullptr;  // device copy of args()
+  // matrix kernels: all of the plan's subgrids qualify (gridding; degridding too unless the
+  // geometry asks for another form), and their tables, one allocation
+  bool matrix_grid = false, matrix_degrid = false;
+  char* d_series = nullptr;
   // image level (invert / predict): Stockham radices of N, twiddles exp(-2 pi i k / N)
   // and the reciprocal of the taper's axis at image resolution (FP64); absent when N
   // is not supported
@@ -119,6 +123,9 @@ struct aidg_plan {
     a.ainvh = d_ainvh;
     a.taper = d_taper;
     a.twiddle = d_tw;
+    a.axis_n1 = reinterpret_cast<const double*>(d_series);
+    a.axis_b = reinterpret_cast<const uint32_t*>(d_series + 8 * g.L);
+    a.taper_cross = reinterpret_cast<const float2*>(d_series + 12 * g.L);
     a.grp_begin = d_grp;
     a.nt_total = nt;
     a.nc_total = nc;
@@ -138,7 +145,7 @@ struct aidg_plan {
   void release() {
     void* ptrs[] = {d_sg,     d_uvw,       d_fc,    d_aterms,  d_taper,    d_tw,     d_scratch,
                     d_excl,   d_grp,       d_args,  d_img_tw,  d_img_itaper, d_ainvh, d_npairs,
-                    d_ncount, d_npartial,  d_nmap};
+                    d_ncount, d_npartial,  d_nmap,  d_series};
     hipStream_t fs = async_mem ? release_stream(device) : nullptr;
     int cur = device;
     if (fs) {
@@ -169,6 +176,7 @@ struct aidg_plan {
     d_ainvh = nullptr;
     d_npairs = nullptr;
     d_ncount = d_npartial = d_nmap = nullptr;
+    d_series = nullptr;
     last = nullptr;
   }
 };
@@ -228,6 +236,7 @@ aidg_status run(aidg_plan* p, KernelClass k, int64_t b0, int64_t n, const void* 
     Group g;
     std::memset(&g, 0, sizeof(g));
     g.n = 1;
+    g.matrix = k == kGridDft ? p->matrix_grid : p->matrix_degrid;
     g.total_sg = n;
     g.total_grp = p->sg_group[b0 + n - 1] - p->sg_group[b0] + 1;
     g.scratch = p->d_scratch;
@@ -375,11 +384,13 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
       if (rc != 0) r = hip_fail((hipError_t)rc, "zeroing excluded visibilities");
     }
   }
-  // group by (direction, L, precision); pack ranges into launches
+  // group by (direction, L, precision, kernels); pack ranges into launches
   std::vector<bool> done(n_items, false);
   for (int32_t i0 = 0; i0 < n_items && r == AIDG_OK; ++i0) {
     if (done[i0]) continue;
     const int dir = items[i0].direction, L = items[i0].plan->g.L, prec = items[i0].plan->g.precision;
+    auto matrix = [&](const aidg_plan* p) { return dir == AIDG_DIR_GRID ? p->matrix_grid : p->matrix_degrid; };
+    const bool mx = matrix(items[i0].plan);
     const int64_t per_sg = (int64_t)4 * L * L * (prec == AIDG_FP32 ? 8 : 16);
     const int64_t cap = std::min<int64_t>(scratch_bytes / per_sg, 65535);
     if (cap < 1) {
@@ -389,6 +400,7 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
     Group g;
     std::memset(&g, 0, sizeof(g));
     g.scratch = scratch;
+    g.matrix = mx;
     int max_nv = 1;
     auto flush = [&]() -> aidg_status {
       if (g.total_sg == 0) return AIDG_OK;
@@ -398,12 +410,15 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
       if (rc == 0) rc = launch_group(k1, L, prec, g, hip_stream, max_nv);
       std::memset(&g, 0, sizeof(g));
       g.scratch = scratch;
+      g.matrix = mx;
       max_nv = 1;
       return rc == 0 ? AIDG_OK : hip_fail((hipError_t)rc, "grouped kernel launch");
     };
     for (int32_t i = i0; i < n_items && r == AIDG_OK; ++i) {
       const aidg_work& w = items[i];
-      if (done[i] || w.direction != dir || w.plan->g.L != L || w.plan->g.precision != prec) continue;
+      if (done[i] || w.direction != dir || w.plan->g.L != L || w.plan->g.precision != prec ||
+          matrix(w.plan) != mx)
+        continue;
       done[i] = true;
       // a launch takes whole or partial groups until `cap` group images
       const aidg_plan* p = w.plan;
@@ -606,6 +621,13 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       uvw_dev.resize(6 * uvw_rows);
       for (size_t i = 0; i < 3 * uvw_rows; ++i) uvw_dev[3 * uvw_rows + i] = -uvw_m[i];
     }
+    const int L = g.L;
+    const bool f32 = g.precision == AIDG_FP32;
+    std::vector<double> T;
+    kaiser_bessel_taper(L, g.beta, &T);
+    WSeries series;
+    if (f32) w_series(L, g.fov, T, &series);
+    bool matrix = f32;
     std::vector<SubgridDev> dev(plan->table.size());
     for (size_t i = 0; i < plan->table.size(); ++i) {
       const aidg_subgrid& s = plan->table[i];
@@ -633,9 +655,25 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       d.dfc = df * inv_c;
       d.R = uniform ? g.R : 1;
       d.kind = degrid_form(g, s.nt, s.nc, uniform);
+      if (matrix) {
+        // w range of the sub-table, from its rows' end channels (frequencies increase)
+        double lo = 1e300, hi = -1e300;
+        for (int64_t r = d.uvw0; r < d.uvw0 + s.nt; ++r)
+          for (int c : {s.c0, s.c0 + s.nc - 1}) {
+            const double w = uvw_dev[3 * r + 2] * (freqs_hz[c] * inv_c) - s.w0;
+            lo = std::min(lo, w);
+            hi = std::max(hi, w);
+          }
+        d.wmid = (float)(0.5 * (lo + hi));
+        const double dw = std::max(hi - d.wmid, d.wmid - lo);
+        d.order = w_series_order(series, dw);
+        matrix = d.order >= 0;
+      }
       plan->n_pervis += d.kind == kDegridPerVis;
       plan->n_direct += d.kind == kDegridDirect;
     }
+    plan->matrix_grid = matrix;
+    plan->matrix_degrid = matrix && g.degrid_form == AIDG_DEGRID_AUTO;
     // inverse A-term mode: distinct (A_p plane, A_q plane) pairs with their visibility
     // counts, for the normalisation map
     std::vector<int32_t> pairs;
@@ -656,9 +694,6 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     }
     std::vector<double> fc(n_chans);
     for (int c = 0; c < n_chans; ++c) fc[c] = freqs_hz[c] * inv_c;
-    const int L = g.L;
-    std::vector<double> T;
-    kaiser_bessel_taper(L, g.beta, &T);
     for (int y = 0; y < L; ++y)
       for (int x = 0; x < L; ++x)
         if ((x + y) & 1) T[(size_t)y * L + x] = -T[(size_t)y * L + x];
@@ -668,8 +703,25 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       tw[2 * k] = std::cos(ang);
       tw[2 * k + 1] = std::sin(ang);
     }
-    const bool f32 = g.precision == AIDG_FP32;
     std::vector<float> Tf(T.begin(), T.end()), twf(tw.begin(), tw.end());
+    std::vector<char> series_host;
+    if (f32) {
+      series_host.resize((size_t)12 * L + (size_t)8 * L * L);
+      double* n1 = reinterpret_cast<double*>(series_host.data());
+      uint32_t* b = reinterpret_cast<uint32_t*>(series_host.data() + 8 * L);
+      float* tc = reinterpret_cast<float*>(series_host.data() + 12 * L);
+      for (int x = 0; x < L; ++x) {
+        n1[x] = series.axis_n1[x];
+        const _Float16 v = (_Float16)(64.0 * series.b[x]);
+        uint16_t u;
+        std::memcpy(&u, &v, 2);
+        b[x] = (uint32_t)u << 16 | u;
+      }
+      for (int i = 0; i < L * L; ++i) {
+        tc[2 * i] = Tf[i];
+        tc[2 * i + 1] = (float)series.cross[i];
+      }
+    }
     // image level: twiddles exp(-2 pi i k / N) and the reciprocal 1 / t[X] of the taper
     // axis at image resolution
     std::vector<double> img_t, img_tw;
@@ -724,6 +776,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         (st = dalloc(&plan->d_grp, plan->grp_begin.size() * sizeof(int64_t), plan, "group index", stream)) ||
         (st = dalloc(&plan->d_scratch, plan->scratch_bytes, plan, "subgrid workspace", stream)) ||
         (st = dalloc(&plan->d_args, sizeof(KernelArgs), plan, "launch parameters", stream)) ||
+        (f32 && (st = dalloc(&plan->d_series, series_host.size(), plan, "w series tables", stream))) ||
         (plan->img_ok &&
          ((st = dalloc(&plan->d_img_tw, (size_t)g.N * plan->elem, plan, "image twiddles", stream)) ||
           (st = dalloc(&plan->d_img_itaper, (size_t)g.N * sizeof(double), plan, "image taper", stream)))) ||
@@ -755,6 +808,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         {plan->d_excl, pr.excluded.data(), pr.excluded.size() * sizeof(int64_t), hipMemcpyHostToDevice},
         {plan->d_grp, plan->grp_begin.data(), plan->grp_begin.size() * sizeof(int64_t), hipMemcpyHostToDevice},
         {plan->d_args, &host_args, sizeof(KernelArgs), hipMemcpyHostToDevice},
+        {plan->d_series, series_host.data(), series_host.size(), hipMemcpyHostToDevice},
         {plan->d_img_tw, f32 ? (const void*)img_twf.data() : (const void*)img_tw.data(),
          plan->img_ok ? (size_t)g.N * plan->elem : 0, hipMemcpyHostToDevice},
         {plan->d_img_itaper, img_t.data(), plan->img_ok ? (size_t)g.N * sizeof(double) : 0,
@@ -907,7 +961,8 @@ aidg_status aidg_footprint_estimate(const aidg_geometry* geo, int32_t n_stations
     const int64_t batch = std::max<int64_t>(1, std::min<int64_t>({g.workspace / per_image, 65535, se.n_groups}));
     int64_t b = al(n_sg * (int64_t)sizeof(SubgridDev)) + al((int64_t)n_baselines * n_times * 24 * (g.fold ? 2 : 1)) +
                 al((int64_t)n_chans * 8) + out->aterm_bytes + al(L * L * elem / 2) + al(L * elem) +
-                al(se.n_excluded * 8) + al((n_sg + 1) * 8) + al(batch * per_image) + al(sizeof(KernelArgs));
+                al(se.n_excluded * 8) + al((n_sg + 1) * 8) + al(batch * per_image) + al(sizeof(KernelArgs)) +
+                (g.precision == AIDG_FP32 ? al(12 * L + 8 * L * L) : 0);
     if (N <= kMaxImageN) b += al(N * elem) + al(N * 8);
     if (g.amode) {
       const int64_t pairs = std::min<int64_t>(n_sg, (int64_t)n_int * n_baselines);

@@ -52,33 +52,11 @@
 
 #include "aidg_internal.h"
 #include "device_common.h"
+#include "subgrid_common.h"
 
 namespace aidg {
 namespace {
 
-constexpr int kThreads = 256;
-// Workgroups are dispatched to the 8 XCDs (each with its own L2) round-robin by
-// linear workgroup index, so index b runs on XCD b % 8.
-constexpr int kXcds = 8;
-
-// Gridder work item of linear workgroup index b: (group slot, pixel chunk) such
-// that all chunks of a slot share one XCD (its visibilities are fetched into one
-// L2) while consecutive slots, longest first, spread over the XCDs.  The launch
-// has ceil(slots / 8) * 8 * chunks workgroups; indices past the last slot exit.
-template <int Chunks>
-__device__ __forceinline__ void grid_work(int64_t b, int64_t* slot, int* chunk) {
-  const int64_t k = b / kXcds;
-  *chunk = (int)(k % Chunks);
-  *slot = (k / Chunks) * kXcds + b % kXcds;
-}
-
-// Degridder subgrid slot of linear workgroup index b < n: within every full tile
-// of 64, XCD x takes the 8 consecutive slots 8x..8x+7 (subgrids of one
-// same-centre group then mostly share their image in one L2); a last partial
-// tile maps one to one.
-__device__ __forceinline__ int64_t degrid_slot(int64_t b, int64_t n) {
-  return b < (n & ~int64_t(63)) ? ((b & ~int64_t(63)) | ((b & 7) << 3) | ((b >> 3) & 7)) : b;
-}
 // Gridder tiling: pixels per lane (PIX; a workgroup pass covers kThreads PIX pixels) and
 // the waves per SIMD the register allocation aims at (W).
 template <typename R> struct GridTune;
@@ -105,89 +83,6 @@ __device__ __forceinline__ SeedPixel pixel_at(int pix, double lstep) {
   const double l = (x - L / 2) * lstep, m = (y - L / 2) * lstep;
   const double r2 = l * l + m * m;
   return {-r2 / (1.0 + sqrt(1.0 - r2)), (float)(x - L / 2), (float)(y - L / 2)};
-}
-
-// Values every lane of a wave holds identically, moved to scalar registers word
-// by word so that loop bounds and addresses derived from them stay wave-uniform
-// (scalar branches, scalar loads of visibilities and uvw).
-template <typename T>
-__device__ __forceinline__ T uniform(const T& v) {
-  static_assert(sizeof(T) % 4 == 0, "word-sized");
-  int w[sizeof(T) / 4];
-  __builtin_memcpy(w, &v, sizeof(T));
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
-  T r;
-  __builtin_memcpy(&r, w, sizeof(T));
-  return r;
-}
-
-// Read-only view of memory no kernel writes while the launch runs: wave-uniform
-// loads through it become scalar loads (the scalar data cache broadcasts them).
-template <typename T>
-using const_view = const __attribute__((address_space(4))) T*;
-template <typename T>
-__device__ __forceinline__ const_view<T> as_const(const T* p) {
-  return (const_view<T>)(uintptr_t)p;
-}
-
-// A record every lane reads from the same address: scalar loads word by word.
-template <typename T>
-__device__ __forceinline__ T load_uniform(const T* p) {
-  static_assert(sizeof(T) % 4 == 0, "word-sized");
-  const_view<int> q = as_const(reinterpret_cast<const int*>(p));
-  int w[sizeof(T) / 4];
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(q[i]);
-  T r;
-  __builtin_memcpy(&r, w, sizeof(T));
-  return r;
-}
-
-// Group slot of a grouped launch: the plan's parameters and its subgrid range.
-struct GroupSlot {
-  KernelArgs a;
-  int64_t sb, se;  // subgrids [sb, se) of the group within the job's range
-  const void* in;
-  void* out;
-  int adjoint;
-};
-__device__ __forceinline__ GroupSlot resolve_group(const Group& g, int64_t slot) {
-  int j = 0;
-  for (int i = 1; i < g.n; ++i)
-    if (slot >= g.job[i].gslot_begin) j = i;
-  GroupSlot r;
-  r.a = load_uniform(g.job[j].args);
-  const int64_t grp = g.job[j].g_first + (slot - g.job[j].gslot_begin);
-  const_view<int64_t> gb = as_const(r.a.grp_begin);
-  r.sb = max(gb[grp], g.job[j].sg_begin);
-  r.se = min(gb[grp + 1], g.job[j].sg_end);
-  r.in = uniform(g.job[j].in);
-  r.out = uniform(g.job[j].out);
-  r.adjoint = uniform(g.job[j].adjoint);
-  return r;
-}
-
-// Subgrid slot of a grouped launch (degridder): parameters, subgrid and the
-// scratch slot holding its group's image.
-struct Slot {
-  KernelArgs a;
-  SubgridDev s;
-  int64_t img_slot;
-  const void* in;
-  void* out;
-};
-__device__ __forceinline__ Slot resolve(const Group& g, int64_t slot) {
-  int j = 0;
-  for (int i = 1; i < g.n; ++i)
-    if (slot >= g.job[i].slot_begin) j = i;
-  Slot r;
-  r.a = load_uniform(g.job[j].args);
-  r.s = load_uniform(r.a.sg + g.job[j].sg_begin + (slot - g.job[j].slot_begin));
-  r.img_slot = g.job[j].gslot_begin + (r.s.group - g.job[j].g_first);
-  r.in = uniform(g.job[j].in);
-  r.out = uniform(g.job[j].out);
-  return r;
 }
 
 // ------------------------------------------------------------------ gridder
@@ -593,20 +488,6 @@ __global__ __launch_bounds__(kThreads) void split_ifft(const Group g) {
 
 // ------------------------------------------------------------------ degridder
 
-__device__ __forceinline__ void swap32(float& x, float& y) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  x = __uint_as_float(r[0]);
-  y = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ void swap16(float& x, float& y) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  x = __uint_as_float(r[0]);
-  y = __uint_as_float(r[1]);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
 __device__ __forceinline__ void swap32(double& x, double& y) {
   float xl = __uint_as_float((unsigned)__double_as_longlong(x));
   float xh = __uint_as_float((unsigned)(__double_as_longlong(x) >> 32));
@@ -636,8 +517,6 @@ __device__ __forceinline__ double dpp(double x) {
 }
 
 constexpr int kDppXor2 = 0x4E, kDppXor1 = 0xB1;  // quad_perm [2,3,0,1] and [1,0,3,2]
-constexpr int kDppRowMirror = 0x140;      // lane c of a row of 16 reads lane 15 - c
-constexpr int kDppRowHalfMirror = 0x141;  // lane c of a half row of 8 reads lane 7 - c
 
 // Degridder channel blocks: the waves' reduced values of up to kChanBlock channels of a
 // row meet in LDS and are added to the output in a fixed order once per block.
@@ -729,19 +608,6 @@ __device__ __forceinline__ void corrected_pixel(const KernelArgs& a, const Subgr
   sp[1] = (cmul<R>(t0, b2) + cmul<R>(t1, b3)) * w;
   sp[2] = (cmul<R>(t2, b0) + cmul<R>(t3, b1)) * w;
   sp[3] = (cmul<R>(t2, b2) + cmul<R>(t3, b3)) * w;
-}
-
-// Output element i (= 8 x channel offset + component) of a degridded row: a folded
-// sub-table returns the conjugate transpose of its prediction at -uvw.
-template <typename R>
-__device__ __forceinline__ void store_vis(R* vrow, int i, R v, bool fold, bool add) {
-  int d = i;
-  if (fold) {
-    const int comp = i & 7, pol = comp >> 1;
-    d = i - comp + (pol == 1 ? 2 : pol == 2 ? 1 : pol) * 2 + (comp & 1);
-    if (comp & 1) v = -v;
-  }
-  vrow[d] = add ? vrow[d] + v : v;
 }
 
 // Pixels per LDS chunk of the per-visibility form: the corrected image (4 values) and
@@ -1171,6 +1037,7 @@ int launch_group(KernelClass k, int L, int precision, const Group& g, void* stre
   if (g.total_sg <= 0) return 0;
   if (g.n < 1 || g.n > kMaxGroup || g.total_grp < 1 || g.total_grp > 65535 || g.total_grp > g.total_sg)
     return (int)hipErrorInvalidValue;
+  if (g.matrix && (k == kGridDft || k == kDegridDft)) return launch_matrix(k, L, g, stream);
   if (precision == AIDG_FP32) {
     switch (L) {
       case 32: return launch_one<32, float>(k, g, st, max_nv);

@@ -611,4 +611,50 @@ void kaiser_bessel_taper(int L, double beta, std::vector<double>* T) {
     for (int x = 0; x < L; ++x) (*T)[(size_t)y * L + x] = t[x] * t[y];
 }
 
+void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out) {
+  auto n1 = [](double r2) { return -r2 / (1.0 + std::sqrt(1.0 - r2)); };
+  std::vector<double> l(L);
+  out->axis_n1.resize(L);
+  for (int x = 0; x < L; ++x) {
+    l[x] = (x - L / 2) * (fov / L);
+    out->axis_n1[x] = n1(l[x] * l[x]);
+  }
+  out->cross.resize((size_t)L * L);
+  int at = 0;  // row of the largest taper-weighted |c|
+  for (int y = 0; y < L; ++y)
+    for (int x = 0; x < L; ++x) {
+      const double c = n1(l[x] * l[x] + l[y] * l[y]) - out->axis_n1[x] - out->axis_n1[y];
+      out->cross[(size_t)y * L + x] = c;
+      double t = std::fabs(taper[(size_t)y * L + x]);
+      for (int j = 1; j <= kMaxWOrder + 1; ++j) {
+        t *= std::fabs(c);
+        if (j == 1 && t > out->peak[1]) at = y;
+        out->peak[j] = std::max(out->peak[j], t);
+      }
+    }
+  // the cross of the peak's row and column: exact on them, and elsewhere off by the part of
+  // c beyond l^2 m^2 terms that does not separate
+  const double d = std::sqrt(std::max(0.0, -out->cross[(size_t)at * L + at]));
+  out->b.resize(L);
+  for (int x = 0; x < L; ++x) out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
+  for (int y = 0; y < L; ++y)
+    for (int x = 0; x < L; ++x)
+      out->residual = std::max(out->residual, std::fabs(taper[(size_t)y * L + x]) *
+                                                  std::fabs(out->cross[(size_t)y * L + x] + out->b[x] * out->b[y]));
+}
+
+// The series is cut where its first missing term is below 3e-8 of the taper's peak, a tenth
+// of the FP32 path's normwise error; the first-order term, taken in FP16, may be 1e-3 (its
+// rounding is then below 5e-8 rms), and the part of c that is not b b below 1e-7.
+int w_series_order(const WSeries& ws, double dw) {
+  const double p = 2.0 * M_PI * dw;
+  if (!(p * ws.peak[1] <= 1e-3) || !(p * ws.residual <= 1e-7)) return -1;
+  double term = 1.0;
+  for (int j = 0; j <= kMaxWOrder; ++j) {
+    term *= p / (j + 1);
+    if (term * ws.peak[j + 1] <= 3e-8) return j;
+  }
+  return -1;
+}
+
 }  // namespace aidg
