@@ -53,6 +53,22 @@ hipStream_t release_stream(int device) {
 
 }  // namespace
 
+// Byte offsets of a plan's tables in their one allocation: taper times (-1)^(x+y) [L][L] and
+// twiddles [L] in the plan's precision, and in FP32 plans the matrix kernels' n1 and b along
+// the axis [L] and taper and cross term [L][L].
+struct TableLayout {
+  size_t taper_cross, axis_n1, twiddle, taper, axis_b, bytes;
+  TableLayout(int L, size_t elem) {
+    const size_t n = (size_t)L * L, matrix = elem == 8 ? 1 : 0;
+    taper_cross = 0;
+    axis_n1 = taper_cross + matrix * 8 * n;
+    twiddle = axis_n1 + matrix * 8 * L;
+    taper = twiddle + elem * L;
+    axis_b = taper + elem / 2 * n;
+    bytes = axis_b + matrix * 4 * L;
+  }
+};
+
 struct aidg_plan {
   Geometry g{};
   int n_st = 0, nbl = 0, nt = 0, nc = 0, n_int = 0, W = 1, max_nv = 1, device = 0;
@@ -72,16 +88,14 @@ struct aidg_plan {
   double* d_uvw = nullptr;
   double* d_fc = nullptr;
   void* d_aterms = nullptr;
-  void* d_taper = nullptr;
-  void* d_tw = nullptr;
+  char* d_tables = nullptr;  // taper, twiddles and the matrix kernels' tables, see table_layout
   void* d_scratch = nullptr;
   int64_t* d_excl = nullptr;
   int64_t* d_grp = nullptr;
   KernelArgs* d_args = nullptr;  // device copy of args()
   // matrix kernels: all of the plan's subgrids qualify (gridding; degridding too unless the
-  // geometry asks for another form), and their tables, one allocation
+  // geometry asks for another form)
   bool matrix_grid = false, matrix_degrid = false;
-  char* d_series = nullptr;
   // image level (invert / predict): Stockham radices of N, twiddles exp(-2 pi i k / N)
   // and the reciprocal of the taper's axis at image resolution (FP64); absent when N
   // is not supported
@@ -121,11 +135,12 @@ struct aidg_plan {
     a.fc = d_fc;
     a.aterms = d_aterms;
     a.ainvh = d_ainvh;
-    a.taper = d_taper;
-    a.twiddle = d_tw;
-    a.axis_n1 = reinterpret_cast<const double*>(d_series);
-    a.axis_b = reinterpret_cast<const uint32_t*>(d_series + 8 * g.L);
-    a.taper_cross = reinterpret_cast<const float2*>(d_series + 12 * g.L);
+    const TableLayout tl(g.L, elem);
+    a.taper = d_tables + tl.taper;
+    a.twiddle = d_tables + tl.twiddle;
+    a.axis_n1 = reinterpret_cast<const double*>(d_tables + tl.axis_n1);
+    a.axis_b = reinterpret_cast<const uint32_t*>(d_tables + tl.axis_b);
+    a.taper_cross = reinterpret_cast<const float2*>(d_tables + tl.taper_cross);
     a.grp_begin = d_grp;
     a.nt_total = nt;
     a.nc_total = nc;
@@ -143,9 +158,9 @@ struct aidg_plan {
   bool async_mem = false;
 
   void release() {
-    void* ptrs[] = {d_sg,     d_uvw,       d_fc,    d_aterms,  d_taper,    d_tw,     d_scratch,
+    void* ptrs[] = {d_sg,     d_uvw,       d_fc,    d_aterms,  d_tables,   d_scratch,
                     d_excl,   d_grp,       d_args,  d_img_tw,  d_img_itaper, d_ainvh, d_npairs,
-                    d_ncount, d_npartial,  d_nmap,  d_series};
+                    d_ncount, d_npartial,  d_nmap};
     hipStream_t fs = async_mem ? release_stream(device) : nullptr;
     int cur = device;
     if (fs) {
@@ -167,7 +182,8 @@ struct aidg_plan {
     timed.clear();
     d_sg = nullptr;
     d_uvw = d_fc = nullptr;
-    d_aterms = d_taper = d_tw = d_scratch = nullptr;
+    d_aterms = d_scratch = nullptr;
+    d_tables = nullptr;
     d_excl = nullptr;
     d_grp = nullptr;
     d_args = nullptr;
@@ -176,7 +192,6 @@ struct aidg_plan {
     d_ainvh = nullptr;
     d_npairs = nullptr;
     d_ncount = d_npartial = d_nmap = nullptr;
-    d_series = nullptr;
     last = nullptr;
   }
 };
@@ -703,13 +718,20 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       tw[2 * k] = std::cos(ang);
       tw[2 * k + 1] = std::sin(ang);
     }
-    std::vector<float> Tf(T.begin(), T.end()), twf(tw.begin(), tw.end());
-    std::vector<char> series_host;
+    const TableLayout tl(L, plan->elem);
+    std::vector<char> tables(tl.bytes);
+    for (int i = 0; i < L * L; ++i) {
+      if (f32) reinterpret_cast<float*>(tables.data() + tl.taper)[i] = (float)T[i];
+      else reinterpret_cast<double*>(tables.data() + tl.taper)[i] = T[i];
+    }
+    for (int k = 0; k < 2 * L; ++k) {
+      if (f32) reinterpret_cast<float*>(tables.data() + tl.twiddle)[k] = (float)tw[k];
+      else reinterpret_cast<double*>(tables.data() + tl.twiddle)[k] = tw[k];
+    }
     if (f32) {
-      series_host.resize((size_t)12 * L + (size_t)8 * L * L);
-      double* n1 = reinterpret_cast<double*>(series_host.data());
-      uint32_t* b = reinterpret_cast<uint32_t*>(series_host.data() + 8 * L);
-      float* tc = reinterpret_cast<float*>(series_host.data() + 12 * L);
+      double* n1 = reinterpret_cast<double*>(tables.data() + tl.axis_n1);
+      uint32_t* b = reinterpret_cast<uint32_t*>(tables.data() + tl.axis_b);
+      float* tc = reinterpret_cast<float*>(tables.data() + tl.taper_cross);
       for (int x = 0; x < L; ++x) {
         n1[x] = series.axis_n1[x];
         const _Float16 v = (_Float16)(64.0 * series.b[x]);
@@ -718,7 +740,9 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         b[x] = (uint32_t)u << 16 | u;
       }
       for (int i = 0; i < L * L; ++i) {
-        tc[2 * i] = Tf[i];
+        // A value passes through three phasors of the transcendental unit (the two axes and the
+        // cross term), whose cosine and sine leave |z| short of 1 by 3.25e-8 on average.
+        tc[2 * i] = (float)(T[i] * (1.0 + 3 * 3.25e-8));
         tc[2 * i + 1] = (float)series.cross[i];
       }
     }
@@ -770,13 +794,11 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         (st = dalloc(&plan->d_uvw, uvw_dev.size() * sizeof(double), plan, "uvw", stream)) ||
         (st = dalloc(&plan->d_fc, fc.size() * sizeof(double), plan, "frequencies", stream)) ||
         (st = dalloc(&plan->d_aterms, plan->aterm_bytes, plan, "A-terms", stream)) ||
-        (st = dalloc(&plan->d_taper, (size_t)L * L * (f32 ? 4 : 8), plan, "taper", stream)) ||
-        (st = dalloc(&plan->d_tw, (size_t)L * (f32 ? 8 : 16), plan, "twiddles", stream)) ||
+        (st = dalloc(&plan->d_tables, tables.size(), plan, "tables", stream)) ||
         (st = dalloc(&plan->d_excl, pr.excluded.size() * sizeof(int64_t), plan, "excluded list", stream)) ||
         (st = dalloc(&plan->d_grp, plan->grp_begin.size() * sizeof(int64_t), plan, "group index", stream)) ||
         (st = dalloc(&plan->d_scratch, plan->scratch_bytes, plan, "subgrid workspace", stream)) ||
         (st = dalloc(&plan->d_args, sizeof(KernelArgs), plan, "launch parameters", stream)) ||
-        (f32 && (st = dalloc(&plan->d_series, series_host.size(), plan, "w series tables", stream))) ||
         (plan->img_ok &&
          ((st = dalloc(&plan->d_img_tw, (size_t)g.N * plan->elem, plan, "image twiddles", stream)) ||
           (st = dalloc(&plan->d_img_itaper, (size_t)g.N * sizeof(double), plan, "image taper", stream)))) ||
@@ -801,14 +823,10 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         {plan->d_uvw, uvw_dev.data(), uvw_dev.size() * sizeof(double), hipMemcpyHostToDevice},
         {plan->d_fc, fc.data(), fc.size() * sizeof(double), hipMemcpyHostToDevice},
         {plan->d_aterms, aterms, plan->aterm_bytes, hipMemcpyDeviceToDevice},
-        {plan->d_taper, f32 ? (const void*)Tf.data() : (const void*)T.data(), (size_t)L * L * (f32 ? 4 : 8),
-         hipMemcpyHostToDevice},
-        {plan->d_tw, f32 ? (const void*)twf.data() : (const void*)tw.data(), (size_t)L * (f32 ? 8 : 16),
-         hipMemcpyHostToDevice},
+        {plan->d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice},
         {plan->d_excl, pr.excluded.data(), pr.excluded.size() * sizeof(int64_t), hipMemcpyHostToDevice},
         {plan->d_grp, plan->grp_begin.data(), plan->grp_begin.size() * sizeof(int64_t), hipMemcpyHostToDevice},
         {plan->d_args, &host_args, sizeof(KernelArgs), hipMemcpyHostToDevice},
-        {plan->d_series, series_host.data(), series_host.size(), hipMemcpyHostToDevice},
         {plan->d_img_tw, f32 ? (const void*)img_twf.data() : (const void*)img_tw.data(),
          plan->img_ok ? (size_t)g.N * plan->elem : 0, hipMemcpyHostToDevice},
         {plan->d_img_itaper, img_t.data(), plan->img_ok ? (size_t)g.N * sizeof(double) : 0,
@@ -960,9 +978,8 @@ aidg_status aidg_footprint_estimate(const aidg_geometry* geo, int32_t n_stations
     const int64_t per_image = 4 * L * L * elem;
     const int64_t batch = std::max<int64_t>(1, std::min<int64_t>({g.workspace / per_image, 65535, se.n_groups}));
     int64_t b = al(n_sg * (int64_t)sizeof(SubgridDev)) + al((int64_t)n_baselines * n_times * 24 * (g.fold ? 2 : 1)) +
-                al((int64_t)n_chans * 8) + out->aterm_bytes + al(L * L * elem / 2) + al(L * elem) +
-                al(se.n_excluded * 8) + al((n_sg + 1) * 8) + al(batch * per_image) + al(sizeof(KernelArgs)) +
-                (g.precision == AIDG_FP32 ? al(12 * L + 8 * L * L) : 0);
+                al((int64_t)n_chans * 8) + out->aterm_bytes + al((int64_t)TableLayout(g.L, (size_t)elem).bytes) +
+                al(se.n_excluded * 8) + al((n_sg + 1) * 8) + al(batch * per_image) + al(sizeof(KernelArgs));
     if (N <= kMaxImageN) b += al(N * elem) + al(N * 8);
     if (g.amode) {
       const int64_t pairs = std::min<int64_t>(n_sg, (int64_t)n_int * n_baselines);

@@ -613,23 +613,26 @@ void kaiser_bessel_taper(int L, double beta, std::vector<double>* T) {
 
 void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out) {
   auto n1 = [](double r2) { return -r2 / (1.0 + std::sqrt(1.0 - r2)); };
-  std::vector<double> l(L);
+  std::vector<double> l2(L);
   out->axis_n1.resize(L);
   for (int x = 0; x < L; ++x) {
-    l[x] = (x - L / 2) * (fov / L);
-    out->axis_n1[x] = n1(l[x] * l[x]);
+    const double l = (x - L / 2) * (fov / L);
+    l2[x] = l * l;
+    out->axis_n1[x] = n1(l2[x]);
   }
+  // (c is symmetric, and so is the taper: x >= y covers the peaks)
   out->cross.resize((size_t)L * L);
   int at = 0;  // row of the largest taper-weighted |c|
   for (int y = 0; y < L; ++y)
-    for (int x = 0; x < L; ++x) {
-      const double c = n1(l[x] * l[x] + l[y] * l[y]) - out->axis_n1[x] - out->axis_n1[y];
-      out->cross[(size_t)y * L + x] = c;
+    for (int x = y; x < L; ++x) {
+      const double c = n1(l2[x] + l2[y]) - out->axis_n1[x] - out->axis_n1[y], m = std::fabs(c);
+      out->cross[(size_t)y * L + x] = out->cross[(size_t)x * L + y] = c;
       double t = std::fabs(taper[(size_t)y * L + x]);
       for (int j = 1; j <= kMaxWOrder + 1; ++j) {
-        t *= std::fabs(c);
-        if (j == 1 && t > out->peak[1]) at = y;
-        out->peak[j] = std::max(out->peak[j], t);
+        t *= m;
+        if (t <= out->peak[j]) continue;
+        out->peak[j] = t;
+        if (j == 1) at = y;
       }
     }
   // the cross of the peak's row and column: exact on them, and elsewhere off by the part of
@@ -638,9 +641,10 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
   out->b.resize(L);
   for (int x = 0; x < L; ++x) out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
   for (int y = 0; y < L; ++y)
-    for (int x = 0; x < L; ++x)
-      out->residual = std::max(out->residual, std::fabs(taper[(size_t)y * L + x]) *
-                                                  std::fabs(out->cross[(size_t)y * L + x] + out->b[x] * out->b[y]));
+    for (int x = y; x < L; ++x) {
+      const size_t i = (size_t)y * L + x;
+      out->residual = std::max(out->residual, std::fabs(taper[i] * (out->cross[i] + out->b[x] * out->b[y])));
+    }
 }
 
 // The series is cut where its first missing term is below 3e-8 of the taper's peak, a tenth

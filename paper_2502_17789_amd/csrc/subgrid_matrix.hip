@@ -26,6 +26,8 @@
 // beside them the VALU that forms the split operands.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "aidg_internal.h"
 #include "device_common.h"
 #include "subgrid_common.h"
@@ -49,26 +51,76 @@ __device__ __forceinline__ acc16 mfma(const Frag& a, const Frag& b, const acc16&
 __device__ __forceinline__ unsigned pk_mul(unsigned a, unsigned b) {
   return __builtin_bit_cast(unsigned, __builtin_bit_cast(half2v, a) * __builtin_bit_cast(half2v, b));
 }
-__device__ __forceinline__ unsigned swap_halves(unsigned p) { return __builtin_amdgcn_alignbit(p, p, 16); }
-constexpr unsigned kNegHigh = 0x80000000u, kNegBoth = 0x80008000u;
+__device__ __forceinline__ unsigned pk_mul_neg(unsigned a, unsigned b) {  // -a b
+  return __builtin_bit_cast(unsigned, -__builtin_bit_cast(half2v, a) * __builtin_bit_cast(half2v, b));
+}
+// (x, y) -> (-y, x), and (x, y) -> (y b_low, x b_high): one packed multiplication each, which
+// takes its operands' halves in any order (the compiler moves the swap behind it).
+__device__ __forceinline__ unsigned swap_mul(unsigned p, unsigned b) {
+  unsigned r;
+  asm("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0] op_sel_hi:[0,1]" : "=v"(r) : "v"(p), "v"(b));
+  return r;
+}
+__device__ __forceinline__ unsigned rot90(unsigned p) {
+  unsigned r;
+  asm("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0] op_sel_hi:[0,1]" : "=v"(r) : "v"(p), "s"(0x3C00BC00u));  // (-1, 1)
+  return r;
+}
+constexpr unsigned kNegLow = 0x8000u;
 
+// Loads and stores of device memory at a wave-uniform base and a lane's byte offset.  The
+// pointers of a launch come out of memory, which leaves their address space unknown: without
+// the casts these would be flat accesses, with 64-bit addresses per lane and an LDS wait each.
+typedef float vec2 __attribute__((ext_vector_type(2)));
+typedef float vec4 __attribute__((ext_vector_type(4)));
+#define AIDG_GLOBAL __attribute__((address_space(1)))
+template <typename V>
+__device__ __forceinline__ V gload(const void* base, unsigned off) {
+  return *(const AIDG_GLOBAL V*)((const AIDG_GLOBAL char*)base + off);
+}
+template <typename V>
+__device__ __forceinline__ void gstore(void* base, unsigned off, V v) {
+  *(AIDG_GLOBAL V*)((AIDG_GLOBAL char*)base + off) = v;
+}
+
+// (x, y) rounded to an FP16 pair (to nearest), and what it leaves of either (exact).
+__device__ __forceinline__ unsigned cvt_pair(float x, float y) {
+  const vec2 v = {x, y};
+  unsigned r = __builtin_bit_cast(unsigned, __builtin_convertvector(v, half2v));
+  asm("" : "+v"(r));  // one packed conversion: not formed again per element by what reads it
+  return r;
+}
+// (v_fma_mix_f32, which the compiler does not form from the subtraction.  Its operand x may
+// come from the transcendental unit, whose result a following instruction must not read at
+// once; the conversion that made p has read it before.)
+__device__ __forceinline__ float rest_low(float x, unsigned p) {
+  float r;
+  asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(x));
+  return r;
+}
+__device__ __forceinline__ float rest_high(float y, unsigned p) {
+  float r;
+  asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(p), "v"(y));
+  return r;
+}
 // (x, y) as FP16 pairs hi + lo.
 __device__ __forceinline__ void split(float x, float y, unsigned& hi, unsigned& lo) {
-  const half2v h = {(_Float16)x, (_Float16)y};
-  const half2v l = {(_Float16)(x - (float)h.x), (_Float16)(y - (float)h.y)};
-  hi = __builtin_bit_cast(unsigned, h);
-  lo = __builtin_bit_cast(unsigned, l);
+  hi = cvt_pair(x, y);
+  lo = cvt_pair(rest_low(x, hi), rest_high(y, hi));
 }
 __device__ __forceinline__ unsigned pair_of(float x) {
   const half2v h = {(_Float16)x, (_Float16)x};
   return __builtin_bit_cast(unsigned, h);
 }
 
-// exp(2 pi i theta) for a phase in turns: reduced in FP64, one rounding to FP32 (2^-26
-// turn), the transcendental unit's cosine and sine (absolute error at most 1.3e-7, rms
+// exp(2 pi i (u x + w z)) for phases in turns, |u x + w z| < 2^18: the sum is formed onto
+// 1.5 2^20, whose last place is 2^-32 turn, so that the low word of the FP64 result is the
+// phase modulo a turn in fixed point (rounded twice, 2^-33 turn); one rounding to FP32 (2^-26
+// turn), then the transcendental unit's cosine and sine (absolute error at most 1.3e-7, rms
 // 3.5e-8 over [-1/2, 1/2] turn, measured over 2^24 points).
-__device__ __forceinline__ float2 turn_phasor(double theta) {
-  const float t = (float)(theta - rint(theta));
+__device__ __forceinline__ float2 turn_phasor(double u, double x, double w, double z) {
+  const double th = fma(u, x, fma(w, z, 1572864.0));
+  const float t = (float)(int)__double_as_longlong(th) * 0x1p-32f;
   return {__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t)};
 }
 
@@ -82,40 +134,54 @@ __device__ __forceinline__ void fit_scale(float m, float& scale, float& unscale)
   unscale = __uint_as_float((unsigned)(127 - 9 + e) << 23);
 }
 
+// Largest of the wave's values (>= 0), by DPP: rotations within each row of 16 lanes, then
+// the four rows.
 __device__ __forceinline__ float wave_max(float m) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  return m;
+  m = fmaxf(m, dpp<0x121>(m));
+  m = fmaxf(m, dpp<0x122>(m));
+  m = fmaxf(m, dpp<0x124>(m));
+  m = fmaxf(m, dpp<0x128>(m));
+  const int v = __float_as_int(m);
+  return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(v, 0)), __int_as_float(__builtin_amdgcn_readlane(v, 16))),
+               fmaxf(__int_as_float(__builtin_amdgcn_readlane(v, 32)), __int_as_float(__builtin_amdgcn_readlane(v, 48))));
 }
 
-// Visibilities per LDS block and the row pitch (complex values) of the tables a lane
-// reads four consecutive visibilities of: 4 more than the block shifts each row by eight
-// banks.
-constexpr int kBlk = 64, kBlkPitch = kBlk + 4;
+// Visibilities per LDS block.
+constexpr int kBlk = 32;
+// Pixels whose Jones matrices are loaded ahead.
+constexpr int kAhead = 2;
 // Subgrid rows (y) of one workgroup pass: 8 per wave.
 constexpr int kRows = 32;
 
 // A block's visibilities: phase coefficients in turns per lattice step (u, v) and
 // wavelengths (w), and 2 pi d_k 2^-12 as an FP16 pair.
+template <int B>
 struct VisBlock {
-  double2 ku_w[kBlk];
-  double2 kv_w[kBlk];
-  unsigned dw[kBlk];
+  double2 ku_w[B];
+  double2 kv_w[B];
+  unsigned dw[B];
 };
 
-__device__ __forceinline__ void stage_vis_phases(const KernelArgs& a, const SubgridDev& s, int k0, int n, float inv_nc,
-                                                 VisBlock* vb) {
-  const int k = threadIdx.x;
-  if (k >= kBlk) return;
+// A visibility's uvw row and frequency, loaded ahead of the block that uses them.
+struct VisPhase {
+  double u, v, w, fc;
+};
+__device__ __forceinline__ VisPhase load_phase(const KernelArgs& a, const SubgridDev& s, int k, float inv_nc) {
+  // (k + 1/2) / nc is at least 1 / (2 nc) from an integer, beyond FP32 rounding for k < 2048
+  const int row = (int)(((float)k + 0.5f) * inv_nc), c = k - row * s.nc;
+  const double* uvw = a.uvw + 3 * s.uvw0;
+  return {gload<double>(uvw, 24 * row), gload<double>(uvw, 24 * row + 8), gload<double>(uvw, 24 * row + 16),
+          gload<double>(a.fc + s.c0, 8 * c)};
+}
+template <int B>
+__device__ __forceinline__ void store_phase(const KernelArgs& a, const SubgridDev& s, const VisPhase& p, bool valid, int k,
+                                            VisBlock<B>* vb) {
   double ku = 0, kv = 0, kw = 0;
   unsigned dw = 0;
-  if (k < n) {
-    const int row = (int)(((float)(k0 + k) + 0.5f) * inv_nc), c = k0 + k - row * s.nc;
-    const double* uvw = a.uvw + 3 * (s.uvw0 + row);
-    const double fc = a.fc[s.c0 + c];
-    ku = (uvw[0] * fc - (s.U0 - a.N / 2) * a.du) * a.lstep;
-    kv = (uvw[1] * fc - (s.V0 - a.N / 2) * a.du) * a.lstep;
-    kw = uvw[2] * fc - s.w0;
+  if (valid) {
+    ku = (p.u * p.fc - (s.U0 - a.N / 2) * a.du) * a.lstep;
+    kv = (p.v * p.fc - (s.V0 - a.N / 2) * a.du) * a.lstep;
+    kw = p.w * p.fc - s.w0;
     dw = pair_of((float)((kw - (double)s.wmid) * (6.283185307179586 / 4096.0)));
   }
   vb->ku_w[k] = {ku, kw};
@@ -123,29 +189,91 @@ __device__ __forceinline__ void stage_vis_phases(const KernelArgs& a, const Subg
   vb->dw[k] = dw;
 }
 
-// beta_k(y) of the workgroup's 32 rows from y0, FP32: [32][kBlkPitch].
-template <int L>
-__device__ __forceinline__ void stage_beta(const VisBlock* vb, const double* axis, int y0, int n8, float2* beta) {
-  const int k = threadIdx.x & (kBlk - 1);
-  if (k >= n8) return;
+// scale beta_k(y) of the workgroup's 32 rows from y0 for the block's first n visibilities,
+// FP32: [32][B + 2] (the pitch shifts each row by four banks: eight rows' 16-byte reads meet
+// no bank twice).
+template <int L, int B>
+__device__ __forceinline__ void stage_beta(const VisBlock<B>* vb, const double* axis, int y0, int n, float scale,
+                                           float2* beta) {
+  static_assert(B == 32 && kThreads == 256 && kRows == 32, "four rows per thread");
+  int tid = threadIdx.x;  // opaque: formed again for each block, not held across it
+  asm volatile("" : "+v"(tid));
+  const int k = tid & 31, y = tid >> 5;
+  if (k >= n) return;
   const double2 kv = vb->kv_w[k];
-#pragma unroll 2
-  for (int y = threadIdx.x / kBlk; y < kRows; y += kThreads / kBlk)
-    beta[y * kBlkPitch + k] = turn_phasor(fma(kv.x, (double)(y0 + y - L / 2), kv.y * axis[y0 + y]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = y + 8 * i;
+    const float2 e = turn_phasor(kv.x, (double)(y0 + r - L / 2), kv.y, axis[y0 + r]);
+    beta[r * (B + 2) + k] = {e.x * scale, e.y * scale};
+  }
+}
+
+// c + a b, fused.
+__device__ __forceinline__ float2 cfma(float2 a, float2 b, float2 c) {
+  return {fmaf(-a.y, b.y, fmaf(a.x, b.x, c.x)), fmaf(a.y, b.x, fmaf(a.x, b.y, c.y))};
+}
+
+// A subgrid pixel's two Jones matrices, taper and cross term.
+struct PixelTerms {
+  vec4 p0, p1, q0, q1;
+  vec2 tc;
+};
+__device__ __forceinline__ PixelTerms load_pixel(const KernelArgs& a, const char* Ap, const char* Aq, unsigned pix) {
+  return {gload<vec4>(Ap, 32 * pix), gload<vec4>(Ap, 32 * pix + 16), gload<vec4>(Aq, 32 * pix),
+          gload<vec4>(Aq, 32 * pix + 16), gload<vec2>(a.taper_cross, 8 * pix)};
+}
+// d += A^H (w E(w_s c) S) B with A = (p0, p1), B = (q0, q1); INV: scaled by 1 / ||A^H B||_F.
+template <bool INV>
+__device__ __forceinline__ void add_corrected(const PixelTerms& x, float wmid, float w, const float2 (&s)[4],
+                                              float (&d)[8]) {
+  const float2 a0 = {x.p0.x, -x.p0.y}, a1 = {x.p0.z, -x.p0.w}, a2 = {x.p1.x, -x.p1.y}, a3 = {x.p1.z, -x.p1.w};  // conj
+  const float2 b0 = {x.q0.x, x.q0.y}, b1 = {x.q0.z, x.q0.w}, b2 = {x.q1.x, x.q1.y}, b3 = {x.q1.z, x.q1.w};
+  w *= x.tc.x;
+  if constexpr (INV) {
+    // ||B_p^H B_q||_F^2 with B_p^H = [[a0, a2], [a1, a3]] (a already conjugated)
+    const float2 m0 = cmul<float>(a0, b0) + cmul<float>(a2, b2), m1 = cmul<float>(a0, b1) + cmul<float>(a2, b3);
+    const float2 m2 = cmul<float>(a1, b0) + cmul<float>(a3, b2), m3 = cmul<float>(a1, b1) + cmul<float>(a3, b3);
+    const float n2 = m0.x * m0.x + m0.y * m0.y + m1.x * m1.x + m1.y * m1.y + m2.x * m2.x + m2.y * m2.y + m3.x * m3.x +
+                     m3.y * m3.y;
+    const float f = w / sqrtf(n2 > 0.0f ? n2 : 1.0f);
+    w = n2 > 0.0f ? f : 0.0f;
+  }
+  // taper and E(w_s c), |w_s c| < 1/2 turn
+  const float ph = wmid * x.tc.y;
+  const float2 e = {w * __builtin_amdgcn_cosf(ph), w * __builtin_amdgcn_sinf(ph)};
+  const float2 s0 = cmul<float>(e, s[0]), s1 = cmul<float>(e, s[1]);
+  const float2 s2 = cmul<float>(e, s[2]), s3 = cmul<float>(e, s[3]);
+  // A_p^H = [[conj a0, conj a2], [conj a1, conj a3]]
+  const float2 t0 = cfma(a2, s2, cmul<float>(a0, s0)), t1 = cfma(a2, s3, cmul<float>(a0, s1));
+  const float2 t2 = cfma(a3, s2, cmul<float>(a1, s0)), t3 = cfma(a3, s3, cmul<float>(a1, s1));
+  const float2 c0 = cfma(t1, b2, cmul<float>(t0, b0)), c1 = cfma(t1, b3, cmul<float>(t0, b1));
+  const float2 c2 = cfma(t3, b2, cmul<float>(t2, b0)), c3 = cfma(t3, b3, cmul<float>(t2, b1));
+  // (added whole: a chain of products onto d would round at the size of the sum four times)
+  d[0] += c0.x; d[1] += c0.y; d[2] += c1.x; d[3] += c1.y;
+  d[4] += c2.x; d[5] += c2.y; d[6] += c3.x; d[7] += c3.y;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(d[i]));  // here, not behind the later pixels
 }
 
 // ------------------------------------------------------------------ gridder
 
-// Gridder LDS: alpha operands, beta, the visibilities [4][kBlkPitch], phases, axis tables.
+// Pixels of a lane whose group sums are held in LDS: at L = 96 the sums and accumulators of
+// all twelve would leave 64 of 256 registers for everything else.
+template <int L>
+constexpr int kLdsPixels = L == 96 ? 5 : 0;
+
+// Gridder LDS: alpha operands, beta, the visibilities [4][kBlk + 2], phases, axis tables.
 template <int L>
 struct GridLds {
   Frag alpha[kBlk / 8][L / 32][2][64];
-  float2 beta[kRows * kBlkPitch];
-  float2 vis[4 * kBlkPitch];
-  VisBlock vb;
+  float2 beta[kRows * (kBlk + 2)];
+  float2 vis[4 * (kBlk + 2)];
+  VisBlock<kBlk> vb;
   double axis[L];
   unsigned b[L];
-  float red[4];
+  float peak;
+  float4 sum[kLdsPixels<L>][2][kThreads];
 };
 
 // One workgroup per (32 rows, group).  Each wave owns 8 rows x 4 polarisations (the 32
@@ -154,9 +282,11 @@ struct GridLds {
 // lane-local and the group's sum stays in registers (a subgrid's image does not go through
 // memory).  Rows are V_k beta_k(y), formed and split by the wave that uses them; columns are
 // alpha_k(x), formed once per workgroup and read from LDS in the operand's lane order.
+// The next block's visibilities and uvw are loaded (into registers) before the products of
+// the current one, across subgrids as well.
 template <int L>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void grid_matrix(const Group g) {
-  constexpr int XT = L / 32, NP = 4;  // column tiles; pixels per lane and tile
+  constexpr int XT = L / 32, NP = 4, NPIX = XT * NP, P0 = kLdsPixels<L>;  // column tiles; pixels per lane
   extern __shared__ unsigned char smem_raw[];
   GridLds<L>& sh = *reinterpret_cast<GridLds<L>*>(smem_raw);
   int64_t local;
@@ -165,9 +295,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (local >= g.total_grp) return;  // padding of the last XCD round (whole workgroup)
   const GroupSlot gs = resolve_group(g, local);
   const KernelArgs& a = gs.a;
-  const float* __restrict__ vis = reinterpret_cast<const float*>(gs.in);
   const bool inv = a.ainvh != nullptr;
-  const float2* At = reinterpret_cast<const float2*>(inv ? a.ainvh : a.aterms);
+  const char* At = static_cast<const char*>(inv ? a.ainvh : a.aterms);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, h = lane >> 5;
   const int y0 = chunk * kRows;
   for (int i = tid; i < L; i += kThreads) {
@@ -176,284 +305,366 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
   // operand row of this lane: polarisation q of row yl of the wave's eight
   const int q = col & 3, yl = wave * 8 + (col >> 2);
+  const unsigned pix0 = (y0 + wave * 8 + h) * L + col;  // pixel (t, p) is 2 p rows and 32 t columns on
 
-  float sum[XT][NP][8];
+  float sum[NPIX - P0][8];
 #pragma unroll
-  for (int t = 0; t < XT; ++t)
+  for (int p = P0; p < NPIX; ++p)
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+    for (int i = 0; i < 8; ++i) sum[p - P0][i] = 0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sum[t][p][i] = 0;
+  for (int p = 0; p < P0; ++p) sh.sum[p][0][tid] = sh.sum[p][1][tid] = {0, 0, 0, 0};
 
-  for (int64_t si = gs.sb; si < gs.se; ++si) {
-    const SubgridDev s = load_uniform(a.sg + si);
+  // Block loads: wave 0 one half (two polarisations) of a visibility per lane, wave 1 the uvw
+  // and frequency of one.
+  static_assert(2 * kBlk == 64, "one wave stages a block");
+  VisPhase next;
+  vec4 next_v;
+  auto prefetch = [&](const SubgridDev& s, int k0) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     const int nv = s.nt * s.nc;
     const float inv_nc = 1.0f / (float)s.nc;
-    // half i & 1 (polarisations 2 (i & 1) and the next) of the subgrid's visibility i >> 1;
-    // (k + 1/2) / nc is at least 1 / (2 nc) from an integer, beyond FP32 rounding for
-    // k < 2048.  A folded sub-table is read as V^H.
-    auto fetch = [&](int i) -> float4 {
-      const int k = i >> 1, row = (int)(((float)k + 0.5f) * inv_nc), c = k - row * s.nc;
-      const float4* src = reinterpret_cast<const float4*>(vis) + (s.vis0 + (int64_t)row * a.nc_total + c) * 2;
-      if (s.fold) {
-        const float4 h0 = src[0], h1 = src[1];
-        return (i & 1) ? float4{h0.z, -h0.w, h1.z, -h1.w} : float4{h0.x, -h0.y, h1.x, -h1.y};
+    if (tid < 2 * kBlk) {
+      const int k = k0 + (tid >> 1);
+      next_v = {0, 0, 0, 0};
+      if (k < nv) {
+        const int row = (int)(((float)k + 0.5f) * inv_nc), c = k - row * s.nc;
+        const char* src = static_cast<const char*>(gs.in) + s.vis0 * 32;
+        const unsigned off = ((unsigned)row * (unsigned)a.nc_total + (unsigned)c) * 32u;
+        if (s.fold) {  // a folded sub-table is read as V^H
+          const vec4 h0 = gload<vec4>(src, off), h1 = gload<vec4>(src, off + 16);
+          next_v = (tid & 1) ? vec4{h0.z, -h0.w, h1.z, -h1.w} : vec4{h0.x, -h0.y, h1.x, -h1.y};
+        } else {
+          next_v = gload<vec4>(src, off + 16 * (tid & 1));
+        }
       }
-      return src[i & 1];
-    };
-    float m = 0;
-    float4 first = {0, 0, 0, 0};
-    for (int i = tid; i < 2 * nv; i += kThreads) {
-      const float4 v = fetch(i);
-      if (i == tid) first = v;
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    } else if (tid < 3 * kBlk) {
+      const int k = k0 + tid - 2 * kBlk;
+      if (k < nv) next = load_phase(a, s, k, inv_nc);
     }
-    m = wave_max(m);
-    if (lane == 0) sh.red[wave] = m;
-    acc16 re[XT], im[XT];
-#pragma unroll
-    for (int t = 0; t < XT; ++t) re[t] = im[t] = acc16{0};
-    float scale = 1, unscale = 1;
+  };
 
-    for (int k0 = 0; k0 < nv; k0 += kBlk) {
-      const int n = min(kBlk, nv - k0), n8 = (n + 7) & ~7;
-      __syncthreads();  // the previous block is no longer read; the maxima are in
-      if (k0 == 0) {
-        fit_scale(fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3])), scale, unscale);
+  acc16 re[XT], im[XT];
+  // Row operands of step ks: W_k = V_k beta_k(y) for the lane's four visibilities, rows
+  // (W_re, -W_im) for the real tile and (W_im, W_re) for the imaginary one, each hi and lo;
+  // g: 2 pi d_k b(y) of the w series, whose first term takes rows times -i g and columns
+  // times b(x) (the tables hold 64 b and d 2^-12 of its value).
+  struct Rows {
+    Frag rh, rl, ih, il;
+    unsigned g[4];
+  };
+  const unsigned by = a.axis_b[y0 + yl];
+  unsigned bx[XT];
+#pragma unroll
+  for (int t = 0; t < XT; ++t) bx[t] = a.axis_b[t * 32 + col];
+  auto rows = [&](int ks) -> Rows {
+    Rows r;
+    const int k = 8 * ks + 4 * h;
+    // (16-byte aligned: even places of even rows)
+    const float4* vp = reinterpret_cast<const float4*>(__builtin_assume_aligned(&sh.vis[q * (kBlk + 2) + k], 16));
+    const float4* bp = reinterpret_cast<const float4*>(__builtin_assume_aligned(&sh.beta[yl * (kBlk + 2) + k], 16));
+    const float4 v01 = vp[0], v23 = vp[1], b01 = bp[0], b23 = bp[1];
+    const float2 vs[4] = {{v01.x, v01.y}, {v01.z, v01.w}, {v23.x, v23.y}, {v23.z, v23.w}};
+    const float2 bs[4] = {{b01.x, b01.y}, {b01.z, b01.w}, {b23.x, b23.y}, {b23.z, b23.w}};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float2 v = vs[i], b = bs[i];
+      split(fmaf(-v.y, b.y, v.x * b.x), fmaf(-v.y, b.x, -(v.x * b.y)), r.rh.w[i], r.rl.w[i]);
+      r.ih.w[i] = rot90(r.rh.w[i]);
+      r.il.w[i] = rot90(r.rl.w[i]);
+      r.g[i] = pk_mul(sh.vb.dw[k + i], by);
+    }
+    return r;
+  };
+  // Products of step ks with the series' first term; order > 1 (wide fields): further terms j,
+  // rows times (-i 2 pi d_k b(y))^j / j!, columns times b(x)^j.
+  auto products = [&](int ks, int order) {
+    Frag bh[XT], bl[XT];
+#pragma unroll
+    for (int t = 0; t < XT; ++t) {
+      bh[t] = sh.alpha[ks][t][0][lane];
+      bl[t] = sh.alpha[ks][t][1][lane];
+    }
+    const Rows r = rows(ks);
+    Frag nr, ni;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      nr.w[i] = pk_mul(r.ih.w[i], r.g[i]);
+      ni.w[i] = pk_mul_neg(r.rh.w[i], r.g[i]);
+    }
+#pragma unroll
+    for (int t = 0; t < XT; ++t) {
+      re[t] = mfma(r.rh, bh[t], re[t]);
+      im[t] = mfma(r.ih, bh[t], im[t]);
+      re[t] = mfma(r.rh, bl[t], re[t]);
+      im[t] = mfma(r.ih, bl[t], im[t]);
+      re[t] = mfma(r.rl, bh[t], re[t]);
+      im[t] = mfma(r.il, bh[t], im[t]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bh[t].w[i] = pk_mul(bh[t].w[i], bx[t]);
+      re[t] = mfma(nr, bh[t], re[t]);
+      im[t] = mfma(ni, bh[t], im[t]);
+    }
+#pragma unroll 1
+    for (int j = 2; j <= order; ++j) {
+      const unsigned f = pair_of(1.0f / (float)j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned gk = pk_mul(r.g[i], f), n = pk_mul(ni.w[i], gk);
+        ni.w[i] = pk_mul_neg(nr.w[i], gk);
+        nr.w[i] = n;
       }
-      stage_vis_phases(a, s, k0, n, inv_nc, &sh.vb);
-      if (tid < 2 * kBlk) {
-        const int k = tid >> 1, p = 2 * (tid & 1);
-        float4 v = {0, 0, 0, 0};
-        if (k < n) v = k0 == 0 ? first : fetch(2 * k0 + tid);
-        sh.vis[p * kBlkPitch + k] = {v.x * scale, v.y * scale};
-        sh.vis[(p + 1) * kBlkPitch + k] = {v.z * scale, v.w * scale};
+#pragma unroll
+      for (int t = 0; t < XT; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bh[t].w[i] = pk_mul(bh[t].w[i], bx[t]);
+        re[t] = mfma(nr, bh[t], re[t]);
+        im[t] = mfma(ni, bh[t], im[t]);
       }
-      __syncthreads();
-      for (int id = tid; id < L * (n8 / 4); id += kThreads) {
-        const int x = id % L, kg = id / L;
+    }
+  };
+  float scale = 0, unscale = 0;
+  SubgridDev s = load_uniform(a.sg + gs.sb);
+  int64_t si = gs.sb;
+  int k0 = 0;
+  prefetch(s, 0);
+  while (true) {
+    const int nv = s.nt * s.nc;
+    const int n = min(kBlk, nv - k0), n8 = (n + 7) & ~7;
+    // an opaque copy of the thread index: what derives from it is cheaper to form again for
+    // each block than to hold in registers through the products
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    __syncthreads();  // the previous block's operands are no longer read
+    if (tid < 2 * kBlk) {
+      const int k = tid >> 1, p = 2 * (tid & 1);
+      const vec4 v = next_v;
+      sh.vis[p * (kBlk + 2) + k] = {v.x, v.y};
+      sh.vis[(p + 1) * (kBlk + 2) + k] = {v.z, v.w};
+      const float m = wave_max(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+      if (lane == 0) sh.peak = m;
+    } else if (tid < 3 * kBlk) {
+      store_phase(a, s, next, k0 + tid - 2 * kBlk < nv, tid - 2 * kBlk, &sh.vb);
+    }
+    __syncthreads();
+    // the data's scale: a power of two that fits the subgrid's largest value so far (folded
+    // into beta); sums under an earlier, larger one are brought to it
+    float sc, un;
+    fit_scale(sh.peak, sc, un);
+    if (k0 == 0) {
+      scale = sc;
+      unscale = un;
+#pragma unroll
+      for (int t = 0; t < XT; ++t) re[t] = im[t] = acc16{0};
+    } else if (sc < scale) {
+      const float f = sc * unscale;
+#pragma unroll
+      for (int t = 0; t < XT; ++t) {
+        re[t] *= f;
+        im[t] *= f;
+      }
+      scale = sc;
+      unscale = un;
+    }
+    // four visibilities per thread (kg), one column of each tile
+    const int kg = tid >> 5, xc = tid & 31;
+    if (4 * kg < n8) {
+      double2 kuw[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kuw[i] = sh.vb.ku_w[4 * kg + i];
+#pragma unroll
+      for (int t = 0; t < XT; ++t) {
+        const int x = 32 * t + xc;
         const double dx = (double)(x - L / 2), ax = sh.axis[x];
         Frag fh, fl;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const double2 kuw = sh.vb.ku_w[4 * kg + i];
-          const float2 e = turn_phasor(fma(kuw.x, dx, kuw.y * ax));
+          const float2 e = turn_phasor(kuw[i].x, dx, kuw[i].y, ax);
           split(e.x, e.y, fh.w[i], fl.w[i]);
         }
-        sh.alpha[kg >> 1][x >> 5][0][32 * (kg & 1) + (x & 31)] = fh;
-        sh.alpha[kg >> 1][x >> 5][1][32 * (kg & 1) + (x & 31)] = fl;
+        Frag* f = &sh.alpha[kg >> 1][t][0][32 * (kg & 1) + xc];
+        f[0] = fh;
+        f[64] = fl;
       }
-      stage_beta<L>(&sh.vb, sh.axis, y0, n8, sh.beta);
-      __syncthreads();
+    }
+    stage_beta<L>(&sh.vb, sh.axis, y0, n8, scale, sh.beta);
+    // the next block: of this subgrid, or the next one's first
+    const SubgridDev cur = s;
+    const bool last = k0 + kBlk >= nv, done = last && si + 1 == gs.se;
+    k0 = last ? 0 : k0 + kBlk;
+    if (last && !done) s = load_uniform(a.sg + ++si);
+    if (!last) prefetch(s, k0);
+    __syncthreads();
 
-      for (int ks = 0; ks < n8 / 8; ++ks) {
-        // W_k = V_k beta_k(y) for the lane's four visibilities: rows (W_re, -W_im) for the
-        // real tile and (W_im, W_re) for the imaginary one
-        const int k = 8 * ks + 4 * h;
-        Frag rh, rl, ih, il;
+#pragma unroll 1
+    for (int ks = 0; ks < n8 / 8; ++ks) products(ks, cur.order);
+    if (!last) continue;
+    // Jones correction of this subgrid, A_p^H S A_q, tapered and added to the group's sum;
+    // a pixel's terms are loaded while the one before is computed
+    const char* Ap = At + (int64_t)cur.ap * L * L * 32;
+    const char* Aq = At + (int64_t)cur.aq * L * L * 32;
+    auto epilogue = [&](auto inverse) {
+      unsigned pe = pix0;
+      asm volatile("" : "+v"(pe));  // the pixels' offsets are not worth holding across subgrids
+      PixelTerms px[kAhead];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float2 w = cmul<float>(sh.vis[q * kBlkPitch + k + i], sh.beta[yl * kBlkPitch + k + i]);
-          unsigned hi, lo;
-          split(w.x, w.y, hi, lo);
-          rh.w[i] = hi ^ kNegHigh;
-          rl.w[i] = lo ^ kNegHigh;
-          ih.w[i] = swap_halves(hi);
-          il.w[i] = swap_halves(lo);
+      for (int i = 0; i < kAhead; ++i) px[i] = load_pixel(a, Ap, Aq, pe + 2 * (i % NP) * L + 32 * (i / NP));
+#pragma unroll
+      for (int i = 0; i < NPIX; ++i) {
+        const int t = i / NP, p = i % NP, n = i + kAhead;
+        const float2 sv[4] = {{re[t][4 * p], im[t][4 * p]}, {re[t][4 * p + 1], im[t][4 * p + 1]},
+                              {re[t][4 * p + 2], im[t][4 * p + 2]}, {re[t][4 * p + 3], im[t][4 * p + 3]}};
+        if (i < P0) {
+          const float4 o0 = sh.sum[i][0][tid], o1 = sh.sum[i][1][tid];
+          float d[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, unscale, sv, d);
+          sh.sum[i][0][tid] = {d[0], d[1], d[2], d[3]};
+          sh.sum[i][1][tid] = {d[4], d[5], d[6], d[7]};
+        } else {
+          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, unscale, sv, sum[i - P0]);
         }
-#pragma unroll
-        for (int t = 0; t < XT; ++t) {
-          const Frag bh = sh.alpha[ks][t][0][lane], bl = sh.alpha[ks][t][1][lane];
-          re[t] = mfma(rh, bh, re[t]);
-          im[t] = mfma(ih, bh, im[t]);
-          re[t] = mfma(rh, bl, re[t]);
-          im[t] = mfma(ih, bl, im[t]);
-          re[t] = mfma(rl, bh, re[t]);
-          im[t] = mfma(il, bh, im[t]);
-        }
-        if (s.order > 0) {
-          // w series: rows times -i 2 pi d_k b(y) / j, columns times b(x), per order j (the
-          // b tables hold 64 b and d 2^-12 of its value)
-          const unsigned by = sh.b[y0 + yl];
-          unsigned bx[XT], gk[4];
-#pragma unroll
-          for (int t = 0; t < XT; ++t) bx[t] = sh.b[t * 32 + col];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) gk[i] = pk_mul(sh.vb.dw[k + i], by);
-          for (int j = 1;; ++j) {
-            Frag nr, ni;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              nr.w[i] = pk_mul(ih.w[i], gk[i]);
-              ni.w[i] = pk_mul(rh.w[i] ^ kNegBoth, gk[i]);
-            }
-            rh = nr;
-            ih = ni;
-#pragma unroll
-            for (int t = 0; t < XT; ++t) {
-              Frag b = sh.alpha[ks][t][0][lane];
-#pragma unroll
-              for (int i = 0; i < 4; ++i) b.w[i] = pk_mul(b.w[i], bx[t]);
-              re[t] = mfma(rh, b, re[t]);
-              im[t] = mfma(ih, b, im[t]);
-            }
-            if (j == s.order) break;
-            const unsigned f = pair_of((float)j / (float)(j + 1));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) gk[i] = pk_mul(gk[i], f);
-#pragma unroll
-            for (int t = 0; t < XT; ++t) bx[t] = pk_mul(bx[t], sh.b[t * 32 + col]);
-          }
-        }
+        asm volatile("" : "+v"(pe));
+        if (n < NPIX) px[i % kAhead] = load_pixel(a, Ap, Aq, pe + 2 * (n % NP) * L + 32 * (n / NP));
+        if (i == 5 % NPIX && !done) prefetch(s, 0);  // behind pixels whose accumulators are free
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-    // Jones correction of this subgrid, A_p^H S A_q, tapered and added to the group's sum
-#pragma unroll
-    for (int t = 0; t < XT; ++t) {
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        const int pix = (y0 + wave * 8 + 2 * p + h) * L + t * 32 + col;
-        const float2* Ap = At + ((int64_t)s.ap * L * L + pix) * 4;
-        const float2* Aq = At + ((int64_t)s.aq * L * L + pix) * 4;
-        float2 a0 = Ap[0], a1 = Ap[1], a2 = Ap[2], a3 = Ap[3];
-        a0.y = -a0.y; a1.y = -a1.y; a2.y = -a2.y; a3.y = -a3.y;  // conj
-        float2 b0 = Aq[0], b1 = Aq[1], b2 = Aq[2], b3 = Aq[3];
-        const float2 tc = a.taper_cross[pix];
-        float w = tc.x * unscale;
-        if (inv) {
-          // ||B_p^H B_q||_F^2 with B_p^H = [[a0, a2], [a1, a3]] (a already conjugated)
-          const float2 m0 = cmul<float>(a0, b0) + cmul<float>(a2, b2), m1 = cmul<float>(a0, b1) + cmul<float>(a2, b3);
-          const float2 m2 = cmul<float>(a1, b0) + cmul<float>(a3, b2), m3 = cmul<float>(a1, b1) + cmul<float>(a3, b3);
-          const float n2 = m0.x * m0.x + m0.y * m0.y + m1.x * m1.x + m1.y * m1.y + m2.x * m2.x + m2.y * m2.y +
-                           m3.x * m3.x + m3.y * m3.y;
-          w = n2 > 0.0f ? w / sqrtf(n2) : 0.0f;
-        }
-        // taper and E(w_s c), |w_s c| < 1/2 turn
-        const float ph = s.wmid * tc.y;
-        const float2 e = {w * __builtin_amdgcn_cosf(ph), w * __builtin_amdgcn_sinf(ph)};
-        const float2 s0 = cmul<float>(e, float2{re[t][4 * p], im[t][4 * p]});
-        const float2 s1 = cmul<float>(e, float2{re[t][4 * p + 1], im[t][4 * p + 1]});
-        const float2 s2 = cmul<float>(e, float2{re[t][4 * p + 2], im[t][4 * p + 2]});
-        const float2 s3 = cmul<float>(e, float2{re[t][4 * p + 3], im[t][4 * p + 3]});
-        // A_p^H = [[conj a0, conj a2], [conj a1, conj a3]]
-        const float2 t0 = cmul<float>(a0, s0) + cmul<float>(a2, s2);
-        const float2 t1 = cmul<float>(a0, s1) + cmul<float>(a2, s3);
-        const float2 t2 = cmul<float>(a1, s0) + cmul<float>(a3, s2);
-        const float2 t3 = cmul<float>(a1, s1) + cmul<float>(a3, s3);
-        const float2 c0 = cmul<float>(t0, b0) + cmul<float>(t1, b2), c1 = cmul<float>(t0, b1) + cmul<float>(t1, b3);
-        const float2 c2 = cmul<float>(t2, b0) + cmul<float>(t3, b2), c3 = cmul<float>(t2, b1) + cmul<float>(t3, b3);
-        float* d = sum[t][p];
-        d[0] += c0.x; d[1] += c0.y; d[2] += c1.x; d[3] += c1.y;
-        d[4] += c2.x; d[5] += c2.y; d[6] += c3.x; d[7] += c3.y;
-      }
-    }
+    };
+    if (inv) epilogue(std::true_type());
+    else epilogue(std::false_type());
+    if (done) break;
   }
 
-  float2* out = reinterpret_cast<float2*>(g.scratch) + local * 4 * L * L;
+  char* out = static_cast<char*>(g.scratch) + local * 4 * L * L * 8;
   // Stokes-I grid: I = (XX + YY) / 2 of the corrected image, plane 0 only
   const float fi = gs.adjoint ? 1.0f : 0.5f;
 #pragma unroll
-  for (int t = 0; t < XT; ++t) {
+  for (int i = 0; i < NPIX; ++i) {
+    const unsigned pix = pix0 + 2 * (i % NP) * L + 32 * (i / NP);
+    float d[8];
+    if (i < P0) {
+      const float4 o0 = sh.sum[i][0][tid], o1 = sh.sum[i][1][tid];
+      d[0] = o0.x; d[1] = o0.y; d[2] = o0.z; d[3] = o0.w;
+      d[4] = o1.x; d[5] = o1.y; d[6] = o1.z; d[7] = o1.w;
+    } else {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int pix = (y0 + wave * 8 + 2 * p + h) * L + t * 32 + col;
-      const float* d = sum[t][p];
-      if (a.npol == 1) {
-        out[pix] = {(d[0] + d[6]) * fi, (d[1] + d[7]) * fi};
-      } else {
+      for (int k = 0; k < 8; ++k) d[k] = sum[i - P0][k];
+    }
+    if (a.npol == 1) {
+      gstore(out, 8 * pix, vec2{(d[0] + d[6]) * fi, (d[1] + d[7]) * fi});
+    } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) out[k * L * L + pix] = {d[2 * k], d[2 * k + 1]};
-      }
+      for (int k = 0; k < 4; ++k) gstore(out, 8 * (k * L * L + pix), vec2{d[2 * k], d[2 * k + 1]});
     }
   }
 }
 
 // ------------------------------------------------------------------ degridder
 
-// Degridder LDS: alpha operands [tile of 32 visibilities][x step], beta, phases, the waves'
-// partial visibilities, axis tables.  While a pass's image is laid out, the first part holds
-// 32 columns of each wave's rows: [hi, lo][wave][row][kLayPitch].
+// Visibilities per degridder block: one tile of the matrix product.
+constexpr int kDegBlk = 32;
+// Degridder LDS: alpha operands [x step][(re, im) hi, lo; (-im, re) hi, lo], beta, phases, the
+// waves' partial visibilities, axis tables.  While a pass's image is laid out, the first part
+// holds 32 columns of each wave's rows: [hi, lo][wave][row][kLayPitch].
 constexpr int kLayPitch = 36;
 template <int L>
 struct DegridLds {
   union {
-    Frag alpha[kBlk / 32][L / 8][2][64];
+    Frag alpha[L / 8][4][64];
     unsigned lay[2][4][32][kLayPitch];
   };
-  float2 beta[kRows * kBlkPitch];
-  VisBlock vb;
-  float2 part[4][kBlk * 4];
+  float2 beta[kRows * (kDegBlk + 2)];
+  VisBlock<kDegBlk> vb;
+  float2 part[4][kDegBlk * 4];
   double axis[L];
-  unsigned b[L];
+  alignas(16) unsigned b[L];  // (-64 b, 64 b) pairs
 };
 
 // One workgroup per subgrid, 32 rows of the subgrid at a time.  Each wave corrects its
 // 8 rows of the group image (A_p S A_q^H, taper, E(-w_s c)), splits them and keeps them in
 // registers as the operand [x][(row, polarisation)] for all visibilities of the pass;
-// alpha_k(x) is formed by the workgroup, 64 visibilities at a time, as the other operand.
-// A tile's 32 visibilities x 8 rows x 4 polarisations are multiplied by conj(beta_k(y)) and
-// summed over the rows across lanes; the waves' sums meet in LDS and are added to the output
-// in wave order (deterministic, no atomics).
+// alpha_k(x) is formed by the workgroup, 32 visibilities at a time, as the other operand, in
+// the two arrangements that give the real and the imaginary part.  A block's
+// 32 visibilities x 8 rows x 4 polarisations are multiplied by conj(beta_k(y)) and summed over
+// the rows across lanes; the waves' sums meet in LDS and are added to the output in wave
+// order (deterministic, no atomics).
 template <int L>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void degrid_matrix(const Group g) {
-  constexpr int XT = L / 32, NP = 4, KS = L / 8;
+  constexpr int XT = L / 32, NP = 4, KS = L / 8, B = kDegBlk;
   extern __shared__ unsigned char smem_raw[];
   DegridLds<L>& sh = *reinterpret_cast<DegridLds<L>*>(smem_raw);
   const int64_t local = degrid_slot(blockIdx.x, g.total_sg);
   const Slot sl = resolve(g, local);
   const KernelArgs& a = sl.a;
   const SubgridDev& s = sl.s;
-  float* __restrict__ vis = reinterpret_cast<float*>(sl.out);
-  const float2* img = reinterpret_cast<const float2*>(g.scratch) + sl.img_slot * 4 * L * L;
-  const float2* At = reinterpret_cast<const float2*>(a.aterms);
+  char* vis = static_cast<char*>(sl.out) + s.vis0 * 32;
+  const char* img = static_cast<const char*>(g.scratch) + sl.img_slot * 4 * L * L * 8;
+  const char* Ap = static_cast<const char*>(a.aterms) + (int64_t)s.ap * L * L * 32;
+  const char* Aq = static_cast<const char*>(a.aterms) + (int64_t)s.aq * L * L * 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, h = lane >> 5;
   const int nv = s.nt * s.nc;
   const float inv_nc = 1.0f / (float)s.nc;
   for (int i = tid; i < L; i += kThreads) {
     sh.axis[i] = a.axis_n1[i];
-    sh.b[i] = a.axis_b[i];
+    sh.b[i] = a.axis_b[i] ^ kNegLow;
   }
   // operand column of this lane: polarisation q of row yl of the wave's eight
   const int q = col & 3, yl = wave * 8 + (col >> 2);
+  VisPhase next;
+  if (tid < B && tid < nv) next = load_phase(a, s, tid, inv_nc);
 
   for (int y0 = 0; y0 < L; y0 += kRows) {
     // the wave's rows, corrected: lane (col, h) takes column x = 32 t + col of rows 2 p + h
     float c[XT][NP][8];
     float m = 0;
+    unsigned pix0 = (y0 + wave * 8 + h) * L + col;
+    struct Pixel {
+      PixelTerms x;
+      vec2 s[4];
+    };
+    auto load = [&](int i) -> Pixel {
+      const unsigned pix = pix0 + 2 * (i % NP) * L + 32 * (i / NP);
+      return {load_pixel(a, Ap, Aq, pix),
+              {gload<vec2>(img, 8 * pix), gload<vec2>(img, 8 * (L * L + pix)), gload<vec2>(img, 8 * (2 * L * L + pix)),
+               gload<vec2>(img, 8 * (3 * L * L + pix))}};
+    };
+    constexpr int kAhead = 3;  // with their image values
+    Pixel px[kAhead];
 #pragma unroll
-    for (int t = 0; t < XT; ++t) {
+    for (int i = 0; i < kAhead; ++i) px[i] = load(i);
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        const int pix = (y0 + wave * 8 + 2 * p + h) * L + t * 32 + col;
-        const float2* Ap = At + ((int64_t)s.ap * L * L + pix) * 4;
-        const float2* Aq = At + ((int64_t)s.aq * L * L + pix) * 4;
-        const float2 a0 = Ap[0], a1 = Ap[1], a2 = Ap[2], a3 = Ap[3];
-        float2 b0 = Aq[0], b1 = Aq[1], b2 = Aq[2], b3 = Aq[3];
-        b0.y = -b0.y; b1.y = -b1.y; b2.y = -b2.y; b3.y = -b3.y;  // conj
-        const float2 tc = a.taper_cross[pix];
-        const float ph = s.wmid * tc.y;
-        const float2 e = {tc.x * __builtin_amdgcn_cosf(ph), -tc.x * __builtin_amdgcn_sinf(ph)};
-        const float2 s0 = cmul<float>(e, img[pix]), s1 = cmul<float>(e, img[L * L + pix]);
-        const float2 s2 = cmul<float>(e, img[2 * L * L + pix]), s3 = cmul<float>(e, img[3 * L * L + pix]);
-        const float2 t0 = cmul<float>(a0, s0) + cmul<float>(a1, s2);
-        const float2 t1 = cmul<float>(a0, s1) + cmul<float>(a1, s3);
-        const float2 t2 = cmul<float>(a2, s0) + cmul<float>(a3, s2);
-        const float2 t3 = cmul<float>(a2, s1) + cmul<float>(a3, s3);
-        // A_q^H = [[conj b0, conj b2], [conj b1, conj b3]]
-        const float2 r0 = cmul<float>(t0, b0) + cmul<float>(t1, b1), r1 = cmul<float>(t0, b2) + cmul<float>(t1, b3);
-        const float2 r2 = cmul<float>(t2, b0) + cmul<float>(t3, b1), r3 = cmul<float>(t2, b2) + cmul<float>(t3, b3);
-        float* d = c[t][p];
-        d[0] = r0.x; d[1] = r0.y; d[2] = r1.x; d[3] = r1.y;
-        d[4] = r2.x; d[5] = r2.y; d[6] = r3.x; d[7] = r3.y;
+    for (int i = 0; i < XT * NP; ++i) {
+      const PixelTerms x = px[i % kAhead].x;
+      vec2 sv[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(d[i]));
+      for (int k = 0; k < 4; ++k) sv[k] = px[i % kAhead].s[k];
+      asm volatile("" : "+v"(pix0));  // loads stay this far ahead of their use
+      if (i + kAhead < XT * NP) px[i % kAhead] = load(i + kAhead);
+      const float2 a0 = {x.p0.x, x.p0.y}, a1 = {x.p0.z, x.p0.w}, a2 = {x.p1.x, x.p1.y}, a3 = {x.p1.z, x.p1.w};
+      const float2 b0 = {x.q0.x, -x.q0.y}, b1 = {x.q0.z, -x.q0.w}, b2 = {x.q1.x, -x.q1.y}, b3 = {x.q1.z, -x.q1.w};
+      const float ph = s.wmid * x.tc.y;
+      const float2 e = {x.tc.x * __builtin_amdgcn_cosf(ph), -x.tc.x * __builtin_amdgcn_sinf(ph)};
+      const float2 s0 = cmul<float>(e, float2{sv[0].x, sv[0].y}), s1 = cmul<float>(e, float2{sv[1].x, sv[1].y});
+      const float2 s2 = cmul<float>(e, float2{sv[2].x, sv[2].y}), s3 = cmul<float>(e, float2{sv[3].x, sv[3].y});
+      const float2 t0 = cfma(a1, s2, cmul<float>(a0, s0)), t1 = cfma(a1, s3, cmul<float>(a0, s1));
+      const float2 t2 = cfma(a3, s2, cmul<float>(a2, s0)), t3 = cfma(a3, s3, cmul<float>(a2, s1));
+      // A_q^H = [[conj b0, conj b2], [conj b1, conj b3]]
+      const float2 r0 = cfma(t1, b1, cmul<float>(t0, b0)), r1 = cfma(t1, b3, cmul<float>(t0, b2));
+      const float2 r2 = cfma(t3, b1, cmul<float>(t2, b0)), r3 = cfma(t3, b3, cmul<float>(t2, b2));
+      float* d = c[i / NP][i % NP];
+      d[0] = r0.x; d[1] = r0.y; d[2] = r1.x; d[3] = r1.y;
+      d[4] = r2.x; d[5] = r2.y; d[6] = r3.x; d[7] = r3.y;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        asm volatile("" : "+v"(d[k]));
+        m = fmaxf(m, fabsf(d[k]));
       }
     }
     float scale, unscale;
     fit_scale(wave_max(m), scale, unscale);
     __syncthreads();  // the previous pass's operands are no longer read
     // operand order: lane (col, h) holds row (yl, q), columns 8 ks + 4 h + 0 .. 3
-    Frag ih[KS], il[KS];
+    Frag sh_[KS], sl_[KS];
 #pragma unroll
     for (int t = 0; t < XT; ++t) {
       __builtin_amdgcn_wave_barrier();
@@ -470,121 +681,150 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        ih[4 * t + i] = *reinterpret_cast<const Frag*>(&sh.lay[0][wave][col][8 * i + 4 * h]);
-        il[4 * t + i] = *reinterpret_cast<const Frag*>(&sh.lay[1][wave][col][8 * i + 4 * h]);
+        sh_[4 * t + i] = *reinterpret_cast<const Frag*>(&sh.lay[0][wave][col][8 * i + 4 * h]);
+        sl_[4 * t + i] = *reinterpret_cast<const Frag*>(&sh.lay[1][wave][col][8 * i + 4 * h]);
       }
     }
 
-    for (int k0 = 0; k0 < nv; k0 += kBlk) {
-      const int n = min(kBlk, nv - k0);
+    for (int k0 = 0; k0 < nv; k0 += B) {
+      const int n = min(B, nv - k0);
+      int tid = threadIdx.x;  // opaque, as in the gridder
+      asm volatile("" : "+v"(tid));
       __syncthreads();  // operands (or the laid-out image) and partial sums no longer read
-      stage_vis_phases(a, s, k0, n, inv_nc, &sh.vb);
-      __syncthreads();
-      const int tiles = (n + 31) / 32;
-      for (int id = tid; id < (L / 4) * 32 * tiles; id += kThreads) {
-        // lane order of the operand: visibility id & 31 of a tile, columns 4 xg .. 4 xg + 3
-        const int k = id & 31, xg = (id >> 5) % (L / 4), tile = (id >> 5) / (L / 4);
-        const double2 kuw = sh.vb.ku_w[32 * tile + k];
-        Frag fh, fl;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int x = 4 * xg + i;
-          const float2 e = turn_phasor(fma(kuw.x, (double)(x - L / 2), kuw.y * sh.axis[x]));
-          split(e.x, e.y, fh.w[i], fl.w[i]);
-        }
-        sh.alpha[tile][xg >> 1][0][32 * (xg & 1) + k] = fh;
-        sh.alpha[tile][xg >> 1][1][32 * (xg & 1) + k] = fl;
+      if (tid < B) {
+        store_phase(a, s, next, tid < n, tid, &sh.vb);
+        // the next block's phases (the next pass starts over)
+        const int k = k0 + B < nv ? k0 + B + tid : tid;
+        if (k < nv) next = load_phase(a, s, k, inv_nc);
       }
-      stage_beta<L>(&sh.vb, sh.axis, y0, 32 * tiles, sh.beta);
       __syncthreads();
-
-      for (int tile = 0; tile < tiles; ++tile) {
-        // sum over x of conj(alpha) S': rows (alpha_re, alpha_im), columns (S_re, S_im) for
-        // the real tile and (S_im, -S_re) for the imaginary one
-        acc16 tr = acc16{0}, ti = acc16{0};
-        const unsigned by = sh.b[y0 + yl], dw = sh.vb.dw[32 * tile + col];
+      {
+        // lane order of the operand: one visibility per thread, columns 4 xg .. 4 xg + 3
+        const int k = tid & 31;
+        const double2 kuw = sh.vb.ku_w[k];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const Frag ah = sh.alpha[tile][ks][0][lane], al = sh.alpha[tile][ks][1][lane];
-          Frag jh, jl;
+        for (int t = 0; t < XT; ++t) {
+          const int xg = (tid >> 5) + 8 * t;
+          Frag rh, rl, jh, jl;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            jh.w[i] = swap_halves(ih[ks].w[i]) ^ kNegHigh;
-            jl.w[i] = swap_halves(il[ks].w[i]) ^ kNegHigh;
+            const int x = 4 * xg + i;
+            const float2 e = turn_phasor(kuw.x, (double)(x - L / 2), kuw.y, sh.axis[x]);
+            split(e.x, e.y, rh.w[i], rl.w[i]);
+            jh.w[i] = rot90(rh.w[i]);
+            jl.w[i] = rot90(rl.w[i]);
           }
-          tr = mfma(ah, ih[ks], tr);
-          ti = mfma(ah, jh, ti);
-          tr = mfma(ah, il[ks], tr);
-          ti = mfma(ah, jl, ti);
-          tr = mfma(al, ih[ks], tr);
-          ti = mfma(al, jh, ti);
-          if (s.order > 0) {
-            // w series, conjugated: rows times 2 pi d_k / j, columns times i b(x) b(y)
-            Frag ar = ah, cr = ih[ks], ci = jh;
-            unsigned bb[4], f = dw;
-            const Frag bx = {sh.b[8 * ks + 4 * h], sh.b[8 * ks + 4 * h + 1], sh.b[8 * ks + 4 * h + 2],
-                             sh.b[8 * ks + 4 * h + 3]};
+          Frag* f = &sh.alpha[xg >> 1][0][32 * (xg & 1) + k];
+          f[0] = rh;
+          f[64] = rl;
+          f[128] = jh;
+          f[192] = jl;
+        }
+      }
+      stage_beta<L>(&sh.vb, sh.axis, y0, B, 1.0f, sh.beta);
+      __syncthreads();
+
+      // sum over x of conj(alpha) S': columns (S_re, S_im), rows (alpha_re, alpha_im) for the
+      // real tile and (-alpha_im, alpha_re) for the imaginary one; ur, ui: the w series
+      // without the factor 2 pi d_k b(y) of its terms, the first from columns i b(x) S'
+      acc16 tr = acc16{0}, ti = acc16{0}, ur = acc16{0}, ui = acc16{0}, pr = acc16{0}, pi = acc16{0};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) bb[i] = pk_mul(bx.w[i], by);
-            for (int j = 1;; ++j) {
-              Frag nr, ni;
+      for (int ks = 0; ks < KS; ++ks) {
+        const Frag rh = sh.alpha[ks][0][lane], rl = sh.alpha[ks][1][lane];
+        const Frag jh = sh.alpha[ks][2][lane], jl = sh.alpha[ks][3][lane];
+        pr = mfma(rh, sh_[ks], pr);
+        pi = mfma(jh, sh_[ks], pi);
+        tr = mfma(rh, sl_[ks], tr);
+        ti = mfma(jh, sl_[ks], ti);
+        tr = mfma(rl, sh_[ks], tr);
+        ti = mfma(jl, sh_[ks], ti);
+        if (s.order > 0) {
+          const Frag bx = *reinterpret_cast<const Frag*>(&sh.b[8 * ks + 4 * h]);
+          Frag u;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) u.w[i] = swap_mul(sh_[ks].w[i], bx.w[i]);
+          ur = mfma(rh, u, ur);
+          ui = mfma(jh, u, ui);
+          if (s.order > 1) {
+            // wide fields: (2 pi d_k)^(j-1) / j! on the rows, (i b(x))^j b(y)^(j-1) S' on the columns
+            const unsigned dw = sh.vb.dw[col], by = sh.b[y0 + yl] & 0xFFFF0000u;
+            const unsigned by2 = by | by >> 16;
+            Frag r2 = rh, j2 = jh;
+            for (int j = 2; j <= s.order; ++j) {
+              const unsigned f = pk_mul(dw, pair_of(1.0f / (float)j));
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
-                ar.w[i] = pk_mul(ar.w[i], f);
-                nr.w[i] = pk_mul(ci.w[i] ^ kNegBoth, bb[i]);
-                ni.w[i] = pk_mul(cr.w[i], bb[i]);
+                r2.w[i] = pk_mul(r2.w[i], f);
+                j2.w[i] = pk_mul(j2.w[i], f);
+                u.w[i] = pk_mul(swap_mul(u.w[i], bx.w[i]), by2);
               }
-              cr = nr;
-              ci = ni;
-              tr = mfma(ar, cr, tr);
-              ti = mfma(ar, ci, ti);
-              if (j == s.order) break;
-              f = pk_mul(f, pair_of((float)j / (float)(j + 1)));
+              ur = mfma(r2, u, ur);
+              ui = mfma(j2, u, ui);
             }
           }
         }
-        // times conj(beta), the wave's eight rows summed: value 2 i + (0: re, 1: im) belongs to
-        // visibility 8 (i >> 2) + 4 h + (i & 3) of the tile
-        float v[32];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float2 b = sh.beta[yl * kBlkPitch + 32 * tile + 8 * (i >> 2) + 4 * h + (i & 3)];
-          v[2 * i] = b.x * tr[i] + b.y * ti[i];
-          v[2 * i + 1] = b.x * ti[i] - b.y * tr[i];
-        }
-        // transpose-reduction over lane bits 4, 3 and 2 (the rows): each lane ends with four
-        // values, 16 (bit 4) + 8 (bit 3) + 4 (bit 2) + 0 .. 3
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          swap16(v[i], v[i + 16]);
-          v[i] = v[i] + v[i + 16];
-        }
-        const bool b3 = lane & 8, b2 = lane & 4;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float keep = b3 ? v[i + 8] : v[i], send = b3 ? v[i] : v[i + 8];
-          v[i] = keep + dpp<kDppRowRor8>(send);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float keep = b2 ? v[i + 4] : v[i], send = b2 ? v[i] : v[i + 4];
-          v[i] = keep + dpp<kDppQuadMirror>(dpp<kDppRowHalfMirror>(send));
-        }
-        const int i0 = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1);
-        const int kk = 32 * tile + 8 * (i0 >> 2) + 4 * h + (i0 & 3);
-        sh.part[wave][kk * 4 + q] = {v[0] * unscale, v[1] * unscale};
-        sh.part[wave][(kk + 1) * 4 + q] = {v[2] * unscale, v[3] * unscale};
       }
+      if (s.order > 0) {
+        const float by = (float)__builtin_bit_cast(half2v, sh.b[y0 + yl]).y;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float f =
+              by * (float)__builtin_bit_cast(half2v, sh.vb.dw[8 * (i >> 2) + 4 * h + (i & 3)]).x;
+          tr[i] = fmaf(f, ur[i], tr[i]);
+          ti[i] = fmaf(f, ui[i], ti[i]);
+        }
+      }
+      tr += pr;
+      ti += pi;
+      // times conj(beta), the wave's eight rows summed: value 2 i + (0: re, 1: im) belongs to
+      // visibility 8 (i >> 2) + 4 h + (i & 3) of the block
+      float v[32];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float2 b = sh.beta[yl * (B + 2) + 8 * (i >> 2) + 4 * h + (i & 3)];
+        v[2 * i] = b.x * tr[i] + b.y * ti[i];
+        v[2 * i + 1] = b.x * ti[i] - b.y * tr[i];
+      }
+      // transpose-reduction over lane bits 4, 3 and 2 (the rows): each lane ends with four
+      // values, 16 (bit 4) + 8 (bit 3) + 4 (bit 2) + 0 .. 3
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        swap16(v[i], v[i + 16]);
+        v[i] = v[i] + v[i + 16];
+      }
+      const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float keep = b3 ? v[i + 8] : v[i], send = b3 ? v[i] : v[i + 8];
+        v[i] = keep + dpp<kDppRowRor8>(send);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float keep = b2 ? v[i + 4] : v[i], send = b2 ? v[i] : v[i + 4];
+        v[i] = keep + dpp<kDppQuadMirror>(dpp<kDppRowHalfMirror>(send));
+      }
+      const int i0 = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1);
+      const int kk = 8 * (i0 >> 2) + 4 * h + (i0 & 3);
+      sh.part[wave][kk * 4 + q] = {v[0] * unscale, v[1] * unscale};
+      sh.part[wave][(kk + 1) * 4 + q] = {v[2] * unscale, v[3] * unscale};
       __syncthreads();
       // the waves' sums in wave order; each output element has one thread, the same in
       // every pass
-      for (int i = tid; i < n * 8; i += kThreads) {
+      if (tid < n * 8) {
         const float* p0 = reinterpret_cast<const float*>(sh.part[0]);
-        float v = p0[i];
+        float o = p0[tid];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) v = v + p0[w * kBlk * 8 + i];
-        const int k = k0 + (i >> 3), row = (int)(((float)k + 0.5f) * inv_nc), ch = k - row * s.nc;
-        store_vis(vis + (s.vis0 + (int64_t)row * a.nc_total + ch) * 8, i & 7, v, s.fold != 0, y0 != 0);
+        for (int w = 1; w < 4; ++w) o = o + p0[w * B * 8 + tid];
+        const int k = k0 + (tid >> 3), row = (int)(((float)k + 0.5f) * inv_nc), ch = k - row * s.nc;
+        int e = tid & 7;
+        if (s.fold) {  // the conjugate transpose of the prediction at -uvw
+          const int pol = e >> 1;
+          if (e & 1) o = -o;
+          e = (pol == 1 ? 4 : pol == 2 ? 2 : 2 * pol) + (e & 1);
+        }
+        const unsigned off = ((unsigned)row * (unsigned)a.nc_total + (unsigned)ch) * 32u + 4u * e;
+        if (y0) o += gload<float>(vis, off);
+        gstore(vis, off, o);
       }
     }
   }
