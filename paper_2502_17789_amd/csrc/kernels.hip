@@ -438,13 +438,13 @@ __global__ __launch_bounds__(kThreads) void fft_add(const Group g) {
   fft_lines<L, -1, true>(buf, tw);
   fft_lines<L, -1, false>(buf, tw);
   R* win = grid + 2 * ((((int64_t)s.wlayer * a.npol + pol) * a.N + (s.V0 - L / 2)) * a.N + (s.U0 - L / 2));
-  for (int e = threadIdx.x; e < L * L; e += kThreads) {
-    const int b = e / L, c = e % L;
-    V2 val = buf[b * pitch(L) + c];
-    if ((b + c) & 1) val = -val;
-    R* dst = win + 2 * ((int64_t)b * a.N + c);
-    unsafeAtomicAdd(dst, val.x);
-    unsafeAtomicAdd(dst + 1, val.y);
+  // one real number per lane: a wave's atomics cover 64 consecutive ones (a complex number
+  // per lane and two atomics would touch every line twice, half of it each time)
+  const R* flat = reinterpret_cast<const R*>(buf);
+  for (int e = threadIdx.x; e < 2 * L * L; e += kThreads) {
+    const int b = e / (2 * L), c = e % (2 * L);
+    const R val = flat[2 * b * pitch(L) + c];
+    unsafeAtomicAdd(win + 2 * (int64_t)b * a.N + c, (b + (c >> 1)) & 1 ? -val : val);
   }
 }
 
