@@ -91,6 +91,31 @@ __device__ __forceinline__ double2 phasor(double theta, double) {
   return {c, s};
 }
 
+// z times exp(DIR 2 pi i / 8), z times exp(DIR 2 pi i k / 12) for k = 1, 2.
+template <typename V2, int DIR>
+__device__ __forceinline__ V2 eighth(V2 z) {
+  using Rt = decltype(z.x);
+  const Rt c = Rt(0.70710678118654752440);
+  return {(z.x - Rt(DIR) * z.y) * c, (z.y + Rt(DIR) * z.x) * c};
+}
+template <typename V2, int DIR>
+__device__ __forceinline__ V2 twelfth(V2 z) {
+  using Rt = decltype(z.x);
+  const Rt c = Rt(0.86602540378443864676), s = Rt(DIR) * Rt(0.5);
+  return {z.x * c - z.y * s, z.y * c + z.x * s};
+}
+template <typename V2, int DIR>
+__device__ __forceinline__ V2 sixth(V2 z) {
+  using Rt = decltype(z.x);
+  const Rt c = Rt(0.5), s = Rt(DIR) * Rt(0.86602540378443864676);
+  return {z.x * c - z.y * s, z.y * c + z.x * s};
+}
+template <typename V2, int DIR>
+__device__ __forceinline__ V2 quarter(V2 z) {
+  using Rt = decltype(z.x);
+  return {Rt(-DIR) * z.y, Rt(DIR) * z.x};
+}
+
 // In-place DFT of R points: v[k] <- sum_j v[j] exp(DIR 2 pi i j k / R), DIR = -1
 // (forward) or +1 (inverse), unnormalised.
 template <typename V2, int R, int DIR>
@@ -108,6 +133,40 @@ __device__ __forceinline__ void butterfly(V2* v) {
     v[1] = t1 + t3;
     v[2] = t0 - t2;
     v[3] = t1 - t3;
+  } else if constexpr (R == 8) {  // two DFTs of 4 points
+    V2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    butterfly<V2, 4, DIR>(e);
+    butterfly<V2, 4, DIR>(o);
+    o[1] = eighth<V2, DIR>(o[1]);
+    o[3] = quarter<V2, DIR>(eighth<V2, DIR>(o[3]));
+    o[2] = quarter<V2, DIR>(o[2]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = e[k] + o[k];
+      v[k + 4] = e[k] - o[k];
+    }
+  } else if constexpr (R == 12) {  // three DFTs of 4 points, then four of 3
+    V2 y[3][4];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) y[r][m] = v[3 * m + r];
+      butterfly<V2, 4, DIR>(y[r]);
+    }
+    y[1][1] = twelfth<V2, DIR>(y[1][1]);
+    y[1][2] = sixth<V2, DIR>(y[1][2]);
+    y[1][3] = quarter<V2, DIR>(y[1][3]);
+    y[2][1] = sixth<V2, DIR>(y[2][1]);
+    y[2][2] = quarter<V2, DIR>(twelfth<V2, DIR>(y[2][2]));
+    y[2][3] = V2{-y[2][3].x, -y[2][3].y};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      V2 t[3] = {y[0][k], y[1][k], y[2][k]};
+      butterfly<V2, 3, DIR>(t);
+      v[k] = t[0];
+      v[k + 4] = t[1];
+      v[k + 8] = t[2];
+    }
   } else if constexpr (R == 3) {
     const Rt c = Rt(-0.5), dd = Rt(DIR) * Rt(0.86602540378443864676);
     const V2 t1 = v[1] + v[2], t2 = v[1] - v[2];

@@ -358,70 +358,74 @@ void grid_dft(const Group g) {
 
 // ------------------------------------------------------------------ subgrid FFT
 
+// Two passes per axis, and the threads that share their butterflies out evenly.
 template <int L> struct Radices;
-template <> struct Radices<32> { static constexpr int n = 3, r[4] = {4, 4, 2, 1}; };
-template <> struct Radices<64> { static constexpr int n = 3, r[4] = {4, 4, 4, 1}; };
-template <> struct Radices<96> { static constexpr int n = 4, r[4] = {4, 4, 2, 3}; };
+template <> struct Radices<32> { static constexpr int r0 = 8, r1 = 4, threads = 256; };
+template <> struct Radices<64> { static constexpr int r0 = 8, r1 = 8, threads = 256; };
+template <> struct Radices<96> { static constexpr int r0 = 12, r1 = 8, threads = 384; };
 
 constexpr int pitch(int L) { return L + 1; }
 
-// One Stockham pass (radix R, NS = product of earlier radices) over every line of
-// the plane held in LDS; lines are rows (stride 1) or columns (stride L+1).
-template <int L, int R, int NS, int DIR, bool ROWS, typename V2>
-__device__ __forceinline__ void stockham_pass(V2* buf, const V2* tw) {
-  constexpr int NB = L / R, TOTAL = L * NB, PER = (TOTAL + kThreads - 1) / kThreads;
+// One Stockham pass (radix R, NS = product of earlier radices) over every line of the plane.
+// Neighbouring lanes take neighbouring lines, whose elements lie one (columns) or L + 1 (rows)
+// complex values apart in LDS: no two on one bank.  load(line, i), store(line, i, v).
+template <int L, int R, int NS, int DIR, typename V2, typename Load, typename Store>
+__device__ __forceinline__ void stockham_pass(const V2* tw, const Load& load, const Store& store) {
+  constexpr int T = Radices<L>::threads, NB = L / R, TOTAL = L * NB, PER = (TOTAL + T - 1) / T;
   constexpr int TSTEP = L / (NS * R);
   V2 v[PER][R];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int b = threadIdx.x + i * kThreads;
-    if (b < TOTAL) {
-      const int line = ROWS ? b / NB : b % L, j = ROWS ? b % NB : b / L;
+    const int b = threadIdx.x + i * T;
+    if (TOTAL % T == 0 || b < TOTAL) {
+      const int line = b % L, j = b / L;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const int idx = j + q * NB;
-        v[i][q] = buf[ROWS ? line * pitch(L) + idx : idx * pitch(L) + line];
-      }
+      for (int q = 0; q < R; ++q) v[i][q] = load(line, j + q * NB);
     }
   }
-  __syncthreads();
+  __syncthreads();  // in place: every read before the first write
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int b = threadIdx.x + i * kThreads;
-    if (b < TOTAL) {
-      const int line = ROWS ? b / NB : b % L, j = ROWS ? b % NB : b / L;
+    const int b = threadIdx.x + i * T;
+    if (TOTAL % T == 0 || b < TOTAL) {
+      const int line = b % L, j = b / L;
       const int k = j % NS;
+      if constexpr (NS > 1) {
 #pragma unroll
-      for (int q = 1; q < R; ++q) {
-        V2 w = tw[(k * q * TSTEP) % L];
-        if (DIR > 0) w.y = -w.y;
-        v[i][q] = {v[i][q].x * w.x - v[i][q].y * w.y, v[i][q].x * w.y + v[i][q].y * w.x};
+        for (int q = 1; q < R; ++q) {
+          V2 w = tw[(k * q * TSTEP) % L];
+          if (DIR > 0) w.y = -w.y;
+          v[i][q] = {v[i][q].x * w.x - v[i][q].y * w.y, v[i][q].x * w.y + v[i][q].y * w.x};
+        }
       }
       butterfly<V2, R, DIR>(v[i]);
       const int base = (j / NS) * NS * R + k;
 #pragma unroll
-      for (int q = 0; q < R; ++q) {
-        const int idx = base + q * NS;
-        buf[ROWS ? line * pitch(L) + idx : idx * pitch(L) + line] = v[i][q];
-      }
+      for (int q = 0; q < R; ++q) store(line, base + q * NS, v[i][q]);
     }
   }
   __syncthreads();
 }
 
-template <int L, int DIR, bool ROWS, typename V2>
-__device__ __forceinline__ void fft_lines(V2* buf, const V2* tw) {
-  using Rd = Radices<L>;
-  constexpr int r0 = Rd::r[0], r1 = Rd::r[1], r2 = Rd::r[2], r3 = Rd::r[3];
-  stockham_pass<L, r0, 1, DIR, ROWS>(buf, tw);
-  stockham_pass<L, r1, r0, DIR, ROWS>(buf, tw);
-  stockham_pass<L, r2, r0 * r1, DIR, ROWS>(buf, tw);
-  if constexpr (Rd::n == 4) stockham_pass<L, r3, r0 * r1 * r2, DIR, ROWS>(buf, tw);
+// The 2-D transform: columns first, whose first pass reads load(row, column) (coalesced along
+// a row); the result is left in buf.
+template <int L, int DIR, typename V2, typename Load>
+__device__ __forceinline__ void fft_plane(V2* buf, const V2* tw, const Load& load) {
+  constexpr int r0 = Radices<L>::r0, r1 = Radices<L>::r1;
+  auto col = [&](int line, int i) -> V2& { return buf[i * pitch(L) + line]; };
+  auto row = [&](int line, int i) -> V2& { return buf[line * pitch(L) + i]; };
+  auto put_col = [&](int line, int i, V2 v) { col(line, i) = v; };
+  auto put_row = [&](int line, int i, V2 v) { row(line, i) = v; };
+  stockham_pass<L, r0, 1, DIR, V2>(tw, [&](int line, int i) { return load(i, line); }, put_col);
+  stockham_pass<L, r1, r0, DIR, V2>(tw, col, put_col);
+  stockham_pass<L, r0, 1, DIR, V2>(tw, row, put_row);
+  stockham_pass<L, r1, r0, DIR, V2>(tw, row, put_row);
 }
 
 template <int L, typename R>
-__global__ __launch_bounds__(kThreads) void fft_add(const Group g) {
+__global__ __launch_bounds__(Radices<L>::threads) void fft_add(const Group g) {
   using V2 = typename C2<R>::T;
+  constexpr int T = Radices<L>::threads;
   __shared__ V2 buf[L * pitch(L)];
   __shared__ V2 tw[L];
   const int pol = blockIdx.x;
@@ -432,16 +436,13 @@ __global__ __launch_bounds__(kThreads) void fft_add(const Group g) {
   const SubgridDev s = load_uniform(a.sg + gs.sb);  // centre and w-layer of the group
   R* grid = reinterpret_cast<R*>(gs.out);
   const V2* in = reinterpret_cast<const V2*>(g.scratch) + (local * 4 + pol) * L * L;
-  for (int e = threadIdx.x; e < L * L; e += kThreads) buf[(e / L) * pitch(L) + e % L] = in[e];
-  for (int e = threadIdx.x; e < L; e += kThreads) tw[e] = reinterpret_cast<const V2*>(a.twiddle)[e];
-  __syncthreads();
-  fft_lines<L, -1, true>(buf, tw);
-  fft_lines<L, -1, false>(buf, tw);
+  for (int e = threadIdx.x; e < L; e += T) tw[e] = reinterpret_cast<const V2*>(a.twiddle)[e];
+  fft_plane<L, -1>(buf, tw, [&](int y, int x) -> V2 { return in[y * L + x]; });
   R* win = grid + 2 * ((((int64_t)s.wlayer * a.npol + pol) * a.N + (s.V0 - L / 2)) * a.N + (s.U0 - L / 2));
   // one real number per lane: a wave's atomics cover 64 consecutive ones (a complex number
   // per lane and two atomics would touch every line twice, half of it each time)
   const R* flat = reinterpret_cast<const R*>(buf);
-  for (int e = threadIdx.x; e < 2 * L * L; e += kThreads) {
+  for (int e = threadIdx.x; e < 2 * L * L; e += T) {
     const int b = e / (2 * L), c = e % (2 * L);
     const R val = flat[2 * b * pitch(L) + c];
     unsafeAtomicAdd(win + 2 * (int64_t)b * a.N + c, (b + (c >> 1)) & 1 ? -val : val);
@@ -449,8 +450,9 @@ __global__ __launch_bounds__(kThreads) void fft_add(const Group g) {
 }
 
 template <int L, typename R>
-__global__ __launch_bounds__(kThreads) void split_ifft(const Group g) {
+__global__ __launch_bounds__(Radices<L>::threads) void split_ifft(const Group g) {
   using V2 = typename C2<R>::T;
+  constexpr int T = Radices<L>::threads;
   __shared__ V2 buf[L * pitch(L)];
   __shared__ V2 tw[L];
   const int pol = blockIdx.x;
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void split_ifft(const Group g) {
   // transform of the one grid plane, planes 1 and 2 zero (whole workgroups).
   const bool stokes = a.npol == 1;
   if (stokes && (pol == 1 || pol == 2)) {
-    for (int e = threadIdx.x; e < L * L; e += kThreads) out[e] = V2{0, 0};
+    for (int e = threadIdx.x; e < L * L; e += T) out[e] = V2{0, 0};
     return;
   }
   const int gp = stokes ? 0 : pol;  // grid plane
@@ -471,19 +473,14 @@ __global__ __launch_bounds__(kThreads) void split_ifft(const Group g) {
   const R* __restrict__ grid = reinterpret_cast<const R*>(gs.in);
   const V2* win = reinterpret_cast<const V2*>(grid) +
                   (((int64_t)s.wlayer * a.npol + gp) * a.N + (s.V0 - L / 2)) * a.N + (s.U0 - L / 2);
-  for (int e = threadIdx.x; e < L * L; e += kThreads) {
-    const int b = e / L, c = e % L;
-    V2 val = win[(int64_t)b * a.N + c];
-    if ((b + c) & 1) val = -val;
-    buf[b * pitch(L) + c] = val;
-  }
-  for (int e = threadIdx.x; e < L; e += kThreads) tw[e] = reinterpret_cast<const V2*>(a.twiddle)[e];
-  __syncthreads();
-  fft_lines<L, +1, true>(buf, tw);
-  fft_lines<L, +1, false>(buf, tw);
+  for (int e = threadIdx.x; e < L; e += T) tw[e] = reinterpret_cast<const V2*>(a.twiddle)[e];
+  fft_plane<L, +1>(buf, tw, [&](int b, int c) -> V2 {
+    const V2 val = win[(int64_t)b * a.N + c];
+    return (b + c) & 1 ? -val : val;
+  });
   // the adjoint of the Stokes-I reduction (XX + YY) / 2 expands I to diag(I, I) / 2
   const R scale = stokes && gs.adjoint ? (R)0.5 : (R)1;
-  for (int e = threadIdx.x; e < L * L; e += kThreads) out[e] = buf[(e / L) * pitch(L) + e % L] * scale;
+  for (int e = threadIdx.x; e < L * L; e += T) out[e] = buf[(e / L) * pitch(L) + e % L] * scale;
 }
 
 // ------------------------------------------------------------------ degridder
@@ -977,10 +974,10 @@ int launch_one(KernelClass k, const Group& g, hipStream_t st, int max_nv) {
                          dim3(kThreads), (size_t)max_nv * 8 * sizeof(R), st, g);
       break;
     case kFftAdd:
-      hipLaunchKernelGGL((fft_add<L, R>), dim3(4, n), dim3(kThreads), 0, st, g);
+      hipLaunchKernelGGL((fft_add<L, R>), dim3(4, n), dim3(Radices<L>::threads), 0, st, g);
       break;
     case kSplitIfft:
-      hipLaunchKernelGGL((split_ifft<L, R>), dim3(4, n), dim3(kThreads), 0, st, g);
+      hipLaunchKernelGGL((split_ifft<L, R>), dim3(4, n), dim3(Radices<L>::threads), 0, st, g);
       break;
     case kDegridDft: {
       constexpr int nt = DegridTune<L, R>::NT;
