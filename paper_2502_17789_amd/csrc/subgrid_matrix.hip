@@ -138,7 +138,7 @@ __device__ __forceinline__ void add_corrected(const PixelTerms& x, float wmid, f
     const float f = w / sqrtf(n2 > 0.0f ? n2 : 1.0f);
     w = n2 > 0.0f ? f : 0.0f;
   }
-  // taper and E(w_s c), |w_s c| < 1/2 turn
+  // taper and E(w_s c), |w_s c| <= 128 turns
   const float ph = wmid * x.tc.y;
   const float2 e = {w * __builtin_amdgcn_cosf(ph), w * __builtin_amdgcn_sinf(ph)};
   const float2 s0 = cmul<float>(e, s[0]), s1 = cmul<float>(e, s[1]);
@@ -183,8 +183,14 @@ struct GridLds {
 // alpha_k(x), formed once per workgroup and read from LDS in the operand's lane order.
 // The next block's visibilities and uvw are loaded (into registers) before the products of
 // the current one, across subgrids as well.
+// Waves per SIMD that the registers are allocated for.  At L = 32 a lane has one column tile
+// and three workgroups fit a compute unit: 72 stations x 16 times x 96 channels, folded: 1.07 ms
+// against 1.25 with two; four spill (1.25 ms), and so do three at L = 64.
 template <int L>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void grid_matrix(const Group g) {
+constexpr int kGridWaves = L == 32 ? 3 : 2;
+template <int L>
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_matrix(const Group g) {
   constexpr int XT = L / 32, NP = 4, NPIX = XT * NP, P0 = kLdsPixels<L>;  // column tiles; pixels per lane
   extern __shared__ unsigned char smem_raw[];
   GridLds<L>& sh = *reinterpret_cast<GridLds<L>*>(smem_raw);
