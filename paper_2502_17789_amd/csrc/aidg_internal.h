@@ -57,16 +57,17 @@ struct Geometry {
 };
 
 // Tables of the matrix kernels.  The w-term n1(l, m) splits into n1(l, 0) + n1(0, m) + c(l, m)
-// and c = -b(l) b(m) to the given residual; peak[j] is the largest taper-weighted |c|^j.
+// and c = -b(l) b(m) to the given residual; peak[j] is the largest taper-weighted |c|^j,
+// axis_peak and cross_peak the largest |n1(l, 0)| and |c|.
 constexpr int kMaxWOrder = 3;
 struct WSeries {
   std::vector<double> axis_n1, b, cross;  // [L], [L], [L][L]
-  double peak[kMaxWOrder + 2] = {0}, residual = 0;
+  double peak[kMaxWOrder + 2] = {0}, residual = 0, axis_peak = 0, cross_peak = 0;
 };
 void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out);
 // Terms of the series in (w - wmid) c that a subgrid with |w - wmid| <= dw needs, or -1
 // where the matrix kernels do not apply.
-int w_series_order(const WSeries& ws, double dw);
+int w_series_order(const WSeries& ws, double wmid, double dw);
 
 // Host-side partition (library's own algorithm); table entries are aidg_subgrid.
 struct PartitionResult {
@@ -159,6 +160,8 @@ enum KernelClass {
 // direct form), and only sub-tables of at most the workgroup's lane count can take the
 // per-visibility form (else the recurrence).
 int32_t degrid_form(const Geometry& g, int nt, int nc, bool uniform);
+// Modelled cost per pixel of a subgrid in its form, in visibilities of the recurrence.
+double degrid_cost(int32_t kind, int nt, int nc);
 
 // Launch one kernel class over a group (kernels.hip).  max_nv: the largest
 // sub-table of the group (degridder LDS).  Returns a hipError_t as int.

@@ -93,8 +93,8 @@ struct aidg_plan {
   int64_t* d_excl = nullptr;
   int64_t* d_grp = nullptr;
   KernelArgs* d_args = nullptr;  // device copy of args()
-  // matrix kernels: all of the plan's subgrids qualify (gridding; degridding too unless the
-  // geometry asks for another form)
+  // matrix kernels: all of the plan's subgrids qualify (degridding: and they are not so
+  // sparse that the other forms take less time, and the geometry asks for none)
   bool matrix_grid = false, matrix_degrid = false;
   // image level (invert / predict): Stockham radices of N, twiddles exp(-2 pi i k / N)
   // and the reciprocal of the taper's axis at image resolution (FP64); absent when N
@@ -643,6 +643,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     WSeries series;
     if (f32) w_series(L, g.fov, T, &series);
     bool matrix = f32;
+    double cost = 0.0;  // of the degridder's other forms
     std::vector<SubgridDev> dev(plan->table.size());
     for (size_t i = 0; i < plan->table.size(); ++i) {
       const aidg_subgrid& s = plan->table[i];
@@ -681,14 +682,23 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
           }
         d.wmid = (float)(0.5 * (lo + hi));
         const double dw = std::max(hi - d.wmid, d.wmid - lo);
-        d.order = w_series_order(series, dw);
+        d.order = w_series_order(series, d.wmid, dw);
         matrix = d.order >= 0;
       }
+      cost += degrid_cost(d.kind, s.nt, s.nc);
       plan->n_pervis += d.kind == kDegridPerVis;
       plan->n_direct += d.kind == kDegridDirect;
     }
     plan->matrix_grid = matrix;
-    plan->matrix_degrid = matrix && g.degrid_form == AIDG_DEGRID_AUTO;
+    // The matrix degridder works in blocks of 32 visibilities and takes the same time for 1
+    // as for 32: 13.6, 44 and 94 ns per subgrid at L = 32, 64, 96 with the chip full.  The
+    // other forms, with one row per subgrid and c channels, take 9 to 11 ns for c = 1 to 10
+    // (L = 32), 42 ns for 1, 45 for 4 and 60 for 16 (L = 64), 78 ns for 1, 88 for 6, 93 for
+    // 8 and 137 for 22 (L = 96); with 8 rows of one channel 17 ns at L = 32.  The lines are
+    // where the two meet, in that model's cost.
+    const double meet = L == 32 ? 13.5 : L == 64 ? 6.0 : 10.0;
+    plan->matrix_degrid =
+        matrix && g.degrid_form == AIDG_DEGRID_AUTO && cost >= meet * (double)plan->table.size();
     // inverse A-term mode: distinct (A_p plane, A_q plane) pairs with their visibility
     // counts, for the normalisation map
     std::vector<int32_t> pairs;

@@ -1000,6 +1000,16 @@ int degrid_lanes(int L) {
 }
 }  // namespace
 
+namespace {
+constexpr double kRow = 2.0, kDirect = 1.95;  // see degrid_form
+double recur_cost(int nt, int nc) { return (double)nt * ((nc + (nc & 1)) + kRow); }
+double direct_cost(int nt, int nc) { return kDirect * (nt * nc + ((nt * nc) & 1)); }
+}  // namespace
+
+double degrid_cost(int32_t kind, int nt, int nc) {
+  return kind == kDegridRecur ? recur_cost(nt, nc) : direct_cost(nt, nc);
+}
+
 int32_t degrid_form(const Geometry& g, int nt, int nc, bool uniform) {
   const int nv = nt * nc;
   const int lanes = g.precision == AIDG_FP32 ? degrid_lanes<float>(g.L) : degrid_lanes<double>(g.L);
@@ -1023,10 +1033,7 @@ int32_t degrid_form(const Geometry& g, int nt, int nc, bool uniform) {
   // single form, or faster, at every k.  Rows of one to three channels take the direct
   // form.  The per-visibility form measured slower than the direct form at every
   // occupancy and is never chosen automatically.
-  constexpr double kRow = 2.0, kDirect = 1.95;
-  const double recur = (double)nt * ((nc + (nc & 1)) + kRow);
-  const double direct = kDirect * (nv + (nv & 1));
-  return direct < recur ? kDegridDirect : kDegridRecur;
+  return direct_cost(nt, nc) < recur_cost(nt, nc) ? kDegridDirect : kDegridRecur;
 }
 
 int launch_group(KernelClass k, int L, int precision, const Group& g, void* stream, int max_nv) {

@@ -619,6 +619,7 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
     const double l = (x - L / 2) * (fov / L);
     l2[x] = l * l;
     out->axis_n1[x] = n1(l2[x]);
+    out->axis_peak = std::max(out->axis_peak, std::fabs(out->axis_n1[x]));
   }
   // (c is symmetric, and so is the taper: x >= y covers the peaks)
   out->cross.resize((size_t)L * L);
@@ -627,6 +628,7 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
     for (int x = y; x < L; ++x) {
       const double c = n1(l2[x] + l2[y]) - out->axis_n1[x] - out->axis_n1[y], m = std::fabs(c);
       out->cross[(size_t)y * L + x] = out->cross[(size_t)x * L + y] = c;
+      out->cross_peak = std::max(out->cross_peak, m);
       double t = std::fabs(taper[(size_t)y * L + x]);
       for (int j = 1; j <= kMaxWOrder + 1; ++j) {
         t *= m;
@@ -650,7 +652,13 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
 // The series is cut where its first missing term is below 3e-8 of the taper's peak, a tenth
 // of the FP32 path's normwise error; the first-order term, taken in FP16, may be 1e-3 (its
 // rounding is then below 5e-8 rms), and the part of c that is not b b below 1e-7.
-int w_series_order(const WSeries& ws, double dw) {
+int w_series_order(const WSeries& ws, double wmid, double dw) {
+  // Phases (turns) stay in the range of the kernels' fixed-point reduction, and E(wmid c),
+  // formed from an FP32 phase, is exact to 2^-24 of its tapered largest phase.
+  const double far = std::fabs(wmid) + dw;
+  if (!(far * ws.axis_peak <= 0x1p17) || !(far * ws.cross_peak <= 128.0) ||
+      !(2.0 * M_PI * std::fabs(wmid) * ws.peak[1] <= 0.5))
+    return -1;
   const double p = 2.0 * M_PI * dw;
   if (!(p * ws.peak[1] <= 1e-3) || !(p * ws.residual <= 1e-7)) return -1;
   double term = 1.0;
