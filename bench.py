@@ -626,11 +626,12 @@ def image_bench(args):
             del G, I, Io, Go
         P = N * N * 8
         npol = geo.n_pol
-        # per polarisation plane: invert reads + writes a plane in each of 2 row passes and
-        # 1 transpose per layer, the first layer's w-stack pass reads 1 and writes 1, the
-        # others read 2 and write 1; predict reads + writes in 2 row passes and 2 transposes
-        by = {"image_fft": reps * npol * 4 * W * 2 * P,
-              "image_wstack": reps * npol * ((W * 2 + 2 + (W - 1) * 3) + 2 * W * 2) * P}
+        # per polarisation plane and layer: invert reads + writes a plane in 1 pass (2 for
+        # rows beyond 2048 points) and its last pass reads 1 and writes 1 (first layer) or
+        # reads 2 and writes 1; predict reads + writes in 2 (3) passes
+        more = 1 if N > 2048 else 0
+        by = {"image_fft": reps * npol * W * (1 + more + 2 + more) * 2 * P,
+              "image_wstack": reps * npol * (2 + (W - 1) * 3) * P}
         cls = {k: {"ms_per_launch": round(kt[k]["ms"] / max(kt[k]["launches"], 1), 4),
                    "launches_per_call_pair": kt[k]["launches"] // reps,
                    "gb_s": round(by[k] / (kt[k]["ms"] * 1e-3) / 1e9, 1)} for k in by}

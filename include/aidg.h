@@ -302,8 +302,8 @@ aidg_status aidg_footprint_estimate(const aidg_geometry* geo, int32_t n_stations
 /* Per-kernel device timing (the paper's per-subroutine breakdown, Sec. 5.4).
  * Kernel classes: 0 gridder DFT + Jones/taper epilogue, 1 FFT + adder,
  * 2 splitter + inverse FFT, 3 degridder DFT with Jones/taper prologue,
- * 4 zeroing of excluded visibilities, 5 image-level row FFTs (aidg_invert /
- * aidg_predict), 6 image-level transposes and w-stacking passes. */
+ * 4 zeroing of excluded visibilities, 5 image-level transform passes
+ * (aidg_invert / aidg_predict), 6 aidg_invert's last pass with the w-stacking. */
 #define AIDG_KERNEL_CLASSES 7
 typedef struct {
   double ms[AIDG_KERNEL_CLASSES];            /* summed device time of the class */

@@ -150,8 +150,8 @@ struct Group {
 // Kernel classes, in the order of aidg_kernel_times.
 enum KernelClass {
   kGridDft = 0, kFftAdd = 1, kSplitIfft = 2, kDegridDft = 3, kZeroVis = 4,
-  kImageFft = 5,      // image-level row FFTs (invert / predict)
-  kImageWstack = 6    // image-level transposes and w-stacking passes
+  kImageFft = 5,      // image-level row and column passes (invert / predict)
+  kImageWstack = 6    // invert's last column pass, with the w-stacking
 };
 
 // Degridder form of a sub-table of nt rows and nc channels (kernels.hip), `uniform`
@@ -175,21 +175,25 @@ int launch_zero_vis(int precision, const int64_t* idx, int64_t n, void* vis, voi
 // factor into radices 4, 2, 3 and 5 and a row must fit in 64 KB.
 constexpr int kMaxImageN = 8192;
 constexpr int kMaxImageRowBytes = 65536;
-constexpr int kMaxImageRadices = 16;
-struct ImageRadices {
+constexpr int kMaxImageRadices = 9;
+constexpr int kMaxImagePart = 128;    // points of a column step
+constexpr int kMaxImageStrip = 2048;  // points of a row whose transform is written transposed
+inline bool image_strips(int N) { return N <= kMaxImageStrip; }
+struct ImageFactors {
   int32_t n;                     // number of Stockham passes
   int32_t r[kMaxImageRadices];   // radix of each pass
 };
-// Factorisation of N in pass order (5s, 3s, then 4s and a 2); false when N is not
-// supported.
+struct ImageRadices {
+  int32_t n1;                    // column steps of n1 and N / n1 points
+  ImageFactors row, col1, col2;
+};
+// Steps and passes of N; false when N is not supported.
 bool image_radices(int N, int elem_bytes, ImageRadices* out);
 void kaiser_bessel_axis(int n, double beta, std::vector<double>* t);
-int launch_image_fft_rows(int precision, int dir, bool predict, const void* src, void* dst, int N,
-                          const ImageRadices& fr, const void* tw, const double* itaper, double dl,
-                          double w0, double inv_l2, void* stream);
-int launch_image_transpose(int precision, const void* src, void* dst, int N, void* stream);
-int launch_image_wstack(int precision, const void* B, void* img, int N, const double* itaper, double dl,
-                        double w0, double inv_l2, int assign, const double* nmap, int L, void* stream);
+enum ImagePass { kInvertRows, kInvertColumns, kInvertStack, kPredictRows, kPredictColumns, kPredictGrid };
+int launch_image_pass(int precision, ImagePass pass, const void* src, void* dst, int planes, int N,
+                      const ImageRadices& fr, const void* tw, const double* itaper, double dl, double w0,
+                      double inv_l2, int assign, const double* nmap, int L, void* stream);
 
 // Device address of the static workspace (kStaticWorkspaceBytes) on `device`, which
 // must be the current device; looked up on the first call per device, then cached.

@@ -1024,30 +1024,25 @@ aidg_status aidg_invert(aidg_plan* plan, const void* grid, void* image, void* wo
   if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
   const int N = plan->g.N, prec = plan->g.precision;
   const size_t plane = (size_t)N * N * plan->elem;
-  char* A = static_cast<char*>(workspace);
-  char* B = A + plane;
   const double dl = plan->g.dl, inv_l2 = 1.0 / ((double)plan->g.L * plan->g.L);
-  for (int pol = 0; pol < plan->g.npol && r == AIDG_OK; ++pol) {
+  for (int pol = 0; pol < plan->g.npol && r == AIDG_OK; pol += 2) {  // the workspace holds two planes
+    const int n = std::min(2, plan->g.npol - pol);
     char* img = static_cast<char*>(image) + pol * plane;
     for (int w = 0; w < plan->W && r == AIDG_OK; ++w) {
       const char* G = static_cast<const char*>(grid) + ((size_t)w * plan->g.npol + pol) * plane;
-      // rows: G[gv][gu] -> A[gv][X]; transpose -> B[X][gv]; rows -> B[X][Y]; add into img[Y][X]
-      r = image_step(plan, st, kImageFft, [&] {
-        return launch_image_fft_rows(prec, +1, false, G, A, N, plan->img_fr, plan->d_img_tw,
-                                     plan->d_img_itaper, dl, 0.0, inv_l2, st);
-      });
-      if (r == AIDG_OK)
-        r = image_step(plan, st, kImageWstack, [&] { return launch_image_transpose(prec, A, B, N, st); });
-      if (r == AIDG_OK)
-        r = image_step(plan, st, kImageFft, [&] {
-          return launch_image_fft_rows(prec, +1, false, B, B, N, plan->img_fr, plan->d_img_tw,
-                                       plan->d_img_itaper, dl, 0.0, inv_l2, st);
+      // rows G[gv][gu] -> A[X][gv]; its rows into img[Y][X].  Or rows -> A[gv][X]; columns, in
+      // place, then into img[Y][X]
+      auto pass = [&](KernelClass k, ImagePass what, const void* in, void* out) {
+        if (r != AIDG_OK) return;
+        r = image_step(plan, st, k, [&] {
+          return launch_image_pass(prec, what, in, out, n, N, plan->img_fr, plan->d_img_tw, plan->d_img_itaper, dl,
+                                   plan->w0[w], inv_l2, w == 0, w == plan->W - 1 ? plan->d_nmap : nullptr, plan->g.L,
+                                   st);
         });
-      if (r == AIDG_OK)
-        r = image_step(plan, st, kImageWstack, [&] {
-          return launch_image_wstack(prec, B, img, N, plan->d_img_itaper, dl, plan->w0[w], inv_l2, w == 0,
-                                     w == plan->W - 1 ? plan->d_nmap : nullptr, plan->g.L, st);
-        });
+      };
+      pass(kImageFft, kInvertRows, G, workspace);
+      if (!image_strips(N)) pass(kImageFft, kInvertColumns, workspace, workspace);
+      pass(kImageWstack, kInvertStack, workspace, img);
     }
   }
   if (r != AIDG_OK) return r;
@@ -1066,28 +1061,24 @@ aidg_status aidg_predict(aidg_plan* plan, const void* image, void* grid, void* w
   if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent");
   const int N = plan->g.N, prec = plan->g.precision;
   const size_t plane = (size_t)N * N * plan->elem;
-  char* A = static_cast<char*>(workspace);
-  char* B = A + plane;
   const double dl = plan->g.dl, inv_l2 = 1.0 / ((double)plan->g.L * plan->g.L);
   for (int w = 0; w < plan->W && r == AIDG_OK; ++w) {
-    for (int pol = 0; pol < plan->g.npol && r == AIDG_OK; ++pol) {
+    for (int pol = 0; pol < plan->g.npol && r == AIDG_OK; pol += 2) {  // the workspace holds two planes
+      const int n = std::min(2, plan->g.npol - pol);
       const char* img = static_cast<const char*>(image) + pol * plane;
       char* G = static_cast<char*>(grid) + ((size_t)w * plan->g.npol + pol) * plane;
-      // rows of img[Y][X] times the w-term -> A[Y][gu]; transpose -> B[gu][Y];
-      // rows -> B[gu][gv]; transpose -> G[gv][gu]
-      r = image_step(plan, st, kImageFft, [&] {
-        return launch_image_fft_rows(prec, -1, true, img, A, N, plan->img_fr, plan->d_img_tw,
-                                     plan->d_img_itaper, dl, plan->w0[w], inv_l2, st);
-      });
-      if (r == AIDG_OK)
-        r = image_step(plan, st, kImageWstack, [&] { return launch_image_transpose(prec, A, B, N, st); });
-      if (r == AIDG_OK)
+      // rows of img[Y][X] times the w-term -> A[gu][Y]; its rows -> G[gv][gu].  Or rows ->
+      // A[Y][gu]; columns, in place, then -> G[gv][gu]
+      auto pass = [&](ImagePass what, const void* in, void* out) {
+        if (r != AIDG_OK) return;
         r = image_step(plan, st, kImageFft, [&] {
-          return launch_image_fft_rows(prec, -1, false, B, B, N, plan->img_fr, plan->d_img_tw,
-                                       plan->d_img_itaper, dl, 0.0, inv_l2, st);
+          return launch_image_pass(prec, what, in, out, n, N, plan->img_fr, plan->d_img_tw, plan->d_img_itaper, dl,
+                                   plan->w0[w], inv_l2, 1, nullptr, plan->g.L, st);
         });
-      if (r == AIDG_OK)
-        r = image_step(plan, st, kImageWstack, [&] { return launch_image_transpose(prec, B, G, N, st); });
+      };
+      pass(kPredictRows, img, workspace);
+      if (!image_strips(N)) pass(kPredictColumns, workspace, workspace);
+      pass(kPredictGrid, workspace, G);
     }
   }
   if (r != AIDG_OK) return r;

@@ -1,6 +1,6 @@
 // Device helpers shared by the (de)gridding kernels and the image-level kernels:
-// complex element types, the FP64-reduced phasor exp(2 pi i theta) and the radix-2/3/4/5
-// DFT butterflies of the Stockham FFTs.
+// complex element types, the FP64-reduced phasor exp(2 pi i theta) and the DFT butterflies
+// of the Stockham FFTs (radix 2, 3, 4, 5, 8, 10, 12, 16).
 #ifndef AIDG_DEVICE_COMMON_H
 #define AIDG_DEVICE_COMMON_H
 
@@ -116,6 +116,34 @@ __device__ __forceinline__ V2 quarter(V2 z) {
   return {Rt(-DIR) * z.y, Rt(DIR) * z.x};
 }
 
+// cos and sin of 2 pi k / R, at compile time (Taylor series; |x| <= pi / 4 after octants).
+template <int R>
+struct Roots {
+  double c[R], s[R];
+};
+constexpr double taylor_sin(double x) {
+  double t = x, r = x;
+  for (int i = 1; i < 12; ++i) r += t *= -x * x / ((2 * i) * (2 * i + 1));
+  return r;
+}
+constexpr double taylor_cos(double x) {
+  double t = 1, r = 1;
+  for (int i = 1; i < 12; ++i) r += t *= -x * x / ((2 * i - 1) * (2 * i));
+  return r;
+}
+template <int R>
+constexpr Roots<R> make_roots() {
+  Roots<R> r{};
+  for (int k = 0; k < R; ++k) {
+    const int q = (8 * k / R + 1) / 2;  // nearest quarter turn
+    const double x = 1.57079632679489661923 * (double)(4 * k - q * R) / R;
+    const double c = taylor_cos(x), s = taylor_sin(x);
+    r.c[k] = q % 4 == 0 ? c : q % 4 == 1 ? -s : q % 4 == 2 ? -c : s;
+    r.s[k] = q % 4 == 0 ? s : q % 4 == 1 ? c : q % 4 == 2 ? -s : -c;
+  }
+  return r;
+}
+
 // In-place DFT of R points: v[k] <- sum_j v[j] exp(DIR 2 pi i j k / R), DIR = -1
 // (forward) or +1 (inverse), unnormalised.
 template <typename V2, int R, int DIR>
@@ -166,6 +194,31 @@ __device__ __forceinline__ void butterfly(V2* v) {
       v[k] = t[0];
       v[k + 4] = t[1];
       v[k + 8] = t[2];
+    }
+  } else if constexpr (R == 10 || R == 16) {  // B DFTs of A points, then A of B
+    constexpr int A = R == 10 ? 2 : 4, B = R / A;
+    constexpr Roots<R> w = make_roots<R>();
+    V2 y[B][A];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+#pragma unroll
+      for (int a = 0; a < A; ++a) y[b][a] = v[B * a + b];
+      butterfly<V2, A, DIR>(y[b]);
+    }
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      V2 t[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int k = a * b;  // < R
+        if (k == 0) t[b] = y[b][a];
+        else if (4 * k == R) t[b] = quarter<V2, DIR>(y[b][a]);
+        else if (8 * k == R) t[b] = eighth<V2, DIR>(y[b][a]);
+        else t[b] = cmul<Rt>(y[b][a], V2{Rt(w.c[k]), Rt(DIR * w.s[k])});
+      }
+      butterfly<V2, B, DIR>(t);
+#pragma unroll
+      for (int b = 0; b < B; ++b) v[a + A * b] = t[b];
     }
   } else if constexpr (R == 3) {
     const Rt c = Rt(-0.5), dd = Rt(DIR) * Rt(0.86602540378443864676);

@@ -587,18 +587,47 @@ void kaiser_bessel_axis(int n, double beta, std::vector<double>* t) {
 
 bool image_radices(int N, int elem_bytes, ImageRadices* out) {
   if (N < 2 || N > kMaxImageN || (int64_t)N * elem_bytes > kMaxImageRowBytes) return false;
-  ImageRadices r{};
-  int n = N;
-  // odd radices first: their lane strides spread the early passes' strided LDS writes
-  // over the banks, where a stride of 4 complex values would conflict
-  for (int radix : {5, 3, 4, 2}) {
-    while (n % radix == 0) {
-      if (r.n == kMaxImageRadices) return false;
-      r.r[r.n++] = radix;
-      n /= radix;
+  int rest = N;
+  for (int p : {2, 3, 5})
+    while (rest % p == 0) rest /= p;
+  if (rest != 1) return false;
+  // best[m]: fewest passes for m points and of those the smallest sum of radices, with the
+  // radix taken last (FP64 points of more than ten would exceed the registers)
+  struct Best {
+    int passes = 1 << 20, sum = 0, radix = 0;
+  };
+  std::vector<Best> best(N + 1);
+  best[1] = {0, 0, 0};
+  for (int m = 2; m <= N; ++m) {
+    if (N % m) continue;
+    for (int radix : {2, 3, 4, 5, 8, 10, 16}) {
+      if (m % radix || radix == N || (elem_bytes > 8 && radix > 10)) continue;
+      const Best& b = best[m / radix];
+      if (b.passes + 1 < best[m].passes || (b.passes + 1 == best[m].passes && b.sum + radix < best[m].sum))
+        best[m] = {b.passes + 1, b.sum + radix, radix};
     }
   }
-  if (n != 1) return false;
+  auto factors = [&](int m, ImageFactors* f) {
+    for (; m > 1; m /= best[m].radix) {
+      if (f->n == kMaxImageRadices) return false;
+      f->r[f->n++] = best[m].radix;
+    }
+    std::sort(f->r, f->r + f->n, [](int32_t x, int32_t y) { return x > y; });  // the first needs no twiddles
+    return true;
+  };
+  ImageRadices r{};
+  int cost = 0;
+  for (int n1 = 2; n1 <= kMaxImagePart; ++n1) {
+    const int n2 = N / n1;
+    if (N % n1 || n2 < 2 || n2 > kMaxImagePart) continue;
+    // (a step of one pass would leave all but one of a column's threads idle)
+    const int c = 1000 * (std::max(best[n1].passes, 2) + std::max(best[n2].passes, 2)) + best[n1].sum + best[n2].sum;
+    if (!r.n1 || c < cost) {
+      r.n1 = n1;
+      cost = c;
+    }
+  }
+  if (!r.n1 || !factors(N, &r.row) || !factors(r.n1, &r.col1) || !factors(N / r.n1, &r.col2) || r.row.n < 2) return false;
   *out = r;
   return true;
 }
