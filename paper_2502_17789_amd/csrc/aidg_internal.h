@@ -23,14 +23,17 @@ constexpr int64_t kStaticWorkspaceBytes = int64_t(128) << 20;
 // A group of same-centre subgrids holds at most this many times the mean
 // visibilities per centre (and at least one subgrid).
 constexpr int64_t kGroupVisFactor = 8;
+// A part of a group costs the gridder at least this much (one subgrid excepted): three
+// subgrids of up to 32 visibilities.
+constexpr int64_t kMinPartCost = 156;
 
 // Per-subgrid record the kernels read (device copy of the partition).
 struct alignas(16) SubgridDev {
   int32_t t0, nt, c0, nc;      // sub-table
   int32_t U0, V0, wlayer, R;   // centre cell, layer, reseed interval (1: every channel)
-  int32_t ap, aq, bl, group;   // A-term plane index (aint * n_st + station) of the left and
-                               // right station (swapped for a folded sub-table); baseline;
-                               // (layer, centre) group in the plan's order
+  int32_t ap, aq, part, group; // A-term plane index (aint * n_st + station) of the left and
+                               // right station (swapped for a folded sub-table); part of
+                               // its group and (layer, centre) group, in the plan's order
   int64_t vis0;                // flat visibility index of (bl, t0, c0)
   int64_t uvw0;                // flat uvw row index of (bl, t0); folded sub-tables index the
                                // negated copy that follows the table
@@ -113,6 +116,7 @@ struct KernelArgs {
   const uint32_t* axis_b;   // device [L]
   const float2* taper_cross;  // device [L][L]
   const int64_t* grp_begin; // device [n_groups + 1]: first subgrid of each (layer, centre) group
+  const int64_t* part_begin;  // device [n_parts + 1]: the same of each part of a group
   int nt_total, nc_total, N;
   int npol;                 // grid planes: 4 (XX, XY, YX, YY) or 1 (Stokes I)
   double du;                // uv cell size, wavelengths
@@ -124,7 +128,9 @@ struct KernelArgs {
 // same w-layer and centre are consecutive (a "group"); the gridder, FFT/adder and
 // splitter/inverse FFT run one workgroup slot per group (slots gslot_begin..), the
 // degridder one slot per subgrid (slots slot_begin..).  Group g of a range owns
-// scratch slot gslot_begin + (g - g_first): its subgrid image sum, [4][L][L].
+// scratch slot gslot_begin + (g - g_first): its subgrid image sum, [4][L][L].  A launch
+// with `split` grids by the parts of groups instead (slots pslot_begin.., scratch slot
+// pslot_begin + (p - p_first)), and the adder sums the images of a group's parts.
 constexpr int kMaxGroup = 16;
 struct JobRef {
   const KernelArgs* args;   // device copy of the plan's parameters
@@ -137,13 +143,17 @@ struct JobRef {
   int32_t adjoint;          // 1: the exact adjoint of the other direction (Stokes-I plans
                             // grid XX + YY and split into diag(I, I) / 2)
   int32_t pad;
+  int64_t p_first;          // part of subgrid sg_begin
+  int64_t pslot_begin;      // first per-part slot of the range in this launch
 };
 struct Group {
   int32_t n;
   int32_t matrix;           // 1: the matrix kernels take the launch's DFTs
   int64_t total_sg;         // per-subgrid slots in the launch
-  int64_t total_grp;        // per-group slots (scratch images) in the launch
-  void* scratch;            // [total_grp][4][L][L] subgrid images
+  int64_t total_grp;        // per-group slots in the launch
+  int64_t total_part;       // per-part slots in the launch
+  int32_t split, pad;       // 1 (gridding): parts of groups
+  void* scratch;            // [total_grp or total_part][4][L][L] subgrid images
   JobRef job[kMaxGroup];
 };
 

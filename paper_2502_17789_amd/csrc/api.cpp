@@ -82,6 +82,13 @@ struct aidg_plan {
   // batch_begin[b+1]) in subgrids, at most `batch` groups each.
   std::vector<int64_t> grp_begin, batch_begin;
   std::vector<int32_t> sg_group;
+  // Gridding may take a group in parts [part_begin[p], part_begin[p + 1]) (sg_part: a
+  // subgrid's; the groups themselves where no part is worth it), see split_groups.
+  // cost_prefix: prefix sums of the gridder's cost over the table; max_group_cost.
+  std::vector<int64_t> part_begin, cost_prefix;
+  std::vector<int32_t> sg_part;
+  int64_t max_group_cost = 0;
+  bool split = false;  // the plan's own calls grid by parts (all of them fit the workspace)
   int64_t batch = 1;
   size_t elem = 8, aterm_bytes = 0, device_bytes = 0, scratch_bytes = 0;
   SubgridDev* d_sg = nullptr;
@@ -142,6 +149,7 @@ struct aidg_plan {
     a.axis_b = reinterpret_cast<const uint32_t*>(d_tables + tl.axis_b);
     a.taper_cross = reinterpret_cast<const float2*>(d_tables + tl.taper_cross);
     a.grp_begin = d_grp;
+    a.part_begin = d_grp + (part_begin.size() == grp_begin.size() ? 0 : grp_begin.size());
     a.nt_total = nt;
     a.nc_total = nc;
     a.N = g.N;
@@ -239,6 +247,50 @@ struct TimedLaunch {
   }
 };
 
+// Gridder cost of a subgrid, in visibilities: the matrix gridder takes 32 at a time, and the
+// Jones epilogue about as long as 20.
+int64_t grid_cost(const aidg_subgrid& s) { return std::max(s.nt * s.nc, 32) + 20; }
+
+// Gridder workgroups in flight over the chip, in units of a group's (L / 32 per group; 256
+// compute units hold three at L = 32, two beyond).
+int64_t groups_in_flight(int L) { return L <= 32 ? 768 : 512 / (L / 32); }
+
+// Whether the heaviest group outlasts the launch's work spread evenly by enough: 2.5 times.
+// By less gains nothing, as the last workgroups of a launch run faster, with a compute unit
+// to themselves, and the sum of the parts takes a launch (at 1.2 and 1.3 times 2179 and 1095
+// us split, 2151 and 1067 whole; at 2 times 53 and 58 without the sum's 5 to 17).  400
+// visibilities are about 30 us of a workgroup at L = 32, 20 to 30 of them to be gained (30 us
+// of 370 groups: 33 split, 30 whole; 37 of 484: 27).  Measured at more: 52 groups of 2664
+// subgrids, L = 32, 788 us whole, 45 split; 13 of 703, L = 96, 1058 and 100; FP64, 19 groups,
+// L = 96, 4089 and 1221; 156 heavy ones, L = 64, 7705 and 2073.
+bool worth_split(int L, int64_t max_cost, int64_t total) {
+  return 2 * max_cost * groups_in_flight(L) > 5 * total && max_cost * L > 400 * 32;
+}
+
+// Split the groups into parts for the gridder: one workgroup per group leaves the chip to
+// the heaviest ones where groups are few or uneven.  Parts of half the work that evenly
+// falls to a workgroup in flight, but not of less than three subgrids' least.
+void split_groups(aidg_plan* p) {
+  const auto& t = p->table;
+  const size_t n = t.size(), groups = p->grp_begin.size() - 1;
+  p->cost_prefix.assign(n + 1, 0);
+  for (size_t i = 0; i < n; ++i) p->cost_prefix[i + 1] = p->cost_prefix[i] + grid_cost(t[i]);
+  const int64_t total = p->cost_prefix[n];
+  for (size_t k = 0; k < groups; ++k)
+    p->max_group_cost = std::max(p->max_group_cost, p->cost_prefix[p->grp_begin[k + 1]] - p->cost_prefix[p->grp_begin[k]]);
+  p->part_begin = p->grp_begin;
+  p->sg_part = p->sg_group;
+  const int64_t cap = std::max<int64_t>(kMinPartCost, total / (2 * groups_in_flight(p->g.L)));
+  if (!worth_split(p->g.L, p->max_group_cost, total) || p->max_group_cost <= cap) return;
+  p->part_begin.assign(1, 0);
+  for (size_t k = 0; k < groups; ++k)
+    for (int64_t b = p->grp_begin[k], e = b; b < p->grp_begin[k + 1]; b = e) {
+      for (; e < p->grp_begin[k + 1] && (e == b || p->cost_prefix[e + 1] - p->cost_prefix[b] <= cap); ++e)
+        p->sg_part[e] = (int32_t)p->part_begin.size() - 1;
+      p->part_begin.push_back(e);
+    }
+}
+
 // Launch one kernel class over subgrids [b0, b0 + n) of one plan.
 aidg_status run(aidg_plan* p, KernelClass k, int64_t b0, int64_t n, const void* in, void* out,
                 void* stream, int adjoint = 0) {
@@ -254,8 +306,10 @@ aidg_status run(aidg_plan* p, KernelClass k, int64_t b0, int64_t n, const void* 
     g.matrix = k == kGridDft ? p->matrix_grid : p->matrix_degrid;
     g.total_sg = n;
     g.total_grp = p->sg_group[b0 + n - 1] - p->sg_group[b0] + 1;
+    g.total_part = p->sg_part[b0 + n - 1] - p->sg_part[b0] + 1;
+    g.split = p->split && (k == kGridDft || k == kFftAdd);
     g.scratch = p->d_scratch;
-    g.job[0] = {p->d_args, in, out, b0, b0 + n, p->sg_group[b0], 0, 0, adjoint, 0};
+    g.job[0] = {p->d_args, in, out, b0, b0 + n, p->sg_group[b0], 0, 0, adjoint, 0, p->sg_part[b0], 0};
     rc = launch_group(k, p->g.L, p->g.precision, g, stream, p->max_nv);
   }
   if (rc != 0) return hip_fail((hipError_t)rc, "kernel launch");
@@ -408,6 +462,20 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
     const bool mx = matrix(items[i0].plan);
     const int64_t per_sg = (int64_t)4 * L * L * (prec == AIDG_FP32 ? 8 : 16);
     const int64_t cap = std::min<int64_t>(scratch_bytes / per_sg, 65535);
+    // grid by parts where they fit one launch's images and the heaviest group of the items
+    // would outlast the others
+    int64_t parts = 0, items_cost = 0, max_cost = 0;
+    for (int32_t i = i0; i < n_items && dir == AIDG_DIR_GRID; ++i) {
+      const aidg_work& w = items[i];
+      const aidg_plan* p = w.plan;
+      if (done[i] || w.direction != dir || p->g.L != L || p->g.precision != prec || matrix(p) != mx ||
+          w.sg_begin == w.sg_end)
+        continue;
+      parts += p->sg_part[w.sg_end - 1] - p->sg_part[w.sg_begin] + 1;
+      items_cost += p->cost_prefix[w.sg_end] - p->cost_prefix[w.sg_begin];
+      max_cost = std::max(max_cost, p->max_group_cost);
+    }
+    const bool split = parts > 0 && parts <= cap && worth_split(L, max_cost, items_cost);
     if (cap < 1) {
       r = fail(AIDG_E_INVALID, "workspace smaller than one subgrid image");
       break;
@@ -416,6 +484,7 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
     std::memset(&g, 0, sizeof(g));
     g.scratch = scratch;
     g.matrix = mx;
+    g.split = split;
     int max_nv = 1;
     auto flush = [&]() -> aidg_status {
       if (g.total_sg == 0) return AIDG_OK;
@@ -426,6 +495,7 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
       std::memset(&g, 0, sizeof(g));
       g.scratch = scratch;
       g.matrix = mx;
+      g.split = split;
       max_nv = 1;
       return rc == 0 ? AIDG_OK : hip_fail((hipError_t)rc, "grouped kernel launch");
     };
@@ -443,10 +513,11 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
         const int64_t g0 = p->sg_group[b], room = cap - g.total_grp;
         const int64_t gn = (int64_t)p->grp_begin.size() - 1;
         const int64_t e = g0 + room < gn ? std::min(w.sg_end, p->grp_begin[g0 + room]) : w.sg_end;
-        g.job[g.n] = {p->d_args, w.in, w.out, b, e, g0, g.total_sg, g.total_grp, 0, 0};
+        g.job[g.n] = {p->d_args, w.in, w.out, b, e, g0, g.total_sg, g.total_grp, 0, 0, p->sg_part[b], g.total_part};
         g.n += 1;
         g.total_sg += e - b;
         g.total_grp += p->sg_group[e - 1] - g0 + 1;
+        g.total_part += p->sg_part[e - 1] - p->sg_part[b] + 1;
         max_nv = std::max(max_nv, p->max_nv);
         b = e;
       }
@@ -617,6 +688,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       }
       t.swap(ordered);
     }
+    split_groups(plan);
     plan->max_nv = 1;
     plan->vp_prefix.assign(plan->table.size() + 1, 0);
     for (size_t i = 0; i < plan->table.size(); ++i) {
@@ -658,7 +730,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       d.wlayer = s.wlayer;
       d.ap = s.aint * n_stations + (s.folded ? s.st2 : s.st1);
       d.aq = s.aint * n_stations + (s.folded ? s.st1 : s.st2);
-      d.bl = s.bl;
+      d.part = plan->sg_part[i];
       d.vis0 = s.vis_offset;
       d.uvw0 = (int64_t)s.bl * n_times + s.t0 + (s.folded ? (int64_t)uvw_rows : 0);
       d.fold = s.folded;
@@ -775,9 +847,12 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     plan->aterm_bytes = (size_t)plan->n_int * n_stations * L * L * 4 * plan->elem;
     const size_t per_sg = (size_t)4 * L * L * plan->elem;
     const int64_t nsg = (int64_t)plan->table.size();
-    const int64_t n_groups = (int64_t)plan->grp_begin.size() - 1;
+    const int64_t n_groups = (int64_t)plan->grp_begin.size() - 1, n_parts = (int64_t)plan->part_begin.size() - 1;
+    std::vector<int64_t> index(plan->grp_begin);
+    if (n_parts > n_groups) index.insert(index.end(), plan->part_begin.begin(), plan->part_begin.end());
     plan->batch = std::max<int64_t>(1, std::min<int64_t>(g.workspace / (int64_t)per_sg, 65535));
-    plan->batch = std::min<int64_t>(plan->batch, std::max<int64_t>(n_groups, 1));
+    plan->split = n_parts > n_groups && n_parts <= plan->batch;
+    plan->batch = std::min<int64_t>(plan->batch, std::max<int64_t>(plan->split ? n_parts : n_groups, 1));
     plan->scratch_bytes = (size_t)plan->batch * per_sg;
     plan->batch_begin.clear();
     for (int64_t k = 0; k < n_groups; k += plan->batch) plan->batch_begin.push_back(plan->grp_begin[k]);
@@ -806,7 +881,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         (st = dalloc(&plan->d_aterms, plan->aterm_bytes, plan, "A-terms", stream)) ||
         (st = dalloc(&plan->d_tables, tables.size(), plan, "tables", stream)) ||
         (st = dalloc(&plan->d_excl, pr.excluded.size() * sizeof(int64_t), plan, "excluded list", stream)) ||
-        (st = dalloc(&plan->d_grp, plan->grp_begin.size() * sizeof(int64_t), plan, "group index", stream)) ||
+        (st = dalloc(&plan->d_grp, index.size() * sizeof(int64_t), plan, "group index", stream)) ||
         (st = dalloc(&plan->d_scratch, plan->scratch_bytes, plan, "subgrid workspace", stream)) ||
         (st = dalloc(&plan->d_args, sizeof(KernelArgs), plan, "launch parameters", stream)) ||
         (plan->img_ok &&
@@ -835,7 +910,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         {plan->d_aterms, aterms, plan->aterm_bytes, hipMemcpyDeviceToDevice},
         {plan->d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice},
         {plan->d_excl, pr.excluded.data(), pr.excluded.size() * sizeof(int64_t), hipMemcpyHostToDevice},
-        {plan->d_grp, plan->grp_begin.data(), plan->grp_begin.size() * sizeof(int64_t), hipMemcpyHostToDevice},
+        {plan->d_grp, index.data(), index.size() * sizeof(int64_t), hipMemcpyHostToDevice},
         {plan->d_args, &host_args, sizeof(KernelArgs), hipMemcpyHostToDevice},
         {plan->d_img_tw, f32 ? (const void*)img_twf.data() : (const void*)img_tw.data(),
          plan->img_ok ? (size_t)g.N * plan->elem : 0, hipMemcpyHostToDevice},
@@ -986,10 +1061,18 @@ aidg_status aidg_footprint_estimate(const aidg_geometry* geo, int32_t n_stations
     // what aidg_plan_create allocates, each allocation at least 256 bytes
     auto al = [](int64_t b) { return std::max<int64_t>(b, 256); };
     const int64_t per_image = 4 * L * L * elem;
-    const int64_t batch = std::max<int64_t>(1, std::min<int64_t>({g.workspace / per_image, 65535, se.n_groups}));
+    // parts of groups beyond one each: none where the cap on groups keeps them even
+    int64_t parts = 0;
+    if (5 * se.n_groups < 2 * kGroupVisFactor * groups_in_flight((int)L)) {
+      const int64_t total = n_vis + 20 * n_sg;
+      const int64_t cap = std::max<int64_t>(kMinPartCost, total / (2 * groups_in_flight((int)L)));
+      parts = std::max<int64_t>(0, std::min(n_sg - se.n_groups, total / cap));
+    }
+    int64_t batch = std::max<int64_t>(1, std::min<int64_t>(g.workspace / per_image, 65535));
+    batch = std::min(batch, std::max<int64_t>(1, se.n_groups + (se.n_groups + parts <= batch ? parts : 0)));
     int64_t b = al(n_sg * (int64_t)sizeof(SubgridDev)) + al((int64_t)n_baselines * n_times * 24 * (g.fold ? 2 : 1)) +
                 al((int64_t)n_chans * 8) + out->aterm_bytes + al((int64_t)TableLayout(g.L, (size_t)elem).bytes) +
-                al(se.n_excluded * 8) + al((n_sg + 1) * 8) + al(batch * per_image) + al(sizeof(KernelArgs));
+                al(se.n_excluded * 8) + al((n_sg + 1) * 8 * (parts ? 2 : 1)) + al(batch * per_image) + al(sizeof(KernelArgs));
     if (N <= kMaxImageN) b += al(N * elem) + al(N * 8);
     if (g.amode) {
       const int64_t pairs = std::min<int64_t>(n_sg, (int64_t)n_int * n_baselines);

@@ -125,8 +125,8 @@ void grid_dft(const Group g) {
   int64_t local;
   int chunk;
   grid_work<(L * L) / kChunk>(blockIdx.x, &local, &chunk);
-  if (local >= g.total_grp) return;  // padding of the last XCD round (whole workgroup)
-  const GroupSlot gs = resolve_group(g, local);
+  if (local >= (g.split ? g.total_part : g.total_grp)) return;  // padding of the last XCD round (whole workgroup)
+  const GroupSlot gs = resolve_group(g, local, g.split != 0);
   const KernelArgs& a = gs.a;
   const R* __restrict__ vis = reinterpret_cast<const R*>(gs.in);
   R* __restrict__ scratch = reinterpret_cast<R*>(g.scratch);
@@ -422,6 +422,33 @@ __device__ __forceinline__ void fft_plane(V2* buf, const V2* tw, const Load& loa
   stockham_pass<L, r1, r0, DIR, V2>(tw, row, put_row);
 }
 
+// Adds the images of each group's parts into the first's, in order.  (In the adder, whose
+// workgroups are few where groups are, the sum alone took 150 us: 52 groups, L = 32.)
+template <int L, typename R>
+__global__ __launch_bounds__(kThreads) void sum_parts(const Group g) {
+  using V4 = typename C4<R>::T;
+  const GroupSlot gs = resolve_group(g, blockIdx.y);
+  const int first = load_uniform(gs.a.sg + gs.sb).part, parts = load_uniform(gs.a.sg + gs.se - 1).part - first + 1;
+  if (parts == 1) return;
+  constexpr int n = 4 * L * L / 2;  // two complex values each
+  const int planes = gs.a.npol == 1 ? 1 : 4;
+  V4* img = reinterpret_cast<V4*>(g.scratch) +
+            (g.job[gs.job].pslot_begin + (first - g.job[gs.job].p_first)) * n;
+  const int e = blockIdx.x * kThreads + threadIdx.x;  // (L^2 / 2 is a multiple of kThreads)
+  if (e >= n / 4 * planes) return;
+  V4 sum = img[e];
+  int i = 1;
+  for (; i + 8 <= parts; i += 8) {
+    V4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = img[(size_t)(i + j) * n + e];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum = sum + v[j];
+  }
+  for (; i < parts; ++i) sum = sum + img[(size_t)i * n + e];
+  img[e] = sum;
+}
+
 template <int L, typename R>
 __global__ __launch_bounds__(Radices<L>::threads) void fft_add(const Group g) {
   using V2 = typename C2<R>::T;
@@ -435,7 +462,9 @@ __global__ __launch_bounds__(Radices<L>::threads) void fft_add(const Group g) {
   if (pol >= a.npol) return;  // a Stokes-I plan has one plane (whole workgroup)
   const SubgridDev s = load_uniform(a.sg + gs.sb);  // centre and w-layer of the group
   R* grid = reinterpret_cast<R*>(gs.out);
-  const V2* in = reinterpret_cast<const V2*>(g.scratch) + (local * 4 + pol) * L * L;
+  // the group's image: with its first part (sum_parts)
+  const int64_t slot = g.split ? g.job[gs.job].pslot_begin + (s.part - g.job[gs.job].p_first) : local;
+  const V2* in = reinterpret_cast<const V2*>(g.scratch) + (slot * 4 + pol) * L * L;
   for (int e = threadIdx.x; e < L; e += T) tw[e] = reinterpret_cast<const V2*>(a.twiddle)[e];
   fft_plane<L, -1>(buf, tw, [&](int y, int x) -> V2 { return in[y * L + x]; });
   R* win = grid + 2 * ((((int64_t)s.wlayer * a.npol + pol) * a.N + (s.V0 - L / 2)) * a.N + (s.U0 - L / 2));
@@ -965,13 +994,28 @@ __global__ void zero_vis(const int64_t* __restrict__ idx, int64_t n, R* vis) {
   if (i < n * 8) vis[idx[i / 8] * 8 + i % 8] = 0;
 }
 
+template <typename R>
+int launch_sum(int L, const Group& g, hipStream_t st) {
+  const dim3 grid((unsigned)(4 * L * L / 2 / kThreads), (unsigned)g.total_grp);
+  switch (L) {
+    case 32: hipLaunchKernelGGL((sum_parts<32, R>), grid, dim3(kThreads), 0, st, g); break;
+    case 64: hipLaunchKernelGGL((sum_parts<64, R>), grid, dim3(kThreads), 0, st, g); break;
+    case 96: hipLaunchKernelGGL((sum_parts<96, R>), grid, dim3(kThreads), 0, st, g); break;
+  }
+  return (int)hipGetLastError();
+}
+int launch_sum(int L, int precision, const Group& g, hipStream_t st) {
+  return precision == AIDG_FP32 ? launch_sum<float>(L, g, st) : launch_sum<double>(L, g, st);
+}
+
 template <int L, typename R>
 int launch_one(KernelClass k, const Group& g, hipStream_t st, int max_nv) {
-  const unsigned n = (unsigned)(k == kDegridDft ? g.total_sg : g.total_grp);
+  const unsigned n = (unsigned)(k == kDegridDft ? g.total_sg : k == kGridDft && g.split ? g.total_part : g.total_grp);
   switch (k) {
     case kGridDft:
       hipLaunchKernelGGL((grid_dft<L, R>), dim3((n + kXcds - 1) / kXcds * kXcds * ((L * L) / (kThreads * GridTune<R>::PIX))),
                          dim3(kThreads), (size_t)max_nv * 8 * sizeof(R), st, g);
+      if (g.split) return launch_sum(L, std::is_same_v<R, float> ? AIDG_FP32 : AIDG_FP64, g, st);
       break;
     case kFftAdd:
       hipLaunchKernelGGL((fft_add<L, R>), dim3(4, n), dim3(Radices<L>::threads), 0, st, g);
@@ -1039,9 +1083,13 @@ int32_t degrid_form(const Geometry& g, int nt, int nc, bool uniform) {
 int launch_group(KernelClass k, int L, int precision, const Group& g, void* stream, int max_nv) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (g.total_sg <= 0) return 0;
-  if (g.n < 1 || g.n > kMaxGroup || g.total_grp < 1 || g.total_grp > 65535 || g.total_grp > g.total_sg)
+  if (g.n < 1 || g.n > kMaxGroup || g.total_grp < 1 || g.total_grp > 65535 || g.total_grp > g.total_sg ||
+      (g.split && (g.total_part < g.total_grp || g.total_part > g.total_sg)))
     return (int)hipErrorInvalidValue;
-  if (g.matrix && (k == kGridDft || k == kDegridDft)) return launch_matrix(k, L, g, stream);
+  if (g.matrix && (k == kGridDft || k == kDegridDft)) {
+    const int rc = launch_matrix(k, L, g, stream);
+    return rc == 0 && k == kGridDft && g.split ? launch_sum(L, precision, g, st) : rc;
+  }
   if (precision == AIDG_FP32) {
     switch (L) {
       case 32: return launch_one<32, float>(k, g, st, max_nv);

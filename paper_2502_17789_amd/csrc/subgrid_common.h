@@ -72,24 +72,28 @@ __device__ __forceinline__ T load_uniform(const T* p) {
   return r;
 }
 
-// Group slot of a grouped launch: the plan's parameters and its subgrid range.
+// Group slot of a grouped launch (or slot of a part of a group): the plan's parameters and
+// its subgrid range.
 struct GroupSlot {
   KernelArgs a;
-  int64_t sb, se;  // subgrids [sb, se) of the group within the job's range
+  int64_t sb, se;  // subgrids [sb, se) of the group or part within the job's range
+  int job;
   const void* in;
   void* out;
   int adjoint;
 };
-__device__ __forceinline__ GroupSlot resolve_group(const Group& g, int64_t slot) {
+__device__ __forceinline__ GroupSlot resolve_group(const Group& g, int64_t slot, bool parts = false) {
   int j = 0;
   for (int i = 1; i < g.n; ++i)
-    if (slot >= g.job[i].gslot_begin) j = i;
+    if (slot >= (parts ? g.job[i].pslot_begin : g.job[i].gslot_begin)) j = i;
   GroupSlot r;
+  r.job = j;
   r.a = load_uniform(g.job[j].args);
-  const int64_t grp = g.job[j].g_first + (slot - g.job[j].gslot_begin);
-  const_view<int64_t> gb = as_const(r.a.grp_begin);
-  r.sb = max(gb[grp], g.job[j].sg_begin);
-  r.se = min(gb[grp + 1], g.job[j].sg_end);
+  const int64_t k = parts ? g.job[j].p_first + (slot - g.job[j].pslot_begin)
+                          : g.job[j].g_first + (slot - g.job[j].gslot_begin);
+  const_view<int64_t> begin = as_const(parts ? r.a.part_begin : r.a.grp_begin);
+  r.sb = max(begin[k], g.job[j].sg_begin);
+  r.se = min(begin[k + 1], g.job[j].sg_end);
   r.in = uniform(g.job[j].in);
   r.out = uniform(g.job[j].out);
   r.adjoint = uniform(g.job[j].adjoint);

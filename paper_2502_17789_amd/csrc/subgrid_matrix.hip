@@ -197,8 +197,8 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
   int64_t local;
   int chunk;
   grid_work<L / kRows>(blockIdx.x, &local, &chunk);
-  if (local >= g.total_grp) return;  // padding of the last XCD round (whole workgroup)
-  const GroupSlot gs = resolve_group(g, local);
+  if (local >= (g.split ? g.total_part : g.total_grp)) return;  // padding of the last XCD round (whole workgroup)
+  const GroupSlot gs = resolve_group(g, local, g.split != 0);
   const KernelArgs& a = gs.a;
   const bool inv = a.ainvh != nullptr;
   const char* At = static_cast<const char*>(inv ? a.ainvh : a.aterms);
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 template <int L>
 int launch_one(KernelClass k, const Group& g, hipStream_t st) {
   if (k == kGridDft) {
-    const unsigned n = (unsigned)g.total_grp;
+    const unsigned n = (unsigned)(g.split ? g.total_part : g.total_grp);
     hipLaunchKernelGGL((grid_matrix<L>), dim3((n + kXcds - 1) / kXcds * kXcds * (L / kRows)), dim3(kThreads),
                        sizeof(GridLds<L>), st, g);
   } else {
