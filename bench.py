@@ -32,12 +32,16 @@ if ROOT not in sys.path:
 # Algorithmic work per (visibility, subgrid pixel) in the method's form: the 2x2
 # complex multiply-accumulate is 16 FP32 FMAs, the phasor step ph <- ph * step is 4
 # FP32 ops (2 mul + 2 FMA); each occupies one FMA issue slot, counted as 2 FLOP: 40.
-# Both kernels pair a recurrence run's channels symmetrically about its centre, so
-# two visibilities take 16 FMA per pixel with real multipliers and one complex phasor
-# step (6 FLOP): 19 FLOP per (visibility, pixel) executed.  Rates are reported at both
-# counts.
+# Executed: the FP32 kernels form the sums as complex matrix products on the matrix cores,
+# 16 real multiply-adds per (visibility, pixel) and product, three products of FP16 halves
+# (hi hi, hi lo, lo hi) and one for the first term of the w series (the order of nearly all
+# subgrids here): 128 FLOP.  The FP64 kernels pair a recurrence run's channels
+# symmetrically about its centre, so two visibilities take 16 FMA per pixel with real
+# multipliers and one complex phasor step (6 FLOP): 19.
 FLOP_PER_VP = 40
-FLOP_PER_VP_EXECUTED = {"grid_dft": 19, "degrid_dft": 19}
+FLOP_PER_VP_EXECUTED = {"fp32": 128, "fp64": 19}
+# Dense FP16 matrix peak of MI355X: 256 CUs x 4 SIMDs x 1024 FLOP per clock x 2.4 GHz.
+PEAK_FP16_MATRIX_TFLOPS = 256 * 4 * 1024 * 2.4e9 / 1e12   # 2516.6
 # FP32 vector peak of MI355X: 256 CUs x 4 SIMDs x 2.4 GHz, each SIMD issuing up to
 # two wave64 VALU instructions per 4 cycles (gfx950 VALU dual issue, counted by
 # SQ_ACTIVE_INST_VALU2) = 128 FMA per clock per CU = 157.3 TFLOP/s at 2 FLOP/FMA.
@@ -99,9 +103,11 @@ def summarize_traffic(copy_fetch: str, copy_write: str, run_fetch: str, run_writ
         return tot, n
 
     def short(name):
-        for k in ("degrid_dft", "grid_dft", "fft_add", "split_ifft", "copyBuffer"):
+        for k, what in (("degrid_matrix", "degrid_dft"), ("grid_matrix", "grid_dft"), ("degrid_dft", "degrid_dft"),
+                        ("grid_dft", "grid_dft"), ("fft_add", "fft_add"), ("split_ifft", "split_ifft"),
+                        ("copyBuffer", "copyBuffer")):
             if k in name:
-                return k
+                return what
         return None
 
     cf, cn = counters(copy_fetch)
@@ -514,6 +520,8 @@ def _kernel_case(aidg, wl, prec, L, lattice=0, form=0, reps=2, reseed=0):
     n = wl.n_vis
     t_grid = ms["grid_dft"] + ms["fft_add"]
     t_degrid = ms["split_ifft"] + ms["degrid_dft"]
+    matrix = {"grid_dft": prec == aidg.FP32, "degrid_dft": prec == aidg.FP32 and form == 0}
+    flop = {k: FLOP_PER_VP_EXECUTED["fp32" if matrix[k] else "fp64"] for k in matrix}
     return {
         "subgrid_size": L, "kernel_support": L // 4, "center_lattice": lattice or "auto",
         "precision": "fp32" if prec == aidg.FP32 else "fp64",
@@ -525,7 +533,7 @@ def _kernel_case(aidg, wl, prec, L, lattice=0, form=0, reps=2, reseed=0):
         "grid_mvis_s": round(n / (t_grid * 1e-3) / 1e6, 1),
         "degrid_mvis_s": round(n / (t_degrid * 1e-3) / 1e6, 1),
         "ms": {k: round(v, 3) for k, v in ms.items() if v > 0},
-        "dft_tflops": {k: round(kt[k]["vis_pixels"] * FLOP_PER_VP_EXECUTED[k] / (ms[k] * reps * 1e-3) / 1e12, 2)
+        "dft_tflops": {k: round(kt[k]["vis_pixels"] * flop[k] / (ms[k] * reps * 1e-3) / 1e12, 2)
                        for k in ("grid_dft", "degrid_dft")}}
 
 
@@ -581,8 +589,7 @@ def image_bench(args):
     MWA-like grid (N = 8000, the plan's w-layers), FP32: aidg_invert and aidg_predict
     timed with HIP events around every launch.  Each kernel class's effective
     bandwidth is the bytes its launches read and write (one N x N plane in and one
-    out per row-FFT pass or transpose; the w-stacking pass also reads the image it
-    adds to) over their time."""
+    out per pass; the w-stacking pass also reads the image it adds to) over their time."""
     import torch
 
     import paper_2502_17789_amd as aidg
@@ -654,15 +661,15 @@ def dataclasses_replace(obj, **kw):
 
 
 def path_roofline(kt, wall_s):
-    """Sustained rate of the whole timed step: both DFT kernels' executed FLOP (19 per
-    vp in the paired-channel form) over the wall time, which also covers the FFTs, the
-    adder, the splitter and the zeroing kernels."""
-    flop = sum(kt[k]["vis_pixels"] * FLOP_PER_VP_EXECUTED[k] for k in ("grid_dft", "degrid_dft"))
+    """Sustained rate of the whole timed step: both DFT kernels' executed matrix-core FLOP
+    over the wall time, which also covers the FFTs, the adder, the splitter and the zeroing
+    kernels."""
+    flop = sum(kt[k]["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"] for k in ("grid_dft", "degrid_dft"))
     achieved = flop / wall_s / 1e12
-    return {"achieved": round(achieved, 3), "peak": round(PEAK_FP32_TFLOPS, 1), "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
-            "scope": "grid_dft + degrid_dft executed FLOP (19 per vp each, paired-channel form) over the "
-                     "wall time of the timed steps"}
+    return {"achieved": round(achieved, 3), "peak": round(PEAK_FP16_MATRIX_TFLOPS, 1), "unit": "TFLOP/s",
+            "frac": round(achieved / PEAK_FP16_MATRIX_TFLOPS, 4),
+            "scope": "grid_dft + degrid_dft executed FP16 matrix FLOP (128 per vp each) over the wall time "
+                     "of the timed steps"}
 
 
 # Rates of the survey's roofline definition: FP32 FMA at the dual-issue peak, FP64 FMA at
@@ -782,13 +789,12 @@ def main():
     dom = max(("grid_dft", "degrid_dft", "fft_add", "split_ifft"), key=lambda k: kt[k]["ms"])
     k = kt[dom]
     if dom in ("grid_dft", "degrid_dft"):
-        achieved = k["vis_pixels"] * FLOP_PER_VP / (k["ms"] * 1e-3) / 1e12
-        roof = {"kernel": dom, "bound": "alu", "achieved": round(achieved, 3),
-                "peak": round(PEAK_FP32_TFLOPS, 1), "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": measured_traffic(dom),
-                "frac_of_single_issue": round(achieved / PEAK_FP32_SINGLE_ISSUE_TFLOPS, 4),
-                "frac_executed": round(k["vis_pixels"] * FLOP_PER_VP_EXECUTED[dom] / (k["ms"] * 1e-3) / 1e12
-                                       / PEAK_FP32_TFLOPS, 4),
+        achieved = k["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"] / (k["ms"] * 1e-3) / 1e12
+        method = k["vis_pixels"] * FLOP_PER_VP / (k["ms"] * 1e-3) / 1e12
+        roof = {"kernel": dom, "bound": "mfma", "achieved": round(achieved, 3),
+                "peak": round(PEAK_FP16_MATRIX_TFLOPS, 1), "unit": "TFLOP/s",
+                "frac": round(achieved / PEAK_FP16_MATRIX_TFLOPS, 4), "traffic": measured_traffic(dom),
+                "method_of_fp32_vector_peak": round(method / PEAK_FP32_TFLOPS, 4),
                 "avg_launch_ms": round(k["ms"] / max(k["launches"], 1), 4),
                 "launches": k["launches"]}
     else:
@@ -800,7 +806,7 @@ def main():
     kernels = {name: {"ms_per_step": round(v["ms"] / args.steps, 3),
                       "launches_per_step": v["launches"] / args.steps,
                       **({"tflops": round(v["vis_pixels"] * FLOP_PER_VP / (v["ms"] * 1e-3) / 1e12, 3),
-                          "tflops_executed": round(v["vis_pixels"] * FLOP_PER_VP_EXECUTED[name]
+                          "tflops_executed": round(v["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"]
                                                    / (v["ms"] * 1e-3) / 1e12, 3)}
                          if name in ("grid_dft", "degrid_dft") and v["ms"] > 0 else {})}
                for name, v in kt.items()}

@@ -4,6 +4,10 @@
 // consecutive groups; a grouped launch covers subgrid ranges of up to 16 plans,
 // with one scratch image slot per group.
 //
+// The two DFTs of FP32 plans go to the matrix cores (subgrid_matrix.hip) where every subgrid's
+// w range allows and, degridding, the subgrids are not too sparse; grid_dft and degrid_dft
+// here take the rest.
+//
 // Gridding of a batch (Sec. 2.5 imaging, steps 2a-2c):
 //   grid_dft   one workgroup per (pixel chunk, group); each lane owns 4 subgrid
 //              pixels (2 in FP64) of the chunk.  For every subgrid of the group the
@@ -16,8 +20,9 @@
 //              an FP64 phase reduced to a quarter turn (Eq. withw).  The subgrid's
 //              T (-1)^(x+y) A_p^H S A_q (Sec. 3.3) is added into the group's image slot.
 //   fft_add    one workgroup per (polarisation, group): Stockham FFT of the L x L
-//              plane in LDS (radix 4/2/3), then (-1)^(a+b) and an atomic add onto
-//              the group's window of its w-layer (Eq. shiftback).
+//              plane in LDS (two passes per axis), then (-1)^(a+b) and an atomic add
+//              onto the group's window of its w-layer (Eq. shiftback).  Where the gridder
+//              took groups in parts, sum_parts first adds the parts' images.
 // Degridding (prediction, step 3), the adjoint chain:
 //   split_ifft one workgroup per (polarisation, group): copy the window times
 //              (-1)^(a+b) into LDS (splitter), inverse FFT, store the group image.

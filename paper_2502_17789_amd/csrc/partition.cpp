@@ -579,10 +579,12 @@ std::vector<aidg_subgrid> split_large(const std::vector<aidg_subgrid>& t, int ma
 void kaiser_bessel_axis(int n, double beta, std::vector<double>* t) {
   t->resize(n);
   const double i0b = std::cyl_bessel_i(0.0, beta);
-  for (int x = 0; x < n; ++x) {
-    const double f = double(x - n / 2) / n;
+  const int c = n / 2;
+  for (int x = 0; x <= c && x < n; ++x) {  // even about c
+    const double f = double(x - c) / n;
     (*t)[x] = std::cyl_bessel_i(0.0, beta * std::sqrt(std::max(0.0, 1.0 - 4.0 * f * f))) / i0b;
   }
+  for (int x = c + 1; x < n; ++x) (*t)[x] = 2 * c >= x ? (*t)[2 * c - x] : (*t)[0];
 }
 
 bool image_radices(int N, int elem_bytes, ImageRadices* out) {
@@ -650,13 +652,16 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
     out->axis_n1[x] = n1(l2[x]);
     out->axis_peak = std::max(out->axis_peak, std::fabs(out->axis_n1[x]));
   }
-  // (c is symmetric, and so is the taper: x >= y covers the peaks)
+  // c is symmetric in x and y and about the centre, and so is the taper: y <= x <= L / 2
+  // covers every value
   out->cross.resize((size_t)L * L);
   int at = 0;  // row of the largest taper-weighted |c|
-  for (int y = 0; y < L; ++y)
-    for (int x = y; x < L; ++x) {
+  for (int y = 0; y <= L / 2; ++y)
+    for (int x = y; x <= L / 2; ++x) {
       const double c = n1(l2[x] + l2[y]) - out->axis_n1[x] - out->axis_n1[y], m = std::fabs(c);
-      out->cross[(size_t)y * L + x] = out->cross[(size_t)x * L + y] = c;
+      for (int p : {x, L - x})
+        for (int q : {y, L - y})
+          if (p < L && q < L) out->cross[(size_t)q * L + p] = out->cross[(size_t)p * L + q] = c;
       out->cross_peak = std::max(out->cross_peak, m);
       double t = std::fabs(taper[(size_t)y * L + x]);
       for (int j = 1; j <= kMaxWOrder + 1; ++j) {
@@ -671,8 +676,8 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
   const double d = std::sqrt(std::max(0.0, -out->cross[(size_t)at * L + at]));
   out->b.resize(L);
   for (int x = 0; x < L; ++x) out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
-  for (int y = 0; y < L; ++y)
-    for (int x = y; x < L; ++x) {
+  for (int y = 0; y <= L / 2; ++y)
+    for (int x = y; x <= L / 2; ++x) {
       const size_t i = (size_t)y * L + x;
       out->residual = std::max(out->residual, std::fabs(taper[i] * (out->cross[i] + out->b[x] * out->b[y])));
     }

@@ -23,7 +23,12 @@
 // and take hi hi alone.
 //
 // What bounds it: the matrix cores at 3 (hi, lo) + 1 (first-order w term) products, and
-// beside them the VALU that forms the split operands.
+// beside them the VALU that forms the split operands: with 256 registers per lane two waves
+// share a SIMD and overlap little.  128 stations x 60 times x 96 channels, L = 96 (46.8M
+// visibilities): gridder 58.4 ms and degridder 66.2 (128.8 and 161.3 in the paired
+// recurrence); the products alone need 27 ms at the clock they run at, the matrix cores are
+// busy 42 % of the time and the VALU 43.  64 stations x 30 x 48, L = 64: 2.14 and 2.51 ms
+// (5.1 and 5.1); 48 x 12 x 3 of every 32nd channel, L = 96, degridder 0.236 (0.69).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -175,7 +180,13 @@ struct GridLds {
   float4 sum[kLdsPixels<L>][2][kThreads];
 };
 
-// One workgroup per (32 rows, group).  Each wave owns 8 rows x 4 polarisations (the 32
+// Waves per SIMD that the registers are allocated for.  At L = 32 a lane has one column tile
+// and three workgroups fit a compute unit: 72 stations x 16 times x 96 channels, folded: 1.07 ms
+// against 1.25 with two; four spill (1.25 ms), and so do three at L = 64.
+template <int L>
+constexpr int kGridWaves = L == 32 ? 3 : 2;
+
+// One workgroup per (32 rows, group or part of one).  Each wave owns 8 rows x 4 polarisations (the 32
 // rows of the matrix tiles) by L columns, real and imaginary parts in separate tiles, so
 // that a lane ends with all four polarisations of its L/8 pixels: the Jones epilogue is
 // lane-local and the group's sum stays in registers (a subgrid's image does not go through
@@ -183,11 +194,6 @@ struct GridLds {
 // alpha_k(x), formed once per workgroup and read from LDS in the operand's lane order.
 // The next block's visibilities and uvw are loaded (into registers) before the products of
 // the current one, across subgrids as well.
-// Waves per SIMD that the registers are allocated for.  At L = 32 a lane has one column tile
-// and three workgroups fit a compute unit: 72 stations x 16 times x 96 channels, folded: 1.07 ms
-// against 1.25 with two; four spill (1.25 ms), and so do three at L = 64.
-template <int L>
-constexpr int kGridWaves = L == 32 ? 3 : 2;
 template <int L>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_matrix(const Group g) {
