@@ -93,7 +93,8 @@ typedef struct {
   int32_t reseed_channels; /* R: each row's channels form runs of at most R (rounded down to
                               even; R = 1: every channel alone) whose phasors are seeded
                               from FP64 at the run's centre and stepped outward in FP32;
-                              0 = 32 */
+                              0 = 32.  FP32 plans with R >= 32 and short w ranges per subgrid
+                              form every phasor from FP64 and the sums on the matrix cores */
   int32_t strict_range;    /* 0: unplaceable visibilities are excluded (grid ignores them,
                               degrid writes 0); 1: plan creation fails with AIDG_E_RANGE */
   int32_t max_subgrid_vis; /* cap on visibilities per subgrid, 0 = 1024, at most 2048
@@ -136,9 +137,10 @@ typedef struct {
                               <grid(V), G> = <V, degrid(G)> / 2.  0: four planes (default) */
   int32_t degrid_form;     /* degridder design per subgrid (Sec. 3.2, Degridder: a kernel
                               design chosen by subgrid occupancy); the forms agree to
-                              rounding.  AIDG_DEGRID_AUTO (0): per subgrid, the form of
-                              least modelled cost (the direct form for rows of a few
-                              channels, the recurrence for longer ones).
+                              rounding.  AIDG_DEGRID_AUTO (0): the matrix cores (see
+                              reseed_channels) unless the plan's subgrids are sparse; else
+                              per subgrid, the form of least modelled cost (the direct form
+                              for rows of a few channels, the recurrence for longer ones).
                               AIDG_DEGRID_RECURRENCE (1): lanes own subgrid pixels, the
                               phasors step outward from the centre of each run of
                               reseed_channels (FP64-seeded there) and each pair of

@@ -714,7 +714,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     kaiser_bessel_taper(L, g.beta, &T);
     WSeries series;
     if (f32) w_series(L, g.fov, T, &series);
-    bool matrix = f32;
+    bool matrix = f32 && g.R >= kReseedDefault;  // a shorter run asks for the seeds' precision
     double cost = 0.0;  // of the degridder's other forms
     std::vector<SubgridDev> dev(plan->table.size());
     for (size_t i = 0; i < plan->table.size(); ++i) {
