@@ -27,7 +27,7 @@
 // share a SIMD and overlap little.  128 stations x 60 times x 96 channels, L = 96 (46.8M
 // visibilities): gridder 58.4 ms and degridder 66.2 (128.8 and 161.3 in the paired
 // recurrence); the products alone need 27 ms at the clock they run at, the matrix cores are
-// busy 42 % of the time and the VALU 43.  64 stations x 30 x 48, L = 64: 2.14 and 2.51 ms
+// busy 46 and 38 % of the time.  64 stations x 30 x 48, L = 64: 2.14 and 2.51 ms
 // (5.1 and 5.1); 48 x 12 x 3 of every 32nd channel, L = 96, degridder 0.236 (0.69).
 #include <hip/hip_runtime.h>
 

@@ -68,10 +68,13 @@ def test_block_edges(aidg, orc, L, n_t, n_c):
     V = synth.random_vis((wl.n_baselines, n_t, n_c), rng)
     table = both_ways(aidg, orc, wl, V, rng, f"L {L}, {n_t} x {n_c}", max_subgrid_vis=2048)
     assert (table["nt"] * table["nc"]).max() == n_t * n_c
-    # the automatic choice against the recurrence and the direct form
     with plan_for(aidg, wl, table=table, max_subgrid_vis=2048) as p:
         G = dev(synth.random_grid(p.n_wlayers, wl.grid_size, rng))
-        auto = host(p.degrid(G))
+        auto, image = host(p.degrid(G)), host(p.grid(dev(V)))
+    # the automatic choice against plans that ask for the general kernels
+    with plan_for(aidg, wl, table=table, max_subgrid_vis=2048, reseed_channels=8) as p:
+        check_grid(image, host(p.grid(dev(V))), 1e-5, "R = 8 grid")
+        check_vis(auto, host(p.degrid(G)), 1e-5, "R = 8 degrid")
     for form in (aidg.DEGRID_RECURRENCE, aidg.DEGRID_DIRECT):
         with plan_for(aidg, wl, table=table, max_subgrid_vis=2048, degrid_form=form) as p:
             check_vis(auto, host(p.degrid(G)), 1e-5, f"form {form}")
