@@ -58,6 +58,11 @@ template <typename V>
 __device__ __forceinline__ void gstore(void* base, unsigned off, V v) {
   *(AIDG_GLOBAL V*)((AIDG_GLOBAL char*)base + off) = v;
 }
+// Byte offset of visibility (row, c) of a sub-table, whose rows are nc_total apart.  A
+// sub-table of 2048 rows reaches 2^32 bytes from 65536 channels on, so it is 64 bits wide.
+__device__ __forceinline__ int64_t vis_offset(int row, int c, int nc_total) {
+  return ((int64_t)row * nc_total + c) * 32;
+}
 
 // (x, y) rounded to an FP16 pair (to nearest), and what it leaves of either (exact).
 __device__ __forceinline__ unsigned cvt_pair(float x, float y) {

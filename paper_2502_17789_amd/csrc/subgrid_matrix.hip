@@ -241,13 +241,12 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
       next_v = {0, 0, 0, 0};
       if (k < nv) {
         const int row = (int)(((float)k + 0.5f) * inv_nc), c = k - row * s.nc;
-        const char* src = static_cast<const char*>(gs.in) + s.vis0 * 32;
-        const unsigned off = ((unsigned)row * (unsigned)a.nc_total + (unsigned)c) * 32u;
+        const char* src = static_cast<const char*>(gs.in) + s.vis0 * 32 + vis_offset(row, c, a.nc_total);
         if (s.fold) {  // a folded sub-table is read as V^H
-          const vec4 h0 = gload<vec4>(src, off), h1 = gload<vec4>(src, off + 16);
+          const vec4 h0 = gload<vec4>(src, 0), h1 = gload<vec4>(src, 16);
           next_v = (tid & 1) ? vec4{h0.z, -h0.w, h1.z, -h1.w} : vec4{h0.x, -h0.y, h1.x, -h1.y};
         } else {
-          next_v = gload<vec4>(src, off + 16 * (tid & 1));
+          next_v = gload<vec4>(src, 16 * (tid & 1));
         }
       }
     } else if (tid < 3 * kBlk) {
@@ -733,9 +732,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
           if (e & 1) o = -o;
           e = (pol == 1 ? 4 : pol == 2 ? 2 : 2 * pol) + (e & 1);
         }
-        const unsigned off = ((unsigned)row * (unsigned)a.nc_total + (unsigned)ch) * 32u + 4u * e;
-        if (y0) o += gload<float>(vis, off);
-        gstore(vis, off, o);
+        char* dst = vis + vis_offset(row, ch, a.nc_total);
+        if (y0) o += gload<float>(dst, 4 * e);
+        gstore(dst, 4 * e, o);
       }
     }
   }
