@@ -61,11 +61,11 @@ struct Geometry {
 
 // Tables of the matrix kernels.  The w-term n1(l, m) splits into n1(l, 0) + n1(0, m) + c(l, m)
 // and c = -b(l) b(m) to the given residual; peak[j] is the largest taper-weighted |c|^j,
-// axis_peak and cross_peak the largest |n1(l, 0)| and |c|.
+// axis_peak, cross_peak and b_peak the largest |n1(l, 0)|, |c| and |b|.
 constexpr int kMaxWOrder = 3;
 struct WSeries {
   std::vector<double> axis_n1, b, cross;  // [L], [L], [L][L]
-  double peak[kMaxWOrder + 2] = {0}, residual = 0, axis_peak = 0, cross_peak = 0;
+  double peak[kMaxWOrder + 2] = {0}, residual = 0, axis_peak = 0, cross_peak = 0, b_peak = 0;
 };
 void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out);
 // Terms of the series in (w - wmid) c that a subgrid with |w - wmid| <= dw needs, or -1
@@ -111,10 +111,12 @@ struct KernelArgs {
   const void* taper;        // device [L][L] taper times (-1)^(x+y)
   const void* twiddle;      // device [L] exp(-2 pi i k / L)
   // matrix kernels (FP32 plans): n1(l, 0) along the lattice axis; the factor b of the
-  // cross term, 64 b as an FP16 pair; taper (as above) and cross term per pixel
+  // cross term over its largest value, as an FP16 pair; taper (as above) and cross term per
+  // pixel; 2 pi times the square of that largest value
   const double* axis_n1;    // device [L]
   const uint32_t* axis_b;   // device [L]
   const float2* taper_cross;  // device [L][L]
+  double w_series;
   const int64_t* grp_begin; // device [n_groups + 1]: first subgrid of each (layer, centre) group
   const int64_t* part_begin;  // device [n_parts + 1]: the same of each part of a group
   int nt_total, nc_total, N;

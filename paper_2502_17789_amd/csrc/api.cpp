@@ -88,6 +88,7 @@ struct aidg_plan {
   std::vector<int64_t> part_begin, cost_prefix;
   std::vector<int32_t> sg_part;
   int64_t max_group_cost = 0;
+  double b_peak = 0;  // matrix kernels: largest factor of the cross term
   bool split = false;  // the plan's own calls grid by parts (all of them fit the workspace)
   int64_t batch = 1;
   size_t elem = 8, aterm_bytes = 0, device_bytes = 0, scratch_bytes = 0;
@@ -148,6 +149,7 @@ struct aidg_plan {
     a.axis_n1 = reinterpret_cast<const double*>(d_tables + tl.axis_n1);
     a.axis_b = reinterpret_cast<const uint32_t*>(d_tables + tl.axis_b);
     a.taper_cross = reinterpret_cast<const float2*>(d_tables + tl.taper_cross);
+    a.w_series = 2.0 * M_PI * b_peak * b_peak;
     a.grp_begin = d_grp;
     a.part_begin = d_grp + (part_begin.size() == grp_begin.size() ? 0 : grp_begin.size());
     a.nt_total = nt;
@@ -714,6 +716,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     kaiser_bessel_taper(L, g.beta, &T);
     WSeries series;
     if (f32) w_series(L, g.fov, T, &series);
+    plan->b_peak = series.b_peak;
     bool matrix = f32 && g.R >= kReseedDefault;  // a shorter run asks for the seeds' precision
     double cost = 0.0;  // of the degridder's other forms
     std::vector<SubgridDev> dev(plan->table.size());
@@ -816,7 +819,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       float* tc = reinterpret_cast<float*>(tables.data() + tl.taper_cross);
       for (int x = 0; x < L; ++x) {
         n1[x] = series.axis_n1[x];
-        const _Float16 v = (_Float16)(64.0 * series.b[x]);
+        const _Float16 v = (_Float16)(series.b_peak > 0 ? series.b[x] / series.b_peak : 0.0);
         uint16_t u;
         std::memcpy(&u, &v, 2);
         b[x] = (uint32_t)u << 16 | u;

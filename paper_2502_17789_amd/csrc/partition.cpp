@@ -675,7 +675,10 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
   // c beyond l^2 m^2 terms that does not separate
   const double d = std::sqrt(std::max(0.0, -out->cross[(size_t)at * L + at]));
   out->b.resize(L);
-  for (int x = 0; x < L; ++x) out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
+  for (int x = 0; x < L; ++x) {
+    out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
+    out->b_peak = std::max(out->b_peak, std::fabs(out->b[x]));
+  }
   for (int y = 0; y <= L / 2; ++y)
     for (int x = y; x <= L / 2; ++x) {
       const size_t i = (size_t)y * L + x;
@@ -693,7 +696,10 @@ int w_series_order(const WSeries& ws, double wmid, double dw) {
   if (!(far * ws.axis_peak <= 0x1p17) || !(far * ws.cross_peak <= 128.0) ||
       !(2.0 * M_PI * std::fabs(wmid) * ws.peak[1] <= 0.5))
     return -1;
+  // The kernels' FP16 series operands are the data, at most 2^10.5, times powers of
+  // 2 pi d b b and of b over its peak: below 2^14 at up to three terms.
   const double p = 2.0 * M_PI * dw;
+  if (!(p * ws.b_peak * ws.b_peak <= 4.0)) return -1;
   if (!(p * ws.peak[1] <= 1e-3) || !(p * ws.residual <= 1e-7)) return -1;
   double term = 1.0;
   for (int j = 0; j <= kMaxWOrder; ++j) {

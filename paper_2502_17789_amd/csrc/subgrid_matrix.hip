@@ -58,7 +58,7 @@ constexpr int kAhead = 2;
 constexpr int kRows = 32;
 
 // A block's visibilities: phase coefficients in turns per lattice step (u, v) and
-// wavelengths (w), and 2 pi d_k 2^-12 as an FP16 pair.
+// wavelengths (w), and d_k times KernelArgs' w_series as an FP16 pair.
 template <int B>
 struct VisBlock {
   double2 ku_w[B];
@@ -86,7 +86,7 @@ __device__ __forceinline__ void store_phase(const KernelArgs& a, const SubgridDe
     ku = (p.u * p.fc - (s.U0 - a.N / 2) * a.du) * a.lstep;
     kv = (p.v * p.fc - (s.V0 - a.N / 2) * a.du) * a.lstep;
     kw = p.w * p.fc - s.w0;
-    dw = pair_of((float)((kw - (double)s.wmid) * (6.283185307179586 / 4096.0)));
+    dw = pair_of((float)((kw - (double)s.wmid) * a.w_series));
   }
   vb->ku_w[k] = {ku, kw};
   vb->kv_w[k] = {kv, kw};
@@ -259,7 +259,8 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
   // Row operands of step ks: W_k = V_k beta_k(y) for the lane's four visibilities, rows
   // (W_re, -W_im) for the real tile and (W_im, W_re) for the imaginary one, each hi and lo;
   // g: 2 pi d_k b(y) of the w series, whose first term takes rows times -i g and columns
-  // times b(x) (the tables hold 64 b and d 2^-12 of its value).
+  // times b(x).  (b is held over its peak and d_k with the peak's square: the factors of a
+  // row stay below 4 and those of a column below 1, whatever the data are largest at.)
   struct Rows {
     Frag rh, rl, ih, il;
     unsigned g[4];
@@ -487,7 +488,7 @@ struct DegridLds {
   VisBlock<kDegBlk> vb;
   float2 part[4][kDegBlk * 4];
   double axis[L];
-  alignas(16) unsigned b[L];  // (-64 b, 64 b) pairs
+  alignas(16) unsigned b[L];  // (-b, b) pairs
 };
 
 // One workgroup per subgrid, 32 rows of the subgrid at a time.  Each wave corrects its

@@ -1,10 +1,12 @@
 """The matrix-core (de)gridder of FP32 plans where its fixed-size arithmetic could end: byte
-offsets of long, wide visibility tables.
+offsets of long, wide visibility tables, and FP16 operands of the w series under isolated
+off-axis sources.
 """
 import numpy as np
 import pytest
 
 import synth
+from gates import check_grid
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -17,6 +19,74 @@ def aidg():
         pytest.skip("no GPU")
     m.library()
     return m
+
+
+LIGHT = 299792458.0
+
+
+class Track:
+    """Baselines of 16 times and 8 channels that stay within a subgrid about the centre, with w
+    from -dw to dw wavelengths in one layer, and identity Jones terms."""
+
+    def __init__(self, aidg, L, fov, dw, n_bl=6, w_mid=0.0):
+        self.L, self.N, self.fov, K, n_t = L, 4 * L, fov, L // 4, 16
+        self.aidg, self.n_st = aidg, n_bl + 1
+        rng = np.random.default_rng(7)
+        self.freqs = np.linspace(149.9e6, 150.1e6, 8)
+        lam = LIGHT / 150e6
+        uv = rng.uniform(-0.2, 0.2, (n_bl, 1, 2)) + rng.uniform(-0.1, 0.1, (n_bl, n_t, 2))
+        uv *= (L - K) / fov
+        w = w_mid + np.broadcast_to(np.linspace(-1, 1, n_t), (n_bl, n_t)) * dw / 1.001
+        self.uvw = np.concatenate([uv, w[..., None]], -1) * lam
+        self.bl = np.array([(i, i + 1) for i in range(n_bl)], np.int32)
+        self.A = torch.zeros((1, self.n_st, L, L, 4), dtype=torch.complex64, device="cuda")
+        self.A[..., 0] = self.A[..., 3] = 1
+        beta = np.pi * K / 4
+        f = (np.arange(L) - L // 2) / L
+        self.taper = np.i0(beta * np.sqrt(1 - 4 * f * f)) / np.i0(beta)
+        self.l = f * fov
+
+    def plan(self, precision=0, **kw):
+        g = self.aidg.Geometry(self.N, self.L, self.L // 4, self.fov / self.N, aterm_interval=16, w_step=-1.0,
+                               precision=precision, **kw)
+        A = self.A.to(torch.complex128) if precision else self.A
+        return self.aidg.Plan(g, self.n_st, self.bl, self.uvw, self.freqs, A)
+
+    def source(self, x, y):
+        """Grid of a source of unit XX and YY at subgrid pixel (x, y) as prediction forms it, its
+        visibilities by the measurement equation, and its taper."""
+        cell = (np.arange(self.N) - self.N // 2) / self.fov
+        T = self.taper[x] * self.taper[y]
+        l, m = self.l[x], self.l[y]
+        g = np.zeros((1, 4, self.N, self.N), np.complex64)
+        g[0, 0] = g[0, 3] = np.outer(np.exp(-2j * np.pi * cell * m), np.exp(-2j * np.pi * cell * l)) / (self.L ** 2 * T)
+        w = self.uvw[:, :, None, :] * (self.freqs / LIGHT)[:, None]
+        n1 = -(l * l + m * m) / (1 + np.sqrt(1 - l * l - m * m))
+        return torch.from_numpy(g).cuda(), np.exp(-2j * np.pi * (w[..., 0] * l + w[..., 1] * m + w[..., 2] * n1)), T
+
+
+# |w| ranges at which the series takes two and three terms; the last is a narrow field
+WIDE = [(32, 0.9, 0.085), (32, 0.9, 0.105), (64, 1.0, 0.2), (64, 1.0, 0.6), (96, 1.2, 0.25), (96, 1.2, 0.7),
+        (32, 0.1, 6.5e3), (96, 0.1, 6.3e4)]
+
+
+@pytest.mark.parametrize("L,fov,dw", WIDE)
+def test_series_operands_stay_in_range(aidg, L, fov, dw):
+    """A lone off-axis source is the largest value of its rows of the subgrid image: the taper does
+    not keep the series' operands small.  Predicted grids carry the rounding of FP32 values of
+    1 / T, which the degridder's taper leaves at some 1e-7 / T of the source."""
+    t = Track(aidg, L, fov, dw)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    with t.plan() as p, t.plan(1) as q:
+        for x, y in ((0.3, 0.3), (0.41, 0.41), (0.45, 0.2), (0.2, 0.45)):
+            x, y = L // 2 + round(x * L), L // 2 - round(y * L)
+            G, ref, T = t.source(x, y)
+            V = p.degrid(G).cpu().numpy()
+            assert np.isfinite(V).all(), (x, y)
+            for pol in (0, 3):
+                assert np.abs(V[..., pol] - ref).max() <= 1e-5 + 1e-6 / T, (x, y)
+        v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        check_grid(p.grid(v).cpu().numpy(), q.grid(v.to(torch.complex128)).cpu().numpy(), 1e-5, f"L {L}, {fov} rad")
 
 
 def test_rows_beyond_4_gib(aidg):
