@@ -41,7 +41,7 @@ struct alignas(16) SubgridDev {
   double w0;                   // layer w, wavelengths
   int32_t fold;                // 1: visibilities enter and leave conjugate-transposed
   int32_t kind;                // degridder form: kDegridRecur, kDegridDirect or kDegridPerVis
-  int32_t order;               // matrix kernels: terms of the w series (0 .. kMaxWOrder)
+  int32_t order;               // matrix kernels: terms of the w series (kWTerms, kWSplit)
   float wmid;                  // matrix kernels: middle of the w range, wavelengths from w0
 };
 // Degridder forms, chosen per subgrid by the plan (degrid_form).
@@ -59,17 +59,19 @@ struct Geometry {
   int64_t workspace;
 };
 
-// Tables of the matrix kernels.  The w-term n1(l, m) splits into n1(l, 0) + n1(0, m) + c(l, m)
-// and c = -b(l) b(m) to the given residual; peak[j] is the largest taper-weighted |c|^j,
-// axis_peak, cross_peak and b_peak the largest |n1(l, 0)|, |c| and |b|.
-constexpr int kMaxWOrder = 3;
+// Tables of the matrix kernels.  The w-term n1(l, m) splits into a(l) + a(m) + c(l, m), a(l)
+// n1(l, 0) but for what makes c smaller (axis_n1, cross), and c = -b(l) b(m) to the given
+// taper-weighted residual; peak[j] is the largest taper-weighted |c|^j,
+// axis_peak, cross_peak and b_peak the largest |a|, |c| and |b|.
+constexpr int kMaxWOrder = 2;
+constexpr int kWTerms = 3, kWSplit = 4;  // SubgridDev::order: number of terms; first term in split operands
 struct WSeries {
   std::vector<double> axis_n1, b, cross;  // [L], [L], [L][L]
   double peak[kMaxWOrder + 2] = {0}, residual = 0, axis_peak = 0, cross_peak = 0, b_peak = 0;
 };
 void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out);
-// Terms of the series in (w - wmid) c that a subgrid with |w - wmid| <= dw needs, or -1
-// where the matrix kernels do not apply.
+// SubgridDev::order of a subgrid with |w - wmid| <= dw: the terms of the series in
+// (w - wmid) c that it needs, or -1 where the matrix kernels do not apply.
 int w_series_order(const WSeries& ws, double wmid, double dw);
 
 // Host-side partition (library's own algorithm); table entries are aidg_subgrid.
@@ -110,11 +112,11 @@ struct KernelArgs {
   const void* ainvh;        // device (A^-1)^H planes of the inverse A-term mode, else null
   const void* taper;        // device [L][L] taper times (-1)^(x+y)
   const void* twiddle;      // device [L] exp(-2 pi i k / L)
-  // matrix kernels (FP32 plans): n1(l, 0) along the lattice axis; the factor b of the
-  // cross term over its largest value, as an FP16 pair; taper (as above) and cross term per
-  // pixel; 2 pi times the square of that largest value
+  // matrix kernels (FP32 plans): a (WSeries) along the lattice axis; the factor b of the
+  // cross term over its largest value, rounded to FP16, then what that leaves, both as FP16
+  // pairs; taper (as above) and cross term per pixel; 2 pi times the square of b's largest
   const double* axis_n1;    // device [L]
-  const uint32_t* axis_b;   // device [L]
+  const uint32_t* axis_b;   // device [2][L]
   const float2* taper_cross;  // device [L][L]
   double w_series;
   const int64_t* grp_begin; // device [n_groups + 1]: first subgrid of each (layer, centre) group
@@ -134,6 +136,7 @@ struct KernelArgs {
 // with `split` grids by the parts of groups instead (slots pslot_begin.., scratch slot
 // pslot_begin + (p - p_first)), and the adder sums the images of a group's parts.
 constexpr int kMaxGroup = 16;
+enum MatrixForm { kMatrixNone = 0, kMatrixPlain = 1, kMatrixWide = 2 };  // Wide: a subgrid of the plan has kWSplit
 struct JobRef {
   const KernelArgs* args;   // device copy of the plan's parameters
   const void* in;           // visibilities (gridder) or grid (splitter)
@@ -150,7 +153,7 @@ struct JobRef {
 };
 struct Group {
   int32_t n;
-  int32_t matrix;           // 1: the matrix kernels take the launch's DFTs
+  int32_t matrix;           // MatrixForm: whether the matrix kernels take the launch's DFTs
   int64_t total_sg;         // per-subgrid slots in the launch
   int64_t total_grp;        // per-group slots in the launch
   int64_t total_part;       // per-part slots in the launch

@@ -65,7 +65,7 @@ struct TableLayout {
     twiddle = axis_n1 + matrix * 8 * L;
     taper = twiddle + elem * L;
     axis_b = taper + elem / 2 * n;
-    bytes = axis_b + matrix * 4 * L;
+    bytes = axis_b + matrix * 8 * L;
   }
 };
 
@@ -103,7 +103,7 @@ struct aidg_plan {
   KernelArgs* d_args = nullptr;  // device copy of args()
   // matrix kernels: all of the plan's subgrids qualify (degridding: and they are not so
   // sparse that the other forms take less time, and the geometry asks for none)
-  bool matrix_grid = false, matrix_degrid = false;
+  MatrixForm matrix_grid = kMatrixNone, matrix_degrid = kMatrixNone;
   // image level (invert / predict): Stockham radices of N, twiddles exp(-2 pi i k / N)
   // and the reciprocal of the taper's axis at image resolution (FP64); absent when N
   // is not supported
@@ -461,7 +461,7 @@ aidg_status execute_items(void* scratch, int64_t scratch_bytes, hipEvent_t last,
     if (done[i0]) continue;
     const int dir = items[i0].direction, L = items[i0].plan->g.L, prec = items[i0].plan->g.precision;
     auto matrix = [&](const aidg_plan* p) { return dir == AIDG_DIR_GRID ? p->matrix_grid : p->matrix_degrid; };
-    const bool mx = matrix(items[i0].plan);
+    const MatrixForm mx = matrix(items[i0].plan);
     const int64_t per_sg = (int64_t)4 * L * L * (prec == AIDG_FP32 ? 8 : 16);
     const int64_t cap = std::min<int64_t>(scratch_bytes / per_sg, 65535);
     // grid by parts where they fit one launch's images and the heaviest group of the items
@@ -718,6 +718,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     if (f32) w_series(L, g.fov, T, &series);
     plan->b_peak = series.b_peak;
     bool matrix = f32 && g.R >= kReseedDefault;  // a shorter run asks for the seeds' precision
+    bool wide = false;
     double cost = 0.0;  // of the degridder's other forms
     std::vector<SubgridDev> dev(plan->table.size());
     for (size_t i = 0; i < plan->table.size(); ++i) {
@@ -759,12 +760,13 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         const double dw = std::max(hi - d.wmid, d.wmid - lo);
         d.order = w_series_order(series, d.wmid, dw);
         matrix = d.order >= 0;
+        wide = wide || (matrix && (d.order & kWSplit));
       }
       cost += degrid_cost(d.kind, s.nt, s.nc);
       plan->n_pervis += d.kind == kDegridPerVis;
       plan->n_direct += d.kind == kDegridDirect;
     }
-    plan->matrix_grid = matrix;
+    plan->matrix_grid = !matrix ? kMatrixNone : wide ? kMatrixWide : kMatrixPlain;
     // The matrix degridder works in blocks of 32 visibilities and takes the same time for 1
     // as for 32: 13.6, 44 and 94 ns per subgrid at L = 32, 64, 96 with the chip full.  The
     // other forms, with one row per subgrid and c channels, take 9 to 11 ns for c = 1 to 10
@@ -772,8 +774,8 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     // 8 and 137 for 22 (L = 96); with 8 rows of one channel 17 ns at L = 32.  The lines are
     // where the two meet, in that model's cost.
     const double meet = L == 32 ? 13.5 : L == 64 ? 6.0 : 10.0;
-    plan->matrix_degrid =
-        matrix && g.degrid_form == AIDG_DEGRID_AUTO && cost >= meet * (double)plan->table.size();
+    if (matrix && g.degrid_form == AIDG_DEGRID_AUTO && cost >= meet * (double)plan->table.size())
+      plan->matrix_degrid = kMatrixPlain;  // its kernel chooses by subgrid
     // inverse A-term mode: distinct (A_p plane, A_q plane) pairs with their visibility
     // counts, for the normalisation map
     std::vector<int32_t> pairs;
@@ -819,10 +821,13 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       float* tc = reinterpret_cast<float*>(tables.data() + tl.taper_cross);
       for (int x = 0; x < L; ++x) {
         n1[x] = series.axis_n1[x];
-        const _Float16 v = (_Float16)(series.b_peak > 0 ? series.b[x] / series.b_peak : 0.0);
-        uint16_t u;
-        std::memcpy(&u, &v, 2);
-        b[x] = (uint32_t)u << 16 | u;
+        const double v = series.b_peak > 0 ? series.b[x] / series.b_peak : 0.0;
+        const _Float16 part[2] = {(_Float16)v, (_Float16)(v - (double)(_Float16)v)};
+        for (int i = 0; i < 2; ++i) {
+          uint16_t u;
+          std::memcpy(&u, &part[i], 2);
+          b[i * L + x] = (uint32_t)u << 16 | u;
+        }
       }
       for (int i = 0; i < L * L; ++i) {
         // A value passes through three phasors of the transcendental unit (the two axes and the

@@ -37,6 +37,28 @@ __device__ __forceinline__ unsigned swap_mul(unsigned p, unsigned b) {
   asm("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0] op_sel_hi:[0,1]" : "=v"(r) : "v"(p), "v"(b));
   return r;
 }
+// The same, plus c, and minus c, fused.
+__device__ __forceinline__ unsigned swap_fma(unsigned p, unsigned b, unsigned c) {
+  unsigned r;
+  asm("v_pk_fma_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[0,1,1]" : "=v"(r) : "v"(p), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ unsigned swap_fma_sub(unsigned p, unsigned b, unsigned c) {
+  unsigned r;
+  asm("v_pk_fma_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[0,1,1] neg_lo:[0,0,1] neg_hi:[0,0,1]"
+      : "=v"(r)
+      : "v"(p), "v"(b), "v"(c));
+  return r;
+}
+// (a + a_lo) (b + b_lo) as hi + lo: what rounding a b leaves is exact in FP16, and the two
+// cross products are below 2^-11 of it.
+__device__ __forceinline__ unsigned mul_rest(unsigned a, unsigned a_lo, unsigned b, unsigned b_lo, unsigned hi) {
+  const half2v x = __builtin_bit_cast(half2v, a), y = __builtin_bit_cast(half2v, b);
+  half2v r = __builtin_elementwise_fma(x, y, -__builtin_bit_cast(half2v, hi));
+  r = __builtin_elementwise_fma(x, __builtin_bit_cast(half2v, b_lo), r);
+  r = __builtin_elementwise_fma(__builtin_bit_cast(half2v, a_lo), y, r);
+  return __builtin_bit_cast(unsigned, r);
+}
 __device__ __forceinline__ unsigned rot90(unsigned p) {
   unsigned r;
   asm("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0] op_sel_hi:[0,1]" : "=v"(r) : "v"(p), "s"(0x3C00BC00u));  // (-1, 1)
@@ -93,6 +115,7 @@ __device__ __forceinline__ unsigned pair_of(float x) {
   const half2v h = {(_Float16)x, (_Float16)x};
   return __builtin_bit_cast(unsigned, h);
 }
+__device__ __forceinline__ float pair_high(unsigned p) { return (float)__builtin_bit_cast(half2v, p).y; }
 
 // Power of two that brings a largest component m to [2^9, 2^10), and its reciprocal (so
 // that the low halves stay normal FP16 numbers down to 2^-23 of m).  Infinities and NaNs

@@ -650,63 +650,91 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
     const double l = (x - L / 2) * (fov / L);
     l2[x] = l * l;
     out->axis_n1[x] = n1(l2[x]);
-    out->axis_peak = std::max(out->axis_peak, std::fabs(out->axis_n1[x]));
   }
   // c is symmetric in x and y and about the centre, and so is the taper: y <= x <= L / 2
   // covers every value
-  out->cross.resize((size_t)L * L);
+  std::vector<double> c((size_t)L * L);
   int at = 0;  // row of the largest taper-weighted |c|
-  for (int y = 0; y <= L / 2; ++y)
-    for (int x = y; x <= L / 2; ++x) {
-      const double c = n1(l2[x] + l2[y]) - out->axis_n1[x] - out->axis_n1[y], m = std::fabs(c);
-      for (int p : {x, L - x})
-        for (int q : {y, L - y})
-          if (p < L && q < L) out->cross[(size_t)q * L + p] = out->cross[(size_t)p * L + q] = c;
-      out->cross_peak = std::max(out->cross_peak, m);
-      double t = std::fabs(taper[(size_t)y * L + x]);
-      for (int j = 1; j <= kMaxWOrder + 1; ++j) {
-        t *= m;
-        if (t <= out->peak[j]) continue;
-        out->peak[j] = t;
-        if (j == 1) at = y;
-      }
-    }
-  // the cross of the peak's row and column: exact on them, and elsewhere off by the part of
-  // c beyond l^2 m^2 terms that does not separate
-  const double d = std::sqrt(std::max(0.0, -out->cross[(size_t)at * L + at]));
-  out->b.resize(L);
-  for (int x = 0; x < L; ++x) {
-    out->b[x] = d > 0 ? -out->cross[(size_t)at * L + x] / d : 0.0;
-    out->b_peak = std::max(out->b_peak, std::fabs(out->b[x]));
-  }
+  double peak = 0;
   for (int y = 0; y <= L / 2; ++y)
     for (int x = y; x <= L / 2; ++x) {
       const size_t i = (size_t)y * L + x;
-      out->residual = std::max(out->residual, std::fabs(taper[i] * (out->cross[i] + out->b[x] * out->b[y])));
+      c[i] = n1(l2[x] + l2[y]) - out->axis_n1[x] - out->axis_n1[y];
+      if (std::fabs(taper[i] * c[i]) > peak) {
+        peak = std::fabs(taper[i] * c[i]);
+        at = y;
+      }
     }
+  // c = -b b with the cross of the peak's row and column: exact on them, and elsewhere off by
+  // the part of c beyond l^2 m^2 terms that does not separate
+  auto row = [&](int x) { return at <= x ? c[(size_t)at * L + x] : c[(size_t)x * L + at]; };
+  const double d = std::sqrt(std::max(0.0, -row(at)));
+  out->b.resize(L);
+  for (int x = 0; x < L; ++x) out->b[x] = d > 0 ? -row(std::min(x, L - x)) / d : 0.0;
+  for (int y = 0; y <= L / 2; ++y)
+    for (int x = y; x <= L / 2; ++x) {
+      const size_t i = (size_t)y * L + x;
+      out->residual = std::max(out->residual, std::fabs(taper[i] * (c[i] + out->b[x] * out->b[y])));
+    }
+  // b less a constant s: -(b(l) - s)(b(m) - s) differs from c by functions of l and of m
+  // alone, which join the axis terms.  The s of the least taper-weighted peak, where the
+  // centre's s^2 meets the largest beyond it, brings it to 1 / 1.7 to 1 / 1.8.
+  auto weighted = [&](double s) {
+    double m = 0;
+    for (int y = 0; y <= L / 2; ++y)
+      for (int x = y; x <= L / 2; ++x)
+        m = std::max(m, std::fabs(taper[(size_t)y * L + x] * (out->b[x] - s) * (out->b[y] - s)));
+    return m;
+  };
+  double lo = 0, hi = d;
+  for (int i = 0; i < 12; ++i) {  // the centre's grows with s, the other falls
+    const double s = 0.5 * (lo + hi);
+    (weighted(s) > s * s * 1.000001 ? lo : hi) = s;
+  }
+  out->cross.resize((size_t)L * L);
+  for (int y = 0; y <= L / 2; ++y)
+    for (int x = y; x <= L / 2; ++x) {
+      const double v = c[(size_t)y * L + x] + lo * (out->b[x] + out->b[y] - lo), m = std::fabs(v);
+      for (int p : {x, L - x})
+        for (int q : {y, L - y})
+          if (p < L && q < L) out->cross[(size_t)q * L + p] = out->cross[(size_t)p * L + q] = v;
+      out->cross_peak = std::max(out->cross_peak, m);
+      double w = std::fabs(taper[(size_t)y * L + x]);
+      for (int j = 1; j <= kMaxWOrder + 1; ++j) out->peak[j] = std::max(out->peak[j], w *= m);
+    }
+  for (int x = 0; x < L; ++x) {
+    out->axis_n1[x] += lo * (0.5 * lo - out->b[x]);
+    out->b[x] -= lo;
+    out->axis_peak = std::max(out->axis_peak, std::fabs(out->axis_n1[x]));
+    out->b_peak = std::max(out->b_peak, std::fabs(out->b[x]));
+  }
 }
 
-// The series is cut where its first missing term is below 3e-8 of the taper's peak, a tenth
-// of the FP32 path's normwise error; the first-order term, taken in FP16, may be 1e-3 (its
-// rounding is then below 5e-8 rms), and the part of c that is not b b below 1e-7.
+// What the series may leave is weighed by the taper, as the rounding of the subgrid's FP32
+// transform is, some 2e-8 of its largest value: a source that prediction has divided by its
+// taper meets both over that taper.
+// - The series is cut where its first missing term is below 1e-8, and c = -b b is exact to 1e-8.
+// - A term of FP16 operands alone is off by 4e-4 of it (eight roundings to 2^-11): a first term
+//   up to 1.5e-5 and a second up to 1e-5.  Above, the first takes split operands (4 matrix
+//   products more than 8), off by 2e-6 of it.  With FP16 alone, lone sources at 0.1 to 0.4 of the
+//   field and first terms of 3e-5, 1e-4, 3e-4 and 1e-3 came out with up to 3, 9, 33 and 72 times
+//   the general kernels' error.
+// - E(wmid c) is formed from an FP32 phase, off by 5e-8 of it: at most 0.05 radian.
 int w_series_order(const WSeries& ws, double wmid, double dw) {
-  // Phases (turns) stay in the range of the kernels' fixed-point reduction, and E(wmid c),
-  // formed from an FP32 phase, is exact to 2^-24 of its tapered largest phase.
+  // phases (turns) stay in the range of the kernels' fixed-point reduction
   const double far = std::fabs(wmid) + dw;
   if (!(far * ws.axis_peak <= 0x1p17) || !(far * ws.cross_peak <= 128.0) ||
-      !(2.0 * M_PI * std::fabs(wmid) * ws.peak[1] <= 0.5))
+      !(2.0 * M_PI * std::fabs(wmid) * ws.peak[1] <= 0.05))
     return -1;
   // The kernels' FP16 series operands are the data, at most 2^10.5, times powers of
-  // 2 pi d b b and of b over its peak: below 2^14 at up to three terms.
+  // 2 pi d b b and of b over its peak: below 2^14.
   const double p = 2.0 * M_PI * dw;
-  if (!(p * ws.b_peak * ws.b_peak <= 4.0)) return -1;
-  if (!(p * ws.peak[1] <= 1e-3) || !(p * ws.residual <= 1e-7)) return -1;
-  double term = 1.0;
-  for (int j = 0; j <= kMaxWOrder; ++j) {
-    term *= p / (j + 1);
-    if (term * ws.peak[j + 1] <= 3e-8) return j;
-  }
-  return -1;
+  if (!(p * ws.b_peak * ws.b_peak <= 4.0) || !(p * ws.residual <= 1e-8)) return -1;
+  const double term[] = {p * ws.peak[1], p * p / 2 * ws.peak[2], p * p * p / 6 * ws.peak[3]};
+  if (term[0] <= 1e-8) return 0;
+  const int wide = term[0] > 1.5e-5 || term[1] > 1e-8 ? kWSplit : 0;
+  if (term[1] <= 1e-8) return 1 | wide;
+  return term[1] <= 1e-5 && term[2] <= 1e-8 ? 2 | wide : -1;
 }
 
 }  // namespace aidg

@@ -1,6 +1,6 @@
 // FP32 (de)gridder on the matrix cores.
 //
-// With n1(l, m) = a(l) + a(m) + c(l, m), a(l) = n1(l, 0), the phasor of visibility k at
+// With n1(l, m) = a(l) + a(m) + c(l, m), a(l) about n1(l, 0), the phasor of visibility k at
 // subgrid pixel (x, y) factors into
 //   alpha_k(x) = E(u_k l_x + w_k a(l_x)),   beta_k(y) = E(v_k m_y + w_k a(m_y)),
 //   E(w_s c(x, y)) E(d_k c(x, y)),          w_k = w_s + d_k,   E(t) = exp(2 pi i t),
@@ -18,9 +18,9 @@
 // nearest: 2^-24 of the largest value, the data scaled to that by a power of two per
 // subgrid) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
 // forms the products exactly and adds in FP32.  Every phase is formed and reduced to
-// [-1/2, 1/2] turn in FP64; there is no recurrence.  The series' terms j >= 1 are small (the
-// plan takes this path only where their largest value, times the taper, is below 1e-3)
-// and take hi hi alone.
+// [-1/2, 1/2] turn in FP64; there is no recurrence.  The series' first term takes hi hi
+// alone where its largest value, times the taper, is below 1.5e-5 (w_series_order), and
+// otherwise split operands as well; a second term is smaller and takes hi hi.
 //
 // What bounds it: the matrix cores at 3 (hi, lo) + 1 (first-order w term) products, and
 // beside them the VALU that forms the split operands: with 256 registers per lane two waves
@@ -58,12 +58,13 @@ constexpr int kAhead = 2;
 constexpr int kRows = 32;
 
 // A block's visibilities: phase coefficients in turns per lattice step (u, v) and
-// wavelengths (w), and d_k times KernelArgs' w_series as an FP16 pair.
+// wavelengths (w), and d_k times KernelArgs' w_series, rounded to FP16 and what that leaves,
+// as FP16 pairs.
 template <int B>
 struct VisBlock {
   double2 ku_w[B];
   double2 kv_w[B];
-  unsigned dw[B];
+  unsigned dw[2][B];
 };
 
 // A visibility's uvw row and frequency, loaded ahead of the block that uses them.
@@ -81,16 +82,19 @@ template <int B>
 __device__ __forceinline__ void store_phase(const KernelArgs& a, const SubgridDev& s, const VisPhase& p, bool valid, int k,
                                             VisBlock<B>* vb) {
   double ku = 0, kv = 0, kw = 0;
-  unsigned dw = 0;
+  unsigned dw = 0, dl = 0;
   if (valid) {
     ku = (p.u * p.fc - (s.U0 - a.N / 2) * a.du) * a.lstep;
     kv = (p.v * p.fc - (s.V0 - a.N / 2) * a.du) * a.lstep;
     kw = p.w * p.fc - s.w0;
-    dw = pair_of((float)((kw - (double)s.wmid) * a.w_series));
+    const float d = (float)((kw - (double)s.wmid) * a.w_series);
+    dw = pair_of(d);
+    dl = pair_of(d - (float)(_Float16)d);
   }
   vb->ku_w[k] = {ku, kw};
   vb->kv_w[k] = {kv, kw};
-  vb->dw[k] = dw;
+  vb->dw[0][k] = dw;
+  vb->dw[1][k] = dl;
 }
 
 // scale beta_k(y) of the workgroup's 32 rows from y0 for the block's first n visibilities,
@@ -175,7 +179,7 @@ struct GridLds {
   float2 vis[4 * (kBlk + 2)];
   VisBlock<kBlk> vb;
   double axis[L];
-  unsigned b[L];
+  unsigned b_rest[L];
   float peak;
   float4 sum[kLdsPixels<L>][2][kThreads];
 };
@@ -194,7 +198,7 @@ constexpr int kGridWaves = L == 32 ? 3 : 2;
 // alpha_k(x), formed once per workgroup and read from LDS in the operand's lane order.
 // The next block's visibilities and uvw are loaded (into registers) before the products of
 // the current one, across subgrids as well.
-template <int L>
+template <int L, bool WIDE>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_matrix(const Group g) {
   constexpr int XT = L / 32, NP = 4, NPIX = XT * NP, P0 = kLdsPixels<L>;  // column tiles; pixels per lane
@@ -212,7 +216,7 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
   const int y0 = chunk * kRows;
   for (int i = tid; i < L; i += kThreads) {
     sh.axis[i] = a.axis_n1[i];
-    sh.b[i] = a.axis_b[i];
+    sh.b_rest[i] = a.axis_b[L + i];
   }
   // operand row of this lane: polarisation q of row yl of the wave's eight
   const int q = col & 3, yl = wave * 8 + (col >> 2);
@@ -284,54 +288,78 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
       split(fmaf(-v.y, b.y, v.x * b.x), fmaf(-v.y, b.x, -(v.x * b.y)), r.rh.w[i], r.rl.w[i]);
       r.ih.w[i] = rot90(r.rh.w[i]);
       r.il.w[i] = rot90(r.rl.w[i]);
-      r.g[i] = pk_mul(sh.vb.dw[k + i], by);
+      r.g[i] = pk_mul(sh.vb.dw[0][k + i], by);
     }
     return r;
   };
-  // Products of step ks with the series' first term; order > 1 (wide fields): further terms j,
-  // rows times (-i 2 pi d_k b(y))^j / j!, columns times b(x)^j.
-  auto products = [&](int ks, int order) {
+  // Products of step ks with the series.  WIDE: the first term in split operands, and a second
+  // one where the subgrid needs it, rows times (-i 2 pi d_k b(y))^2 / 2 and columns times
+  // b(x)^2; one column tile at a time, which takes no more registers than the others.
+  auto products = [&](int ks, int terms) {
     Frag bh[XT], bl[XT];
+    if constexpr (!WIDE) {
 #pragma unroll
-    for (int t = 0; t < XT; ++t) {
-      bh[t] = sh.alpha[ks][t][0][lane];
-      bl[t] = sh.alpha[ks][t][1][lane];
+      for (int t = 0; t < XT; ++t) {
+        bh[t] = sh.alpha[ks][t][0][lane];
+        bl[t] = sh.alpha[ks][t][1][lane];
+      }
     }
     const Rows r = rows(ks);
-    Frag nr, ni;
+    Frag nr, ni, mr, mi;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       nr.w[i] = pk_mul(r.ih.w[i], r.g[i]);
       ni.w[i] = pk_mul_neg(r.rh.w[i], r.g[i]);
     }
+    if constexpr (WIDE) {
+      const unsigned y_rest = sh.b_rest[y0 + yl];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned dw = sh.vb.dw[0][8 * ks + 4 * h + i], dl = sh.vb.dw[1][8 * ks + 4 * h + i];
+        mr.w[i] = mul_rest(r.ih.w[i], r.il.w[i], r.g[i], mul_rest(dw, dl, by, y_rest, r.g[i]), nr.w[i]);
+        mi.w[i] = rot90(mr.w[i]);  // (as ni is of nr)
+      }
+    }
 #pragma unroll
     for (int t = 0; t < XT; ++t) {
+      if constexpr (WIDE) {
+        __builtin_amdgcn_sched_barrier(0);
+        bh[t] = sh.alpha[ks][t][0][lane];
+        bl[t] = sh.alpha[ks][t][1][lane];
+      }
       re[t] = mfma(r.rh, bh[t], re[t]);
       im[t] = mfma(r.ih, bh[t], im[t]);
       re[t] = mfma(r.rh, bl[t], re[t]);
       im[t] = mfma(r.ih, bl[t], im[t]);
       re[t] = mfma(r.rl, bh[t], re[t]);
       im[t] = mfma(r.il, bh[t], im[t]);
+      Frag c;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) bh[t].w[i] = pk_mul(bh[t].w[i], bx[t]);
-      re[t] = mfma(nr, bh[t], re[t]);
-      im[t] = mfma(ni, bh[t], im[t]);
-    }
-#pragma unroll 1
-    for (int j = 2; j <= order; ++j) {
-      const unsigned f = pair_of(1.0f / (float)j);
+      for (int i = 0; i < 4; ++i) c.w[i] = pk_mul(bh[t].w[i], bx[t]);
+      if constexpr (WIDE) {
+        const unsigned x_rest = sh.b_rest[t * 32 + col];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const unsigned gk = pk_mul(r.g[i], f), n = pk_mul(ni.w[i], gk);
-        ni.w[i] = pk_mul_neg(nr.w[i], gk);
-        nr.w[i] = n;
+        for (int i = 0; i < 4; ++i) bl[t].w[i] = mul_rest(bh[t].w[i], bl[t].w[i], bx[t], x_rest, c.w[i]);
+        re[t] = mfma(nr, bl[t], re[t]);
+        im[t] = mfma(ni, bl[t], im[t]);
+        re[t] = mfma(mr, c, re[t]);
+        im[t] = mfma(mi, c, im[t]);
       }
+      re[t] = mfma(nr, c, re[t]);
+      im[t] = mfma(ni, c, im[t]);
+      if constexpr (WIDE) {
+        if (terms > 1) {
+          Frag n2r, n2i;
 #pragma unroll
-      for (int t = 0; t < XT; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bh[t].w[i] = pk_mul(bh[t].w[i], bx[t]);
-        re[t] = mfma(nr, bh[t], re[t]);
-        im[t] = mfma(ni, bh[t], im[t]);
+          for (int i = 0; i < 4; ++i) {
+            const unsigned g = pk_mul(r.g[i], pair_of(0.5f));
+            n2r.w[i] = pk_mul(ni.w[i], g);
+            n2i.w[i] = pk_mul_neg(nr.w[i], g);
+            c.w[i] = pk_mul(c.w[i], bx[t]);
+          }
+          re[t] = mfma(n2r, c, re[t]);
+          im[t] = mfma(n2i, c, im[t]);
+        }
       }
     }
   };
@@ -409,7 +437,7 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
     __syncthreads();
 
 #pragma unroll 1
-    for (int ks = 0; ks < n8 / 8; ++ks) products(ks, cur.order);
+    for (int ks = 0; ks < n8 / 8; ++ks) products(ks, cur.order & kWTerms);
     if (!last) continue;
     // Jones correction of this subgrid, A_p^H S A_q, tapered and added to the group's sum;
     // a pixel's terms are loaded while the one before is computed
@@ -488,7 +516,7 @@ struct DegridLds {
   VisBlock<kDegBlk> vb;
   float2 part[4][kDegBlk * 4];
   double axis[L];
-  alignas(16) unsigned b[L];  // (-b, b) pairs
+  alignas(16) unsigned b[2][L];  // (-b, b) pairs: FP16, and what that leaves
 };
 
 // One workgroup per subgrid, 32 rows of the subgrid at a time.  Each wave corrects its
@@ -517,7 +545,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const float inv_nc = 1.0f / (float)s.nc;
   for (int i = tid; i < L; i += kThreads) {
     sh.axis[i] = a.axis_n1[i];
-    sh.b[i] = a.axis_b[i] ^ kNegLow;
+    sh.b[0][i] = a.axis_b[i] ^ kNegLow;
+    sh.b[1][i] = a.axis_b[L + i] ^ kNegLow;
   }
   // operand column of this lane: polarisation q of row yl of the wave's eight
   const int q = col & 3, yl = wave * 8 + (col >> 2);
@@ -650,18 +679,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         tr = mfma(rl, sh_[ks], tr);
         ti = mfma(jl, sh_[ks], ti);
         if (s.order > 0) {
-          const Frag bx = *reinterpret_cast<const Frag*>(&sh.b[8 * ks + 4 * h]);
+          const Frag bx = *reinterpret_cast<const Frag*>(&sh.b[0][8 * ks + 4 * h]);
           Frag u;
 #pragma unroll
           for (int i = 0; i < 4; ++i) u.w[i] = swap_mul(sh_[ks].w[i], bx.w[i]);
           ur = mfma(rh, u, ur);
           ui = mfma(jh, u, ui);
-          if (s.order > 1) {
+          if (s.order & kWSplit) {
+            const Frag b_rest = *reinterpret_cast<const Frag*>(&sh.b[1][8 * ks + 4 * h]);
+            Frag rest;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const unsigned r = swap_fma_sub(sh_[ks].w[i], bx.w[i], u.w[i]);
+              rest.w[i] = swap_fma(sl_[ks].w[i], bx.w[i], swap_fma(sh_[ks].w[i], b_rest.w[i], r));
+            }
+            ur = mfma(rh, rest, ur);
+            ui = mfma(jh, rest, ui);
+            ur = mfma(rl, u, ur);
+            ui = mfma(jl, u, ui);
+          }
+          if ((s.order & kWTerms) > 1) {
             // wide fields: (2 pi d_k)^(j-1) / j! on the rows, (i b(x))^j b(y)^(j-1) S' on the columns
-            const unsigned dw = sh.vb.dw[col], by = sh.b[y0 + yl] & 0xFFFF0000u;
+            const unsigned dw = sh.vb.dw[0][col], by = sh.b[0][y0 + yl] & 0xFFFF0000u;
             const unsigned by2 = by | by >> 16;
             Frag r2 = rh, j2 = jh;
-            for (int j = 2; j <= s.order; ++j) {
+            for (int j = 2; j <= (s.order & kWTerms); ++j) {
               const unsigned f = pk_mul(dw, pair_of(1.0f / (float)j));
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
@@ -676,11 +718,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
       }
       if (s.order > 0) {
-        const float by = (float)__builtin_bit_cast(half2v, sh.b[y0 + yl]).y;
+        const float by = pair_high(sh.b[0][y0 + yl]) + pair_high(sh.b[1][y0 + yl]);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const float f =
-              by * (float)__builtin_bit_cast(half2v, sh.vb.dw[8 * (i >> 2) + 4 * h + (i & 3)]).x;
+          const int k = 8 * (i >> 2) + 4 * h + (i & 3);
+          const float f = by * (pair_high(sh.vb.dw[0][k]) + pair_high(sh.vb.dw[1][k]));
           tr[i] = fmaf(f, ur[i], tr[i]);
           ti[i] = fmaf(f, ui[i], ti[i]);
         }
@@ -745,8 +787,11 @@ template <int L>
 int launch_one(KernelClass k, const Group& g, hipStream_t st) {
   if (k == kGridDft) {
     const unsigned n = (unsigned)(g.split ? g.total_part : g.total_grp);
-    hipLaunchKernelGGL((grid_matrix<L>), dim3((n + kXcds - 1) / kXcds * kXcds * (L / kRows)), dim3(kThreads),
-                       sizeof(GridLds<L>), st, g);
+    const dim3 grid((n + kXcds - 1) / kXcds * kXcds * (L / kRows));
+    if (g.matrix == kMatrixWide)
+      hipLaunchKernelGGL((grid_matrix<L, true>), grid, dim3(kThreads), sizeof(GridLds<L>), st, g);
+    else
+      hipLaunchKernelGGL((grid_matrix<L, false>), grid, dim3(kThreads), sizeof(GridLds<L>), st, g);
   } else {
     hipLaunchKernelGGL((degrid_matrix<L>), dim3((unsigned)g.total_sg), dim3(kThreads), sizeof(DegridLds<L>), st, g);
   }

@@ -1,6 +1,6 @@
 """The matrix-core (de)gridder of FP32 plans where its fixed-size arithmetic could end: byte
 offsets of long, wide visibility tables, and FP16 operands of the w series under isolated
-off-axis sources.
+off-axis sources, their range and their rounding.
 """
 import numpy as np
 import pytest
@@ -87,6 +87,28 @@ def test_series_operands_stay_in_range(aidg, L, fov, dw):
                 assert np.abs(V[..., pol] - ref).max() <= 1e-5 + 1e-6 / T, (x, y)
         v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
         check_grid(p.grid(v).cpu().numpy(), q.grid(v.to(torch.complex128)).cpu().numpy(), 1e-5, f"L {L}, {fov} rad")
+
+
+@pytest.mark.parametrize("L", [32, 64, 96])
+@pytest.mark.parametrize("fov", [0.15, 0.58])
+@pytest.mark.parametrize("first", [1e-6, 2.4e-5, 1e-4, 4e-4, 1e-3])
+def test_sources_over_w_ranges(aidg, L, fov, first):
+    """Lone predicted sources over w ranges whose first series term is up to `first` of the tapered
+    field.  The rounding of FP32 cells 1 / (L^2 T) and of the subgrid's transform is some 2.5e-8
+    of the source after the taper, that of a phasor 1e-7: twice the sum is the bar."""
+    n1 = lambda r2: -r2 / (1 + np.sqrt(1 - r2))
+    t = Track(aidg, L, fov, 0.0)
+    l2 = t.l ** 2
+    c = n1(l2[:, None] + l2) - n1(l2)[:, None] - n1(l2)
+    t = Track(aidg, L, fov, first / (2 * np.pi * (np.outer(t.taper, t.taper) * -c).max()))
+    with t.plan() as p:
+        for r in (0.1, 0.2, 0.25, 0.3, 0.35, 0.4):
+            x = L // 2 + round(r * L)
+            G, ref, T = t.source(x, x)
+            d = np.abs(p.degrid(G).cpu().numpy()[..., 0] - ref)
+            rms = np.sqrt((d ** 2).mean())
+            print(f"L {L} fov {fov} first {first} source {r} taper {T:.1e}: rms {rms:.2e}")
+            assert rms <= 2 * (1e-7 + 2.5e-8 / T), r
 
 
 def test_rows_beyond_4_gib(aidg):
