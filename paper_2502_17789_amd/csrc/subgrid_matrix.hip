@@ -17,7 +17,8 @@
 // Precision: each FP32 factor is split into two FP16 numbers (x = hi + lo, both rounded to
 // nearest: 2^-24 of the largest value, the data scaled to that by a power of two per
 // subgrid) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
-// forms the products exactly and adds in FP32.  Every phase is formed and reduced to
+// forms the products exactly and adds in FP32; the gridder adds eight visibilities' sum at
+// once, the degridder sums the small products apart.  Every phase is formed and reduced to
 // [-1/2, 1/2] turn in FP64; there is no recurrence.  The series' first term takes hi hi
 // alone where its largest value, times the taper, is below 1.5e-5 (w_series_order), and
 // otherwise split operands as well; a second term is smaller and takes hi hi.
@@ -327,12 +328,11 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
         bh[t] = sh.alpha[ks][t][0][lane];
         bl[t] = sh.alpha[ks][t][1][lane];
       }
-      re[t] = mfma(r.rh, bh[t], re[t]);
-      im[t] = mfma(r.ih, bh[t], im[t]);
-      re[t] = mfma(r.rh, bl[t], re[t]);
-      im[t] = mfma(r.ih, bl[t], im[t]);
-      re[t] = mfma(r.rl, bh[t], re[t]);
-      im[t] = mfma(r.il, bh[t], im[t]);
+      // small products first, and the step's sum added whole: a chain of products onto the
+      // accumulators would round at the size of the subgrid's sum four times or more
+      acc16 cr = mfma(r.rl, bh[t], acc16{0}), ci = mfma(r.il, bh[t], acc16{0});
+      cr = mfma(r.rh, bl[t], cr);
+      ci = mfma(r.ih, bl[t], ci);
       Frag c;
 #pragma unroll
       for (int i = 0; i < 4; ++i) c.w[i] = pk_mul(bh[t].w[i], bx[t]);
@@ -340,13 +340,13 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
         const unsigned x_rest = sh.b_rest[t * 32 + col];
 #pragma unroll
         for (int i = 0; i < 4; ++i) bl[t].w[i] = mul_rest(bh[t].w[i], bl[t].w[i], bx[t], x_rest, c.w[i]);
-        re[t] = mfma(nr, bl[t], re[t]);
-        im[t] = mfma(ni, bl[t], im[t]);
-        re[t] = mfma(mr, c, re[t]);
-        im[t] = mfma(mi, c, im[t]);
+        cr = mfma(nr, bl[t], cr);
+        ci = mfma(ni, bl[t], ci);
+        cr = mfma(mr, c, cr);
+        ci = mfma(mi, c, ci);
       }
-      re[t] = mfma(nr, c, re[t]);
-      im[t] = mfma(ni, c, im[t]);
+      cr = mfma(nr, c, cr);
+      ci = mfma(ni, c, ci);
       if constexpr (WIDE) {
         if (terms > 1) {
           Frag n2r, n2i;
@@ -357,10 +357,14 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
             n2i.w[i] = pk_mul_neg(nr.w[i], g);
             c.w[i] = pk_mul(c.w[i], bx[t]);
           }
-          re[t] = mfma(n2r, c, re[t]);
-          im[t] = mfma(n2i, c, im[t]);
+          cr = mfma(n2r, c, cr);
+          ci = mfma(n2i, c, ci);
         }
       }
+      cr = mfma(r.rh, bh[t], cr);
+      ci = mfma(r.ih, bh[t], ci);
+      re[t] += cr;
+      im[t] += ci;
     }
   };
   float scale = 0, unscale = 0;

@@ -111,6 +111,25 @@ def test_sources_over_w_ranges(aidg, L, fov, first):
             assert rms <= 2 * (1e-7 + 2.5e-8 / T), r
 
 
+@pytest.mark.parametrize("L", [32, 64, 96])
+def test_gridder_rounds_no_more_than_the_general_kernel(aidg, L):
+    """Sums over a subgrid's visibilities: the matrix gridder adds a step of eight at once, the
+    general one (plans that ask for runs below 32 channels) two, so its error against the FP64
+    plan is no larger but for the draw's spread, some 5 % over these six."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    err = {0: 0.0, 31: 0.0}
+    for dw in (0.0, 0.1, 0.6):
+        t = Track(aidg, L, 0.3, dw)
+        with t.plan() as p, t.plan(reseed_channels=31) as r, t.plan(1) as q:
+            for _ in range(2):
+                v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
+                ref = q.grid(v.to(torch.complex128))
+                for plan, key in ((p, 0), (r, 31)):
+                    err[key] += float(((plan.grid(v) - ref).norm() / ref.norm()) ** 2 / 6)
+    print(f"L {L}: matrix {err[0] ** 0.5:.3e}, general {err[31] ** 0.5:.3e}")
+    assert err[0] <= 1.1 ** 2 * err[31]
+
+
 def test_rows_beyond_4_gib(aidg):
     """One sub-table of 2048 rows in the last of 65600 channels: its last rows start beyond 2^32
     bytes.  The same rows as a table of that one channel give the same visibilities bit for bit
