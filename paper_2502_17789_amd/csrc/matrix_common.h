@@ -127,6 +127,10 @@ __device__ __forceinline__ void fit_scale(float m, float& scale, float& unscale)
   unscale = __uint_as_float((unsigned)(127 - 9 + e) << 23);
 }
 
+__device__ __forceinline__ float inverse_power(float p) {  // of a power of two, 2^-126 to 2^126
+  return __uint_as_float((254u << 23) - __float_as_uint(p));
+}
+
 // Largest of the wave's values (>= 0), by DPP: rotations within each row of 16 lanes, then
 // the four rows.
 __device__ __forceinline__ float wave_max(float m) {
@@ -137,6 +141,17 @@ __device__ __forceinline__ float wave_max(float m) {
   const int v = __float_as_int(m);
   return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(v, 0)), __int_as_float(__builtin_amdgcn_readlane(v, 16))),
                fmaxf(__int_as_float(__builtin_amdgcn_readlane(v, 32)), __int_as_float(__builtin_amdgcn_readlane(v, 48))));
+}
+// Largest of the values (>= 0) of the wave's lanes of the same parity, in each lane.
+__device__ __forceinline__ float parity_max(float m) {
+  m = fmaxf(m, dpp<0x122>(m));
+  m = fmaxf(m, dpp<0x124>(m));
+  m = fmaxf(m, dpp<0x128>(m));
+  float n = m;
+  swap16(m, n);
+  m = n = fmaxf(m, n);
+  swap32(m, n);
+  return fmaxf(m, n);
 }
 
 // Visibilities per LDS block.

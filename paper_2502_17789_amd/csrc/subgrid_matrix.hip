@@ -16,7 +16,7 @@
 //
 // Precision: each FP32 factor is split into two FP16 numbers (x = hi + lo, both rounded to
 // nearest: 2^-24 of the largest value, the data scaled to that by a power of two per
-// subgrid) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
+// subgrid and polarisation) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
 // forms the products exactly and adds in FP32; the gridder adds eight visibilities' sum at
 // once, the degridder sums the small products apart.  Every phase is formed and reduced to
 // [-1/2, 1/2] turn in FP64; there is no recurrence.  The series' first term takes hi hi
@@ -98,12 +98,11 @@ __device__ __forceinline__ void store_phase(const KernelArgs& a, const SubgridDe
   vb->dw[1][k] = dl;
 }
 
-// scale beta_k(y) of the workgroup's 32 rows from y0 for the block's first n visibilities,
+// beta_k(y) of the workgroup's 32 rows from y0 for the block's first n visibilities,
 // FP32: [32][B + 2] (the pitch shifts each row by four banks: eight rows' 16-byte reads meet
 // no bank twice).
 template <int L, int B>
-__device__ __forceinline__ void stage_beta(const VisBlock<B>* vb, const double* axis, int y0, int n, float scale,
-                                           float2* beta) {
+__device__ __forceinline__ void stage_beta(const VisBlock<B>* vb, const double* axis, int y0, int n, float2* beta) {
   static_assert(B == 32 && kThreads == 256 && kRows == 32, "four rows per thread");
   int tid = threadIdx.x;  // opaque: formed again for each block, not held across it
   asm volatile("" : "+v"(tid));
@@ -113,8 +112,7 @@ __device__ __forceinline__ void stage_beta(const VisBlock<B>* vb, const double* 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = y + 8 * i;
-    const float2 e = turn_phasor(kv.x, (double)(y0 + r - L / 2), kv.y, axis[y0 + r]);
-    beta[r * (B + 2) + k] = {e.x * scale, e.y * scale};
+    beta[r * (B + 2) + k] = turn_phasor(kv.x, (double)(y0 + r - L / 2), kv.y, axis[y0 + r]);
   }
 }
 
@@ -132,27 +130,28 @@ __device__ __forceinline__ PixelTerms load_pixel(const KernelArgs& a, const char
   return {gload<vec4>(Ap, 32 * pix), gload<vec4>(Ap, 32 * pix + 16), gload<vec4>(Aq, 32 * pix),
           gload<vec4>(Aq, 32 * pix + 16), gload<vec2>(a.taper_cross, 8 * pix)};
 }
-// d += A^H (w E(w_s c) S) B with A = (p0, p1), B = (q0, q1); INV: scaled by 1 / ||A^H B||_F.
+// d += A^H (f E(w_s c) S) B with A = (p0, p1), B = (q0, q1) and f a factor per polarisation;
+// INV: scaled by 1 / ||A^H B||_F.
 template <bool INV>
-__device__ __forceinline__ void add_corrected(const PixelTerms& x, float wmid, float w, const float2 (&s)[4],
+__device__ __forceinline__ void add_corrected(const PixelTerms& x, float wmid, const float4& f, const float2 (&s)[4],
                                               float (&d)[8]) {
   const float2 a0 = {x.p0.x, -x.p0.y}, a1 = {x.p0.z, -x.p0.w}, a2 = {x.p1.x, -x.p1.y}, a3 = {x.p1.z, -x.p1.w};  // conj
   const float2 b0 = {x.q0.x, x.q0.y}, b1 = {x.q0.z, x.q0.w}, b2 = {x.q1.x, x.q1.y}, b3 = {x.q1.z, x.q1.w};
-  w *= x.tc.x;
+  float w = x.tc.x;
   if constexpr (INV) {
     // ||B_p^H B_q||_F^2 with B_p^H = [[a0, a2], [a1, a3]] (a already conjugated)
     const float2 m0 = cmul<float>(a0, b0) + cmul<float>(a2, b2), m1 = cmul<float>(a0, b1) + cmul<float>(a2, b3);
     const float2 m2 = cmul<float>(a1, b0) + cmul<float>(a3, b2), m3 = cmul<float>(a1, b1) + cmul<float>(a3, b3);
     const float n2 = m0.x * m0.x + m0.y * m0.y + m1.x * m1.x + m1.y * m1.y + m2.x * m2.x + m2.y * m2.y + m3.x * m3.x +
                      m3.y * m3.y;
-    const float f = w / sqrtf(n2 > 0.0f ? n2 : 1.0f);
-    w = n2 > 0.0f ? f : 0.0f;
+    const float v = w / sqrtf(n2 > 0.0f ? n2 : 1.0f);
+    w = n2 > 0.0f ? v : 0.0f;
   }
   // taper and E(w_s c), |w_s c| <= 128 turns
   const float ph = wmid * x.tc.y;
   const float2 e = {w * __builtin_amdgcn_cosf(ph), w * __builtin_amdgcn_sinf(ph)};
-  const float2 s0 = cmul<float>(e, s[0]), s1 = cmul<float>(e, s[1]);
-  const float2 s2 = cmul<float>(e, s[2]), s3 = cmul<float>(e, s[3]);
+  const float2 s0 = cmul<float>(e, s[0]) * f.x, s1 = cmul<float>(e, s[1]) * f.y;
+  const float2 s2 = cmul<float>(e, s[2]) * f.z, s3 = cmul<float>(e, s[3]) * f.w;
   // A_p^H = [[conj a0, conj a2], [conj a1, conj a3]]
   const float2 t0 = cfma(a2, s2, cmul<float>(a0, s0)), t1 = cfma(a2, s3, cmul<float>(a0, s1));
   const float2 t2 = cfma(a3, s2, cmul<float>(a1, s0)), t3 = cfma(a3, s3, cmul<float>(a1, s1));
@@ -181,7 +180,8 @@ struct GridLds {
   VisBlock<kBlk> vb;
   double axis[L];
   unsigned b_rest[L];
-  float peak;
+  float4 unscale, shrink;  // of the polarisations
+  int shrunk;
   float4 sum[kLdsPixels<L>][2][kThreads];
 };
 
@@ -367,7 +367,6 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
       im[t] += ci;
     }
   };
-  float scale = 0, unscale = 0;
   SubgridDev s = load_uniform(a.sg + gs.sb);
   int64_t si = gs.sb;
   int k0 = 0;
@@ -383,32 +382,40 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
     if (tid < 2 * kBlk) {
       const int k = tid >> 1, p = 2 * (tid & 1);
       const vec4 v = next_v;
-      sh.vis[p * (kBlk + 2) + k] = {v.x, v.y};
-      sh.vis[(p + 1) * (kBlk + 2) + k] = {v.z, v.w};
-      const float m = wave_max(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-      if (lane == 0) sh.peak = m;
+      // The scale of the lane's two polarisations' data: a power of two that fits the subgrid's
+      // largest values so far (each polarisation has its own: cross hands may be orders of
+      // magnitude below the parallel ones), and what brings sums under the previous one to it.
+      const float2 before = reinterpret_cast<const float2*>(&sh.unscale)[tid & 1];
+      float2 un, scale, shrink;
+      fit_scale(parity_max(fmaxf(fabsf(v.x), fabsf(v.y))), scale.x, un.x);
+      fit_scale(parity_max(fmaxf(fabsf(v.z), fabsf(v.w))), scale.y, un.y);
+      if (k0) un = {fmaxf(un.x, before.x), fmaxf(un.y, before.y)};
+      scale = {inverse_power(un.x), inverse_power(un.y)};
+      shrink = {before.x * scale.x, before.y * scale.y};
+      sh.vis[p * (kBlk + 2) + k] = {v.x * scale.x, v.y * scale.x};
+      sh.vis[(p + 1) * (kBlk + 2) + k] = {v.z * scale.y, v.w * scale.y};
+      const bool shrunk = __ballot(shrink.x < 1.0f || shrink.y < 1.0f) != 0;
+      if (lane < 2) {
+        reinterpret_cast<float2*>(&sh.unscale)[lane] = un;
+        reinterpret_cast<float2*>(&sh.shrink)[lane] = shrink;
+        sh.shrunk = shrunk;
+      }
     } else if (tid < 3 * kBlk) {
       store_phase(a, s, next, k0 + tid - 2 * kBlk < nv, tid - 2 * kBlk, &sh.vb);
     }
     __syncthreads();
-    // the data's scale: a power of two that fits the subgrid's largest value so far (folded
-    // into beta); sums under an earlier, larger one are brought to it
-    float sc, un;
-    fit_scale(sh.peak, sc, un);
     if (k0 == 0) {
-      scale = sc;
-      unscale = un;
 #pragma unroll
       for (int t = 0; t < XT; ++t) re[t] = im[t] = acc16{0};
-    } else if (sc < scale) {
-      const float f = sc * unscale;
+    } else if (__builtin_amdgcn_readfirstlane(sh.shrunk)) {
+      const float4 f = uniform(sh.shrink);
 #pragma unroll
-      for (int t = 0; t < XT; ++t) {
-        re[t] *= f;
-        im[t] *= f;
-      }
-      scale = sc;
-      unscale = un;
+      for (int t = 0; t < XT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          re[t][i] *= (&f.x)[i & 3];
+          im[t][i] *= (&f.x)[i & 3];
+        }
     }
     // four visibilities per thread (kg), one column of each tile
     const int kg = tid >> 5, xc = tid & 31;
@@ -431,7 +438,7 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
         f[64] = fl;
       }
     }
-    stage_beta<L>(&sh.vb, sh.axis, y0, n8, scale, sh.beta);
+    stage_beta<L>(&sh.vb, sh.axis, y0, n8, sh.beta);
     // the next block: of this subgrid, or the next one's first
     const SubgridDev cur = s;
     const bool last = k0 + kBlk >= nv, done = last && si + 1 == gs.se;
@@ -447,6 +454,7 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
     // a pixel's terms are loaded while the one before is computed
     const char* Ap = At + (int64_t)cur.ap * L * L * 32;
     const char* Aq = At + (int64_t)cur.aq * L * L * 32;
+    const float4 un = uniform(sh.unscale);
     auto epilogue = [&](auto inverse) {
       unsigned pe = pix0;
       asm volatile("" : "+v"(pe));  // the pixels' offsets are not worth holding across subgrids
@@ -461,11 +469,11 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
         if (i < P0) {
           const float4 o0 = sh.sum[i][0][tid], o1 = sh.sum[i][1][tid];
           float d[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, unscale, sv, d);
+          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, un, sv, d);
           sh.sum[i][0][tid] = {d[0], d[1], d[2], d[3]};
           sh.sum[i][1][tid] = {d[4], d[5], d[6], d[7]};
         } else {
-          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, unscale, sv, sum[i - P0]);
+          add_corrected<decltype(inverse)::value>(px[i % kAhead], cur.wmid, un, sv, sum[i - P0]);
         }
         asm volatile("" : "+v"(pe));
         if (n < NPIX) px[i % kAhead] = load_pixel(a, Ap, Aq, pe + 2 * (n % NP) * L + 32 * (n / NP));
@@ -560,7 +568,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   for (int y0 = 0; y0 < L; y0 += kRows) {
     // the wave's rows, corrected: lane (col, h) takes column x = 32 t + col of rows 2 p + h
     float c[XT][NP][8];
-    float m = 0;
+    float m[4] = {0, 0, 0, 0};  // largest of each polarisation
     unsigned pix0 = (y0 + wave * 8 + h) * L + col;
     struct Pixel {
       PixelTerms x;
@@ -601,11 +609,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         asm volatile("" : "+v"(d[k]));
-        m = fmaxf(m, fabsf(d[k]));
+        m[k >> 1] = fmaxf(m[k >> 1], fabsf(d[k]));
       }
     }
-    float scale, unscale;
-    fit_scale(wave_max(m), scale, unscale);
+    float scale[4], unscale = 0;  // a scale per polarisation, as in the gridder; the lane's q
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float un;
+      fit_scale(wave_max(m[k]), scale[k], un);
+      if (q == k) unscale = un;
+    }
     __syncthreads();  // the previous pass's operands are no longer read
     // operand order: lane (col, h) holds row (yl, q), columns 8 ks + 4 h + 0 .. 3
     Frag sh_[KS], sl_[KS];
@@ -617,7 +630,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           unsigned hi, lo;
-          split(c[t][p][2 * k] * scale, c[t][p][2 * k + 1] * scale, hi, lo);
+          split(c[t][p][2 * k] * scale[k], c[t][p][2 * k + 1] * scale[k], hi, lo);
           sh.lay[0][wave][(2 * p + h) * 4 + k][col] = hi;
           sh.lay[1][wave][(2 * p + h) * 4 + k][col] = lo;
         }
@@ -665,7 +678,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
           f[192] = jl;
         }
       }
-      stage_beta<L>(&sh.vb, sh.axis, y0, B, 1.0f, sh.beta);
+      stage_beta<L>(&sh.vb, sh.axis, y0, B, sh.beta);
       __syncthreads();
 
       // sum over x of conj(alpha) S': columns (S_re, S_im), rows (alpha_re, alpha_im) for the
