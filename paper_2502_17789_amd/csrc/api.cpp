@@ -742,17 +742,21 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       d.group = plan->sg_group[i];
       const double df = s.nc > 1 ? freqs_hz[s.c0 + 1] - freqs_hz[s.c0] : 0.0;
       bool uniform = true;
-      for (int c = s.c0 + 1; c < s.c0 + s.nc; ++c)
+      double f_lo = freqs_hz[s.c0], f_hi = f_lo;  // a caller's table takes them in any order
+      for (int c = s.c0 + 1; c < s.c0 + s.nc; ++c) {
         if (std::fabs((freqs_hz[c] - freqs_hz[c - 1]) - df) > 1e-9 * std::fabs(df)) uniform = false;
+        f_lo = std::min(f_lo, freqs_hz[c]);
+        f_hi = std::max(f_hi, freqs_hz[c]);
+      }
       d.dfc = df * inv_c;
       d.R = uniform ? g.R : 1;
       d.kind = degrid_form(g, s.nt, s.nc, uniform);
       if (matrix) {
-        // w range of the sub-table, from its rows' end channels (frequencies increase)
+        // w range of the sub-table
         double lo = 1e300, hi = -1e300;
         for (int64_t r = d.uvw0; r < d.uvw0 + s.nt; ++r)
-          for (int c : {s.c0, s.c0 + s.nc - 1}) {
-            const double w = uvw_dev[3 * r + 2] * (freqs_hz[c] * inv_c) - s.w0;
+          for (double f : {f_lo * inv_c, f_hi * inv_c}) {
+            const double w = uvw_dev[3 * r + 2] * f - s.w0;
             lo = std::min(lo, w);
             hi = std::max(hi, w);
           }
