@@ -752,18 +752,23 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
       d.R = uniform ? g.R : 1;
       d.kind = degrid_form(g, s.nt, s.nc, uniform);
       if (matrix) {
-        // w range of the sub-table
+        // w range of the sub-table; a caller's table may also hold rows that are not finite or
+        // far off the window, whose phases the fixed-point reduction would not take
         double lo = 1e300, hi = -1e300;
         for (int64_t r = d.uvw0; r < d.uvw0 + s.nt; ++r)
           for (double f : {f_lo * inv_c, f_hi * inv_c}) {
-            const double w = uvw_dev[3 * r + 2] * f - s.w0;
+            const double* x = &uvw_dev[3 * r];
+            const double w = x[2] * f - s.w0;
             lo = std::min(lo, w);
             hi = std::max(hi, w);
+            if (table && !(std::fabs(x[0] * f * g.fov - (s.U0 - g.N / 2)) <= 0x1p18 &&
+                           std::fabs(x[1] * f * g.fov - (s.V0 - g.N / 2)) <= 0x1p18 && std::isfinite(w)))
+              matrix = false;
           }
         d.wmid = (float)(0.5 * (lo + hi));
         const double dw = std::max(hi - d.wmid, d.wmid - lo);
         d.order = w_series_order(series, d.wmid, dw);
-        matrix = d.order >= 0;
+        matrix = matrix && d.order >= 0;
         wide = wide || (matrix && (d.order & kWSplit));
       }
       cost += degrid_cost(d.kind, s.nt, s.nc);

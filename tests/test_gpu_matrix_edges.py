@@ -177,6 +177,25 @@ def test_channels_in_any_order(aidg, L):
             assert float((x - y).norm() / y.norm()) <= 1e-6
 
 
+@pytest.mark.parametrize("row", [(np.nan, 0, 0), (0, np.inf, 0), (0, 0, np.nan), (1.6e7 + 5.3, 0, 0), (0, 5.3 - 1.6e7, 0)])
+def test_rows_that_have_no_phase_in_fixed_point(aidg, row):
+    """Rows that are not finite have no phase and give NaN; rows a long way off the window have one,
+    here of up to 2e6 turns (the general kernels count quarter turns in 32 bits)."""
+    t = Track(aidg, 32, 0.25, 0.0)
+    t.freqs = np.full(1, LIGHT)  # metres are wavelengths
+    t.uvw[0, 3] = row
+    table = one_subgrid(t)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    with t.plan(table=table) as p, t.plan(1, table=table) as q:
+        v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        G = torch.randn(p.grid_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        for x, y in ((p.grid(v), q.grid(v.to(torch.complex128))), (p.degrid(G), q.degrid(G.to(torch.complex128)))):
+            assert torch.equal(x.isnan(), y.isnan())
+            assert x.isnan().any() == (not np.isfinite(row).all())
+            x, y = x[~y.isnan()], y[~y.isnan()]
+            assert float((x - y).norm()) <= 1e-6 * float(y.norm())
+
+
 def test_rows_beyond_4_gib(aidg):
     """One sub-table of 2048 rows in the last of 65600 channels: its last rows start beyond 2^32
     bytes.  The same rows as a table of that one channel give the same visibilities bit for bit
