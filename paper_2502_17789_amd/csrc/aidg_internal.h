@@ -91,8 +91,12 @@ aidg_status partition(const Geometry& g, int n_st, int nbl, int nt, int nc, cons
 // subgrids (per row: the channel runs its uv extent needs, plus one per gap or layer
 // change, plus the splits at max_sg_vis), and of the number of same-centre groups (the
 // distinct (layer, lattice centre) pairs of the runs' midpoints, plus a quarter).
+struct CentreEstimate {
+  double n_subgrids = 0, n_vis = 0;
+};
 struct ShapeEstimate {
   int64_t jmin = 0, jmax = 0, n_excluded = 0, n_subgrids = 0, n_groups = 0;
+  std::vector<CentreEstimate> centres;  // the distinct pairs
 };
 void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uvw, const double* freqs,
                     ShapeEstimate* out);

@@ -293,6 +293,25 @@ void split_groups(aidg_plan* p) {
     }
 }
 
+// Parts beyond one per group that split_groups would make of an estimated partition: its
+// rules, each centre's subgrids taken as equal, and a quarter more where they decide.
+int64_t estimate_parts(const Geometry& g, const ShapeEstimate& se) {
+  double vis = 0, total = 0, heaviest = 0, parts = 0;
+  auto cost = [](const CentreEstimate& c) { return std::max(c.n_vis, 32 * c.n_subgrids) + 20 * c.n_subgrids; };
+  for (const CentreEstimate& c : se.centres) {
+    vis += c.n_vis;
+    total += cost(c);
+  }
+  const double cap_vis = std::max<double>(g.max_sg_vis, kGroupVisFactor * vis / std::max<size_t>(se.centres.size(), 1));
+  const double cap = std::max<double>(kMinPartCost, total / (2 * groups_in_flight(g.L)));
+  for (const CentreEstimate& c : se.centres) {
+    heaviest = std::max(heaviest, cost(c) * std::min(1.0, cap_vis / std::max(c.n_vis, 1.0)));
+    parts += std::ceil(c.n_subgrids / std::max(1.0, std::floor(cap * c.n_subgrids / cost(c)))) - 1;
+  }
+  if (!worth_split(g.L, (int64_t)(1.25 * heaviest) + 1, (int64_t)total) || 1.25 * heaviest <= cap) return 0;
+  return std::max<int64_t>(0, std::min<int64_t>((int64_t)parts, se.n_subgrids - se.n_groups));
+}
+
 // Launch one kernel class over subgrids [b0, b0 + n) of one plan.
 aidg_status run(aidg_plan* p, KernelClass k, int64_t b0, int64_t n, const void* in, void* out,
                 void* stream, int adjoint = 0) {
@@ -1078,13 +1097,7 @@ aidg_status aidg_footprint_estimate(const aidg_geometry* geo, int32_t n_stations
     // what aidg_plan_create allocates, each allocation at least 256 bytes
     auto al = [](int64_t b) { return std::max<int64_t>(b, 256); };
     const int64_t per_image = 4 * L * L * elem;
-    // parts of groups beyond one each: none where the cap on groups keeps them even
-    int64_t parts = 0;
-    if (5 * se.n_groups < 2 * kGroupVisFactor * groups_in_flight((int)L)) {
-      const int64_t total = n_vis + 20 * n_sg;
-      const int64_t cap = std::max<int64_t>(kMinPartCost, total / (2 * groups_in_flight((int)L)));
-      parts = std::max<int64_t>(0, std::min(n_sg - se.n_groups, total / cap));
-    }
+    const int64_t parts = estimate_parts(g, se);
     int64_t batch = std::max<int64_t>(1, std::min<int64_t>(g.workspace / per_image, 65535));
     batch = std::min(batch, std::max<int64_t>(1, se.n_groups + (se.n_groups + parts <= batch ? parts : 0)));
     int64_t b = al(n_sg * (int64_t)sizeof(SubgridDev)) + al((int64_t)n_baselines * n_times * 24 * (g.fold ? 2 : 1)) +

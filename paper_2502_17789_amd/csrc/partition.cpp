@@ -3,7 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <unordered_set>
+#include <unordered_map>
 #include <vector>
 
 #include "aidg_internal.h"
@@ -330,15 +330,17 @@ void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uv
   // Same-centre groups: the partition centres a run near the middle of its uv span on
   // the lattice N/2 + k lattice (clamped so that the window stays on the grid), so the
   // distinct (layer, nearest lattice cell) pairs of the runs' midpoints count them.
-  std::unordered_set<uint64_t> centres;
+  std::unordered_map<uint64_t, CentreEstimate> centres;
   auto lattice_cell = [&](double c) {
     const double k = std::nearbyint((c - g.N / 2) / g.lattice);
     const double lo = std::ceil((g.L / 2 - g.N / 2) / (double)g.lattice),
                  hi = std::floor((g.N - g.L / 2 - g.N / 2) / (double)g.lattice);
     return (uint64_t)((int64_t)std::min(std::max(k, lo), hi) + (1 << 19)) & 0xFFFFF;
   };
-  auto mark = [&](double cu, double cv, int64_t lay) {
-    centres.insert(((uint64_t)(lay + (1 << 23)) & 0xFFFFFF) << 40 | lattice_cell(cu) << 20 | lattice_cell(cv));
+  auto mark = [&](double cu, double cv, int64_t lay, double subgrids, double vis) {
+    CentreEstimate& c = centres[((uint64_t)(lay + (1 << 23)) & 0xFFFFFF) << 40 | lattice_cell(cu) << 20 | lattice_cell(cv)];
+    c.n_subgrids += subgrids;
+    c.n_vis += vis;
   };
   auto take = [&](int64_t lay) {
     out->jmin = any ? std::min(out->jmin, lay) : lay;
@@ -382,7 +384,8 @@ void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uv
           const int64_t j0 = x.layer(bl, t, 0), j1 = x.layer(bl, t, nc - 1);
           for (int64_t i = 0; i < runs; ++i) {
             const double f = (i + 0.5) / runs;
-            mark(u0 + f * (u1 - u0), v0 + f * (v1 - v0), std::llround(j0 + f * (double)(j1 - j0)));
+            mark(u0 + f * (u1 - u0), v0 + f * (v1 - v0), std::llround(j0 + f * (double)(j1 - j0)),
+                 (double)(runs + layers) / runs, (double)(te - ta) * nc / (double)(segs * runs));
           }
         }
         placed += (int64_t)(te - ta) * nc;
@@ -390,7 +393,7 @@ void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uv
       }
       for (int t = ta; t < te; ++t) {
       Box b;
-      int64_t prev_layer = 0, pieces = 0;
+      int64_t prev_layer = 0, pieces = 0, row_vis = 0;
       bool prev_ok = false;
       for (int c = 0; c < nc; ++c) {
         if (!x.placeable(bl, t, c)) {
@@ -404,11 +407,13 @@ void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uv
         prev_layer = lay;
         b.add(x.cell(bl, t, c, 0), x.cell(bl, t, c, 1));
         take(lay);
-        ++placed;
+        ++row_vis;
       }
+      placed += row_vis;
       if (pieces) {
-        out->n_subgrids += pieces + (int64_t)std::floor(std::max(b.uhi - b.ulo, b.vhi - b.vlo) / comfy);
-        mark(0.5 * (b.ulo + b.uhi), 0.5 * (b.vlo + b.vhi), prev_layer);
+        const int64_t n = pieces + (int64_t)std::floor(std::max(b.uhi - b.ulo, b.vhi - b.vlo) / comfy);
+        out->n_subgrids += n;
+        mark(0.5 * (b.ulo + b.uhi), 0.5 * (b.vlo + b.vhi), prev_layer, (double)n, (double)row_vis);
       }
       }
     }
@@ -416,6 +421,8 @@ void estimate_shape(const Geometry& g, int nbl, int nt, int nc, const double* uv
   // a quarter more for the groups the size cap splits (at most one in eight) and the
   // centres the midpoint sample misses
   out->n_groups = std::min<int64_t>(((int64_t)centres.size() * 5 + 3) / 4, out->n_subgrids);
+  out->centres.reserve(centres.size());
+  for (const auto& c : centres) out->centres.push_back(c.second);
 }
 
 aidg_status partition(const Geometry& g, int n_st, int nbl, int nt, int nc, const int32_t* baselines,
