@@ -190,10 +190,23 @@ typedef struct {
   int64_t n_groups;        /* runs of subgrids with one w-layer and centre that share one
                               subgrid FFT; a centre holding more than 8x the mean
                               visibilities per centre is split into several */
-  int64_t n_subgrids_pervis; /* subgrids the degridder takes in its per-visibility form
-                              (geometry degrid_form) */
-  int64_t n_subgrids_direct; /* subgrids the degridder takes in its direct form */
+  int64_t n_subgrids_pervis; /* subgrids the general degridder takes in its per-visibility
+                              form (geometry degrid_form) */
+  int64_t n_subgrids_direct; /* subgrids the general degridder takes in its direct form; on the
+                              matrix cores (aidg_plan_kernels) there are no forms */
 } aidg_plan_info;
+
+/* Kernels that a plan's calls take: the general ones, or those on the matrix cores (FP32,
+ * reseed_channels of 32 or more, w ranges per subgrid that a short series in w serves, and
+ * for degridding the automatic degrid_form and subgrids that are not too sparse). */
+enum { AIDG_KERNEL_GENERAL = 0, AIDG_KERNEL_MATRIX = 1, AIDG_KERNEL_MATRIX_WIDE = 2 };
+typedef struct {
+  int32_t grid_kernel;     /* AIDG_KERNEL_MATRIX_WIDE: n_subgrids_split is not 0 */
+  int32_t degrid_kernel;   /* AIDG_KERNEL_GENERAL or AIDG_KERNEL_MATRIX */
+  int32_t w_terms;         /* most terms of the series in a subgrid (0 to 2) */
+  int32_t reserved;
+  int64_t n_subgrids_split; /* subgrids whose first term takes split operands */
+} aidg_plan_kernel_info;
 
 typedef struct aidg_plan aidg_plan;
 
@@ -224,6 +237,7 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
                              aidg_plan** out);
 
 aidg_status aidg_plan_info_get(const aidg_plan* plan, aidg_plan_info* info);
+aidg_status aidg_plan_kernels(const aidg_plan* plan, aidg_plan_kernel_info* info);
 
 /* Copy the plan's subgrid table (after splitting) to host memory; cap records at most. */
 aidg_status aidg_plan_subgrids(const aidg_plan* plan, aidg_subgrid* out, int64_t cap);

@@ -59,6 +59,14 @@ class _PlanInfo(ctypes.Structure):
                 ("n_subgrids_direct", ctypes.c_int64)]
 
 
+class _PlanKernels(ctypes.Structure):
+    _fields_ = [("grid_kernel", ctypes.c_int32), ("degrid_kernel", ctypes.c_int32), ("w_terms", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("n_subgrids_split", ctypes.c_int64)]
+
+
+KERNEL_GENERAL, KERNEL_MATRIX, KERNEL_MATRIX_WIDE = 0, 1, 2
+
+
 class _Footprint(ctypes.Structure):
     _fields_ = [("n_wlayers", ctypes.c_int32), ("n_pol", ctypes.c_int32), ("w_step", ctypes.c_double),
                 ("n_subgrids", ctypes.c_int64), ("n_excluded", ctypes.c_int64), ("grid_bytes", ctypes.c_int64),
@@ -137,6 +145,7 @@ def library() -> ctypes.CDLL:
         "aidg_partition": (I32, [P, I32, I32, I32, I32, P, P, P, P, I64, P, P]),
         "aidg_plan_create": (I32, [P, I32, I32, I32, I32, P, P, P, P, P, I64, P, P]),
         "aidg_plan_info_get": (I32, [P, P]),
+        "aidg_plan_kernels": (I32, [P, P]),
         "aidg_plan_subgrids": (I32, [P, P, I64]),
         "aidg_plan_wlayers": (I32, [P, P, I32]),
         "aidg_plan_set_aterms": (I32, [P, P, P]),
@@ -261,6 +270,13 @@ class Plan:
         out = np.zeros(max(self.info["n_subgrids"], 1), SUBGRID_DTYPE)
         _check(library().aidg_plan_subgrids(self._h, _ptr(out), out.shape[0]))
         return out[:self.info["n_subgrids"]].copy()
+
+    def kernels(self) -> dict:
+        """The kernels that the plan's calls take (``KERNEL_GENERAL`` or those on the matrix
+        cores), the most terms of their w series and the subgrids that split its first."""
+        k = _PlanKernels()
+        _check(library().aidg_plan_kernels(self._h, ctypes.byref(k)))
+        return {name: getattr(k, name) for name, _ in _PlanKernels._fields_ if name != "reserved"}
 
     def wlayers(self) -> np.ndarray:
         out = np.zeros(self.n_wlayers)

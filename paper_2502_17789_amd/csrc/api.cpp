@@ -104,6 +104,8 @@ struct aidg_plan {
   // matrix kernels: all of the plan's subgrids qualify (degridding: and they are not so
   // sparse that the other forms take less time, and the geometry asks for none)
   MatrixForm matrix_grid = kMatrixNone, matrix_degrid = kMatrixNone;
+  int32_t w_terms = 0;  // of the series, most in a subgrid
+  int64_t n_split = 0;  // subgrids with kWSplit
   // image level (invert / predict): Stockham radices of N, twiddles exp(-2 pi i k / N)
   // and the reciprocal of the taper's axis at image resolution (FP64); absent when N
   // is not supported
@@ -737,7 +739,6 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     if (f32) w_series(L, g.fov, T, &series);
     plan->b_peak = series.b_peak;
     bool matrix = f32 && g.R >= kReseedDefault;  // a shorter run asks for the seeds' precision
-    bool wide = false;
     double cost = 0.0;  // of the degridder's other forms
     std::vector<SubgridDev> dev(plan->table.size());
     for (size_t i = 0; i < plan->table.size(); ++i) {
@@ -788,13 +789,17 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
         const double dw = std::max(hi - d.wmid, d.wmid - lo);
         d.order = w_series_order(series, d.wmid, dw);
         matrix = matrix && d.order >= 0;
-        wide = wide || (matrix && (d.order & kWSplit));
+        if (matrix) {
+          plan->w_terms = std::max(plan->w_terms, d.order & kWTerms);
+          plan->n_split += (d.order & kWSplit) != 0;
+        }
       }
       cost += degrid_cost(d.kind, s.nt, s.nc);
       plan->n_pervis += d.kind == kDegridPerVis;
       plan->n_direct += d.kind == kDegridDirect;
     }
-    plan->matrix_grid = !matrix ? kMatrixNone : wide ? kMatrixWide : kMatrixPlain;
+    if (!matrix) plan->w_terms = plan->n_split = 0;
+    plan->matrix_grid = !matrix ? kMatrixNone : plan->n_split ? kMatrixWide : kMatrixPlain;
     // The matrix degridder works in blocks of 32 visibilities and takes the same time for 1
     // as for 32: 13.6, 44 and 94 ns per subgrid at L = 32, 64, 96 with the chip full.  The
     // other forms, with one row per subgrid and c channels, take 9 to 11 ns for c = 1 to 10
@@ -1003,6 +1008,14 @@ aidg_status aidg_plan_info_get(const aidg_plan* plan, aidg_plan_info* info) {
   info->max_subgrid_vis = plan->max_nv;
   info->n_subgrids_pervis = plan->n_pervis;
   info->n_subgrids_direct = plan->n_direct;
+  return AIDG_OK;
+}
+
+aidg_status aidg_plan_kernels(const aidg_plan* plan, aidg_plan_kernel_info* info) {
+  if (!plan || !info) return fail(AIDG_E_INVALID, "NULL plan or info");
+  static_assert(kMatrixNone == AIDG_KERNEL_GENERAL && kMatrixPlain == AIDG_KERNEL_MATRIX &&
+                    kMatrixWide == AIDG_KERNEL_MATRIX_WIDE, "one numbering");
+  *info = {plan->matrix_grid, plan->matrix_degrid, plan->w_terms, 0, plan->n_split};
   return AIDG_OK;
 }
 

@@ -1,7 +1,7 @@
 """The matrix-core (de)gridder of FP32 plans where its fixed-size arithmetic could end: byte
 offsets of long, wide visibility tables, and FP16 operands of the w series under isolated
 off-axis sources, their range and their rounding; polarisations of very different sizes;
-and tables of a caller that the library's own partition would not make.
+tables of a caller that the library's own partition would not make; and which kernels plans take.
 """
 import numpy as np
 import pytest
@@ -29,14 +29,14 @@ class Track:
     """Baselines of 16 times and 8 channels that stay within a subgrid about the centre, with w
     from -dw to dw wavelengths in one layer, and identity Jones terms."""
 
-    def __init__(self, aidg, L, fov, dw, n_bl=6, w_mid=0.0):
+    def __init__(self, aidg, L, fov, dw, n_bl=6, w_mid=0.0, nearby=False):
         self.L, self.N, self.fov, K, n_t = L, 4 * L, fov, L // 4, 16
         self.aidg, self.n_st = aidg, n_bl + 1
         rng = np.random.default_rng(7)
         self.freqs = np.linspace(149.9e6, 150.1e6, 8)
         lam = LIGHT / 150e6
         uv = rng.uniform(-0.2, 0.2, (n_bl, 1, 2)) + rng.uniform(-0.1, 0.1, (n_bl, n_t, 2))
-        uv *= (L - K) / fov
+        uv *= (L - K) / fov * (0.2 if nearby else 1.0)  # nearby: one subgrid per baseline
         w = w_mid + np.broadcast_to(np.linspace(-1, 1, n_t), (n_bl, n_t)) * dw / 1.001
         self.uvw = np.concatenate([uv, w[..., None]], -1) * lam
         self.bl = np.array([(i, i + 1) for i in range(n_bl)], np.int32)
@@ -64,6 +64,16 @@ class Track:
         w = self.uvw[:, :, None, :] * (self.freqs / LIGHT)[:, None]
         n1 = -(l * l + m * m) / (1 + np.sqrt(1 - l * l - m * m))
         return torch.from_numpy(g).cuda(), np.exp(-2j * np.pi * (w[..., 0] * l + w[..., 1] * m + w[..., 2] * n1)), T
+
+
+def first_term(aidg, L, fov, first, **kw):
+    """A track whose series' first term is up to `first` of the tapered field before the constant
+    that the plan takes off b (1.7 to 1.8 times less with it)."""
+    n1 = lambda r2: -r2 / (1 + np.sqrt(1 - r2))
+    t = Track(aidg, L, fov, 0.0)
+    l2 = t.l ** 2
+    c = n1(l2[:, None] + l2) - n1(l2)[:, None] - n1(l2)
+    return Track(aidg, L, fov, first / (2 * np.pi * (np.outer(t.taper, t.taper) * -c).max()), **kw)
 
 
 # |w| ranges at which the series takes two and three terms; the last is a narrow field
@@ -97,11 +107,7 @@ def test_sources_over_w_ranges(aidg, L, fov, first):
     """Lone predicted sources over w ranges whose first series term is up to `first` of the tapered
     field.  The rounding of FP32 cells 1 / (L^2 T) and of the subgrid's transform is some 2.5e-8
     of the source after the taper, that of a phasor 1e-7: twice the sum is the bar."""
-    n1 = lambda r2: -r2 / (1 + np.sqrt(1 - r2))
-    t = Track(aidg, L, fov, 0.0)
-    l2 = t.l ** 2
-    c = n1(l2[:, None] + l2) - n1(l2)[:, None] - n1(l2)
-    t = Track(aidg, L, fov, first / (2 * np.pi * (np.outer(t.taper, t.taper) * -c).max()))
+    t = first_term(aidg, L, fov, first)
     with t.plan() as p:
         for r in (0.1, 0.2, 0.25, 0.3, 0.35, 0.4):
             x = L // 2 + round(r * L)
@@ -110,6 +116,49 @@ def test_sources_over_w_ranges(aidg, L, fov, first):
             rms = np.sqrt((d ** 2).mean())
             print(f"L {L} fov {fov} first {first} source {r} taper {T:.1e}: rms {rms:.2e}")
             assert rms <= 2 * (1e-7 + 2.5e-8 / T), r
+
+
+@pytest.mark.parametrize("L", [32, 64, 96])
+def test_kernels_that_plans_take(aidg, L):
+    """Every length of the series, split and not, and every reason for the general kernels."""
+    general, matrix, wide = aidg.KERNEL_GENERAL, aidg.KERNEL_MATRIX, aidg.KERNEL_MATRIX_WIDE
+    for first, grid, terms in ((0.0, matrix, 0), (5e-9, matrix, 0), (1e-6, matrix, 1), (2e-5, matrix, 1),
+                               (4e-5, wide, 1), (4e-4, wide, 2), (3e-3, general, 0)):
+        with first_term(aidg, L, 0.3, first, nearby=True).plan() as p:
+            k = p.kernels()
+            assert (k["grid_kernel"], k["w_terms"]) == (grid, terms), (first, k)
+            assert k["degrid_kernel"] == min(grid, matrix)
+            assert (k["n_subgrids_split"] > 0) == (grid == wide)
+    t = Track(aidg, L, 0.3, 0.1)
+    for kw, grid, degrid in (({}, matrix, matrix), (dict(precision=1), general, general),
+                             (dict(reseed_channels=31), general, general), (dict(reseed_channels=96), matrix, matrix),
+                             (dict(degrid_form=aidg.DEGRID_RECURRENCE), matrix, general),
+                             (dict(degrid_form=aidg.DEGRID_DIRECT), matrix, general)):
+        with t.plan(**kw) as p:
+            k = p.kernels()
+            assert (k["grid_kernel"], k["degrid_kernel"]) == (grid, degrid), (kw, k)
+    t.uvw, t.freqs = np.ascontiguousarray(t.uvw[:, :1]), t.freqs[:1]  # one visibility per subgrid
+    with t.plan() as p:
+        assert p.kernels()["degrid_kernel"] == general
+    with Track(aidg, L, 0.9, 0.0, w_mid=3e5).plan() as p:  # FP32 phases of the middle w
+        assert p.kernels()["grid_kernel"] == general
+
+
+@pytest.mark.parametrize("L", [32, 64, 96])
+@pytest.mark.parametrize("n_t,n_c", [(2, 1), (2, 4), (3, 3), (4, 8), (11, 3), (16, 8)])
+def test_wide_series_at_block_edges(aidg, L, n_t, n_c):
+    """The gridder and degridder of split series operands at part-filled steps and blocks: FP32
+    sums, 2e-7 of the FP64 plan's, twice that is the bar."""
+    t = first_term(aidg, L, 0.3, 3e-4, nearby=True)
+    t.uvw, t.freqs = np.ascontiguousarray(t.uvw[:, np.linspace(0, 15, n_t).astype(int)]), t.freqs[:n_c]
+    g = torch.Generator(device="cuda").manual_seed(9)
+    with t.plan() as p, t.plan(1, table=p.subgrids()) as q:
+        assert p.kernels()["grid_kernel"] == aidg.KERNEL_MATRIX_WIDE
+        assert len(p.subgrids()) == len(t.bl)
+        v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        G = torch.randn(p.grid_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        for x, y in ((p.grid(v), q.grid(v.to(torch.complex128))), (p.degrid(G), q.degrid(G.to(torch.complex128)))):
+            assert float((x - y).norm() / y.norm()) <= 4e-7
 
 
 @pytest.mark.parametrize("L", [32, 64, 96])
