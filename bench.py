@@ -32,14 +32,15 @@ if ROOT not in sys.path:
 # Algorithmic work per (visibility, subgrid pixel) in the method's form: the 2x2
 # complex multiply-accumulate is 16 FP32 FMAs, the phasor step ph <- ph * step is 4
 # FP32 ops (2 mul + 2 FMA); each occupies one FMA issue slot, counted as 2 FLOP: 40.
-# Executed: the FP32 kernels form the sums as complex matrix products on the matrix cores,
-# 16 real multiply-adds per (visibility, pixel) and product, three products of FP16 halves
-# (hi hi, hi lo, lo hi) and one for the first term of the w series (the order of nearly all
-# subgrids here): 128 FLOP.  The FP64 kernels pair a recurrence run's channels
-# symmetrically about its centre, so two visibilities take 16 FMA per pixel with real
-# multipliers and one complex phasor step (6 FLOP): 19.
+# Executed on the matrix cores (the kernels of a plan: Plan.kernels): the sums are complex
+# matrix products, 16 real multiply-adds per (visibility, pixel) and product, three products of
+# FP16 halves (hi hi, hi lo, lo hi) and one for the first term of the w series, 128 FLOP; two
+# products more where that term takes split operands (subgrids of the degridder, all of a
+# gridder that has any; second terms are not counted).  The general kernels pair a recurrence
+# run's channels symmetrically about its centre, so two visibilities take 16 FMA per pixel with
+# real multipliers and one complex phasor step (6 FLOP): 19 vector FLOP.
 FLOP_PER_VP = 40
-FLOP_PER_VP_EXECUTED = {"fp32": 128, "fp64": 19}
+FLOP_PER_VP_MATRIX, FLOP_PER_VP_SPLIT, FLOP_PER_VP_GENERAL = 128, 64, 19
 # Dense FP16 matrix peak of MI355X: 256 CUs x 4 SIMDs x 1024 FLOP per clock x 2.4 GHz.
 PEAK_FP16_MATRIX_TFLOPS = 256 * 4 * 1024 * 2.4e9 / 1e12   # 2516.6
 # FP32 vector peak of MI355X: 256 CUs x 4 SIMDs x 2.4 GHz, each SIMD issuing up to
@@ -49,6 +50,15 @@ PEAK_FP16_MATRIX_TFLOPS = 256 * 4 * 1024 * 2.4e9 / 1e12   # 2516.6
 PEAK_FP32_TFLOPS = 256 * 4 * 32 * 2.4e9 * 2 / 1e12   # 157.3
 PEAK_FP32_SINGLE_ISSUE_TFLOPS = PEAK_FP32_TFLOPS / 2
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_mwa.json")
+
+
+def flop_executed(kernels: dict, n_subgrids: int) -> dict:
+    """FLOP per visibility and pixel that the DFT kernels of a plan (Plan.kernels) execute,
+    and the unit they execute them on."""
+    split = kernels["n_subgrids_split"] / max(n_subgrids, 1)
+    per = {"grid_dft": (kernels["grid_kernel"], 1.0 if split else 0.0), "degrid_dft": (kernels["degrid_kernel"], split)}
+    return {name: {"flop": FLOP_PER_VP_MATRIX + FLOP_PER_VP_SPLIT * part if kernel else FLOP_PER_VP_GENERAL,
+                   "unit": "fp16 matrix cores" if kernel else "vector"} for name, (kernel, part) in per.items()}
 
 
 def library_source_hash() -> str:
@@ -213,7 +223,8 @@ def workload_description(wl, info):
                     "Kolmogorov screen 2 rad rms)",
         "n_vis": int(wl.n_vis), "grid_size": wl.grid_size, "subgrid_size": wl.subgrid_size,
         "kernel_support": wl.kernel_support, "n_subgrids": int(info["n_subgrids"]),
-        "n_wlayers": int(info["n_wlayers"]), "precision": "fp32 (fp64 phase origins)",
+        "n_wlayers": int(info["n_wlayers"]),
+        "precision": "fp32 (phases of visibilities in fp64; products of fp32 values split into fp16 pairs, summed in fp32)",
     }
 
 
@@ -514,14 +525,13 @@ def _kernel_case(aidg, wl, prec, L, lattice=0, form=0, reps=2, reseed=0):
         torch.cuda.synchronize()
         kt = plan.kernel_times()
         info = plan.info
+        executed = flop_executed(plan.kernels(), info["n_subgrids"])
         del V, G, Vo
     torch.cuda.empty_cache()
     ms = {k: v["ms"] / reps for k, v in kt.items()}
     n = wl.n_vis
     t_grid = ms["grid_dft"] + ms["fft_add"]
     t_degrid = ms["split_ifft"] + ms["degrid_dft"]
-    matrix = {"grid_dft": prec == aidg.FP32, "degrid_dft": prec == aidg.FP32 and form == 0}
-    flop = {k: FLOP_PER_VP_EXECUTED["fp32" if matrix[k] else "fp64"] for k in matrix}
     return {
         "subgrid_size": L, "kernel_support": L // 4, "center_lattice": lattice or "auto",
         "precision": "fp32" if prec == aidg.FP32 else "fp64",
@@ -533,8 +543,9 @@ def _kernel_case(aidg, wl, prec, L, lattice=0, form=0, reps=2, reseed=0):
         "grid_mvis_s": round(n / (t_grid * 1e-3) / 1e6, 1),
         "degrid_mvis_s": round(n / (t_degrid * 1e-3) / 1e6, 1),
         "ms": {k: round(v, 3) for k, v in ms.items() if v > 0},
-        "dft_tflops": {k: round(kt[k]["vis_pixels"] * flop[k] / (ms[k] * reps * 1e-3) / 1e12, 2)
-                       for k in ("grid_dft", "degrid_dft")}}
+        "dft_unit": {k: executed[k]["unit"] for k in executed},
+        "dft_tflops": {k: round(kt[k]["vis_pixels"] * executed[k]["flop"] / (ms[k] * reps * 1e-3) / 1e12, 2)
+                       for k in executed}}
 
 
 def kernel_sweep(args):
@@ -660,15 +671,15 @@ def dataclasses_replace(obj, **kw):
     return dataclasses.replace(obj, **kw)
 
 
-def path_roofline(kt, wall_s):
+def path_roofline(kt, wall_s, executed):
     """Sustained rate of the whole timed step: both DFT kernels' executed matrix-core FLOP
     over the wall time, which also covers the FFTs, the adder, the splitter and the zeroing
     kernels."""
-    flop = sum(kt[k]["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"] for k in ("grid_dft", "degrid_dft"))
+    flop = sum(kt[k]["vis_pixels"] * executed[k]["flop"] for k in executed if executed[k]["unit"] != "vector")
     achieved = flop / wall_s / 1e12
     return {"achieved": round(achieved, 3), "peak": round(PEAK_FP16_MATRIX_TFLOPS, 1), "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_FP16_MATRIX_TFLOPS, 4),
-            "scope": "grid_dft + degrid_dft executed FP16 matrix FLOP (128 per vp each) over the wall time "
+            "scope": "grid_dft + degrid_dft executed FP16 matrix FLOP (flop_per_vp of each) over the wall time "
                      "of the timed steps"}
 
 
@@ -747,6 +758,8 @@ def main():
     plan = aidg.Plan(geo, wl.n_stations, wl.baselines, wl.uvw, wl.freqs, A)
     plan_s = time.perf_counter() - t0
     info = plan.info
+    kernels_taken = plan.kernels()
+    executed = flop_executed(kernels_taken, info["n_subgrids"])
     gen = torch.Generator(device="cuda")
     gen.manual_seed(2)
     V = torch.randn(plan.vis_shape(), dtype=torch.complex64, device="cuda", generator=gen)
@@ -789,11 +802,13 @@ def main():
     dom = max(("grid_dft", "degrid_dft", "fft_add", "split_ifft"), key=lambda k: kt[k]["ms"])
     k = kt[dom]
     if dom in ("grid_dft", "degrid_dft"):
-        achieved = k["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"] / (k["ms"] * 1e-3) / 1e12
+        achieved = k["vis_pixels"] * executed[dom]["flop"] / (k["ms"] * 1e-3) / 1e12
         method = k["vis_pixels"] * FLOP_PER_VP / (k["ms"] * 1e-3) / 1e12
-        roof = {"kernel": dom, "bound": "mfma", "achieved": round(achieved, 3),
-                "peak": round(PEAK_FP16_MATRIX_TFLOPS, 1), "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK_FP16_MATRIX_TFLOPS, 4), "traffic": measured_traffic(dom),
+        matrix = executed[dom]["unit"] != "vector"
+        peak = PEAK_FP16_MATRIX_TFLOPS if matrix else PEAK_FP32_TFLOPS
+        roof = {"kernel": dom, "bound": "mfma" if matrix else "alu", "achieved": round(achieved, 3),
+                "peak": round(peak, 1), "unit": "TFLOP/s",
+                "frac": round(achieved / peak, 4), "traffic": measured_traffic(dom),
                 "method_of_fp32_vector_peak": round(method / PEAK_FP32_TFLOPS, 4),
                 "avg_launch_ms": round(k["ms"] / max(k["launches"], 1), 4),
                 "launches": k["launches"]}
@@ -806,7 +821,8 @@ def main():
     kernels = {name: {"ms_per_step": round(v["ms"] / args.steps, 3),
                       "launches_per_step": v["launches"] / args.steps,
                       **({"tflops": round(v["vis_pixels"] * FLOP_PER_VP / (v["ms"] * 1e-3) / 1e12, 3),
-                          "tflops_executed": round(v["vis_pixels"] * FLOP_PER_VP_EXECUTED["fp32"]
+                          "flop_per_vp": round(executed[name]["flop"], 2), "unit": executed[name]["unit"],
+                          "tflops_executed": round(v["vis_pixels"] * executed[name]["flop"]
                                                    / (v["ms"] * 1e-3) / 1e12, 3)}
                          if name in ("grid_dft", "degrid_dft") and v["ms"] > 0 else {})}
                for name, v in kt.items()}
@@ -817,8 +833,9 @@ def main():
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 3),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32", "data": "synthetic",
-        "config": {**workload_description(wl, info),
+        "dtype": "f32 (matrix products of split f16 pairs)" if kernels_taken["grid_kernel"] else "f32",
+        "data": "synthetic",
+        "config": {**workload_description(wl, info), "kernels": kernels_taken,
                    "aterm_mode": "inverse (normalised A^-1)" if args.aterm_mode else "adjoint (A^H)",
                    "grid_planes": 1 if args.stokes_i else 4},
         "grid_mvis_s": round(n / (np.median(t_grid) * 1e-3) / 1e6, 3),
@@ -828,7 +845,7 @@ def main():
                        "job": "one grid job + one degrid job of the whole observation"},
         "plan_build_s": round(plan_s, 3),
         "roofline": roof,
-        "path_roofline": path_roofline(kt, wall),
+        "path_roofline": path_roofline(kt, wall, executed),
         "kernels": kernels,
     }
     if not args.no_cpu_baseline:
