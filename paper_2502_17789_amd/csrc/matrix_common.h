@@ -118,11 +118,12 @@ __device__ __forceinline__ unsigned pair_of(float x) {
 __device__ __forceinline__ float pair_high(unsigned p) { return (float)__builtin_bit_cast(half2v, p).y; }
 
 // Power of two that brings a largest component m to [2^9, 2^10), and its reciprocal (so
-// that the low halves stay normal FP16 numbers down to 2^-23 of m).  Infinities and NaNs
-// stay what they are under either factor.
+// that the low halves stay normal FP16 numbers down to 2^-23 of m); below 2^-117 to less, as
+// the reciprocal is at least 2^-126: the smallest normal m to 1.  Infinities and NaNs stay
+// what they are under either factor.
 __device__ __forceinline__ void fit_scale(float m, float& scale, float& unscale) {
   int e = (int)((__float_as_uint(m) >> 23) & 255) - 127;
-  e = max(-110, min(e, 127));
+  e = max(-117, min(e, 127));
   scale = __uint_as_float((unsigned)(127 + 9 - e) << 23);
   unscale = __uint_as_float((unsigned)(127 - 9 + e) << 23);
 }

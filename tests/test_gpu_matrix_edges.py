@@ -181,7 +181,7 @@ def test_gridder_rounds_no_more_than_the_general_kernel(aidg, L):
 
 
 @pytest.mark.parametrize("L", [32, 64, 96])
-@pytest.mark.parametrize("scales", ["one", "over time"])
+@pytest.mark.parametrize("scales", ["one", "over time", "smallest"])
 def test_faint_polarisations_keep_their_digits(aidg, L, scales):
     """With Jones matrices that do not mix them, each polarisation is as exact as if it were alone:
     FP32 sums of 128 visibilities and of the subgrid transform, 2e-7 of each plane; twice that
@@ -192,6 +192,8 @@ def test_faint_polarisations_keep_their_digits(aidg, L, scales):
     if scales == "over time":
         k = torch.arange(16, device="cuda", dtype=torch.float32)
         f = torch.stack([2.0 ** (2 * k), 2.0 ** (-2 * k - 10), 1e-6 * 10.0 ** (k // 4 % 2), (k > 7).float()], dim=1)
+    if scales == "smallest":  # about and below the smallest normal FP32 number
+        f = torch.full((16, 4), 2.0 ** -125, device="cuda")
     with t.plan() as p, t.plan(1) as q:
         v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g) * f[None, :, None, :]
         got, ref = p.grid(v), q.grid(v.to(torch.complex128))
