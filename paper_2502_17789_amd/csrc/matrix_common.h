@@ -71,6 +71,7 @@ constexpr unsigned kNegLow = 0x8000u;
 // the casts these would be flat accesses, with 64-bit addresses per lane and an LDS wait each.
 typedef float vec2 __attribute__((ext_vector_type(2)));
 typedef float vec4 __attribute__((ext_vector_type(4)));
+typedef vec4 vec4_of_2 __attribute__((aligned(8)));  // a caller's complex values: aligned as they are
 #define AIDG_GLOBAL __attribute__((address_space(1)))
 template <typename V>
 __device__ __forceinline__ V gload(const void* base, unsigned off) {

@@ -248,10 +248,10 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
         const int row = (int)(((float)k + 0.5f) * inv_nc), c = k - row * s.nc;
         const char* src = static_cast<const char*>(gs.in) + s.vis0 * 32 + vis_offset(row, c, a.nc_total);
         if (s.fold) {  // a folded sub-table is read as V^H
-          const vec4 h0 = gload<vec4>(src, 0), h1 = gload<vec4>(src, 16);
+          const vec4 h0 = gload<vec4_of_2>(src, 0), h1 = gload<vec4_of_2>(src, 16);
           next_v = (tid & 1) ? vec4{h0.z, -h0.w, h1.z, -h1.w} : vec4{h0.x, -h0.y, h1.x, -h1.y};
         } else {
-          next_v = gload<vec4>(src, 16 * (tid & 1));
+          next_v = gload<vec4_of_2>(src, 16 * (tid & 1));
         }
       }
     } else if (tid < 3 * kBlk) {

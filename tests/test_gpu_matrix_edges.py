@@ -206,6 +206,26 @@ def test_faint_polarisations_keep_their_digits(aidg, L, scales):
             assert e <= 4e-7 and d <= 4e-7, pol
 
 
+@pytest.mark.parametrize("L", [32, 96])
+def test_data_between_16_byte_boundaries(aidg, L):
+    """Buffers are aligned as complex64, no more: one element on gives the same results."""
+    def shifted(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        assert y.data_ptr() % 16 == 8 and y.is_contiguous()
+        return y.copy_(x)
+    t = first_term(aidg, L, 0.3, 1e-4, nearby=True)
+    t.bl = t.bl[:1]  # one subgrid: one order of the adder's sums
+    t.uvw = t.uvw[:1]
+    g = torch.Generator(device="cuda").manual_seed(10)
+    with t.plan() as p:
+        v = torch.randn(p.vis_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        G = torch.randn(p.grid_shape(), dtype=torch.complex64, device="cuda", generator=g)
+        assert torch.equal(p.grid(shifted(v), shifted(torch.zeros_like(G))), p.grid(v))
+        assert torch.equal(p.degrid(shifted(G), shifted(v)), p.degrid(G))
+        assert torch.equal(p.invert(shifted(G)), p.invert(G))
+        assert torch.equal(p.predict(shifted(G[0])), p.predict(G[0]))
+
+
 def one_subgrid(t):
     """A caller's table: baseline 0 of a track in one subgrid about the grid's centre."""
     table = np.zeros(1, t.aidg.SUBGRID_DTYPE)
