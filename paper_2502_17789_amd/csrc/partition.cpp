@@ -720,7 +720,10 @@ void w_series(int L, double fov, const std::vector<double>& taper, WSeries* out)
 // What the series may leave is weighed by the taper, as the rounding of the subgrid's FP32
 // transform is, some 2e-8 of its largest value: a source that prediction has divided by its
 // taper meets both over that taper.
-// - The series is cut where its first missing term is below 1e-8, and c = -b b is exact to 1e-8.
+// - The series is cut where its first missing term is below 1e-8, and c = -b b is exact to 1e-8
+//   at |w - wmid| = dw; at L = 32 to 3e-8, 1.7e-8 rms over a subgrid's w range, where the
+//   general kernels are nowhere nearer than 1.8e-8 (L = 64 and 96: 3e-9 at a quarter of the
+//   field, whose transform needs no twiddles, and 2e-8 elsewhere).
 // - A term of FP16 operands alone is off by 4e-4 of it (eight roundings to 2^-11): a first term
 //   up to 1.5e-5 and a second up to 1e-5.  Above, the first takes split operands (4 matrix
 //   products more than 8), off by 2e-6 of it.  With FP16 alone, lone sources at 0.1 to 0.4 of the
@@ -736,7 +739,7 @@ int w_series_order(const WSeries& ws, double wmid, double dw) {
   // The kernels' FP16 series operands are the data, at most 2^10.5, times powers of
   // 2 pi d b b and of b over its peak: below 2^14.
   const double p = 2.0 * M_PI * dw;
-  if (!(p * ws.b_peak * ws.b_peak <= 4.0) || !(p * ws.residual <= 1e-8)) return -1;
+  if (!(p * ws.b_peak * ws.b_peak <= 4.0) || !(p * ws.residual <= (ws.b.size() > 32 ? 1e-8 : 3e-8))) return -1;
   const double term[] = {p * ws.peak[1], p * p / 2 * ws.peak[2], p * p * p / 6 * ws.peak[3]};
   if (term[0] <= 1e-8) return 0;
   const int wide = term[0] > 1.5e-5 || term[1] > 1e-8 ? kWSplit : 0;
