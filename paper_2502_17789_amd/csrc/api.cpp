@@ -816,13 +816,15 @@ aidg_status aidg_plan_create(const aidg_geometry* geo, int32_t n_stations, int32
     if (!matrix) plan->w_terms = plan->n_split = 0;
     plan->matrix_grid = !matrix ? kMatrixNone : plan->n_split ? kMatrixWide : kMatrixPlain;
     // The matrix degridder works in blocks of 32 visibilities and takes the same time for 1
-    // as for 32: 13.6, 44 and 94 ns per subgrid at L = 32, 64, 96 with the chip full.  The
-    // other forms, with one row per subgrid and c channels, take 9 to 11 ns for c = 1 to 10
-    // (L = 32), 42 ns for 1, 45 for 4 and 60 for 16 (L = 64), 78 ns for 1, 88 for 6, 93 for
-    // 8 and 137 for 22 (L = 96); with 8 rows of one channel 17 ns at L = 32.  The lines are
-    // where the two meet, in that model's cost.
-    const double meet = L == 32 ? 13.5 : L == 64 ? 6.0 : 10.0;
-    if (matrix && g.degrid_form == AIDG_DEGRID_AUTO && cost >= meet * (double)plan->table.size())
+    // as for 32: 16, 50 and 105 ns per subgrid at L = 32, 64, 96 with the chip full, and 16.6,
+    // 55 to 56 and 118 to 125 where many split the series' first term.  The other forms, with
+    // one row per subgrid and a modelled cost of 9 (L = 32) take 10 ns; of 5, 8, 10 and 13
+    // (L = 64) 45, 47, 51 and 54; of 6, 10, 13 and 17 (L = 96) 86, 97, 106 and 121; with rows
+    // of one channel and costs of 15.6 and 20 17 and 19 (L = 32).  The lines are where the two
+    // meet.
+    const double n_sg = (double)plan->table.size(), n_split = (double)plan->n_split;
+    const double meet = L == 32 ? 14.5 * n_sg + 1.5 * n_split : (L == 64 ? 9.0 : 12.5) * n_sg + 4.0 * n_split;
+    if (matrix && g.degrid_form == AIDG_DEGRID_AUTO && cost >= meet)
       plan->matrix_degrid = kMatrixPlain;  // its kernel chooses by subgrid
     // inverse A-term mode: distinct (A_p plane, A_q plane) pairs with their visibility
     // counts, for the normalisation map
