@@ -64,6 +64,9 @@ __device__ __forceinline__ unsigned rot90(unsigned p) {
   asm("v_pk_mul_f16 %0, %1, %2 op_sel:[1,0] op_sel_hi:[0,1]" : "=v"(r) : "v"(p), "s"(0x3C00BC00u));  // (-1, 1)
   return r;
 }
+__device__ __forceinline__ Frag rot90(const Frag& f) {
+  return {rot90(f.w[0]), rot90(f.w[1]), rot90(f.w[2]), rot90(f.w[3])};
+}
 constexpr unsigned kNegLow = 0x8000u;
 
 // Loads and stores of device memory at a wave-uniform base and a lane's byte offset.  The

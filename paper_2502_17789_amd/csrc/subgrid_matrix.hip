@@ -293,78 +293,94 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
     }
     return r;
   };
-  // Products of step ks with the series.  WIDE: the first term in split operands, and a second
-  // one where the subgrid needs it, rows times (-i 2 pi d_k b(y))^2 / 2 and columns times
-  // b(x)^2; one column tile at a time, which takes no more registers than the others.
-  auto products = [&](int ks, int terms) {
+  // Products of step ks with the series' first term.  The small products come first and the
+  // step's sum is added whole: a chain of products onto the accumulators would round at the
+  // size of the subgrid's sum four times or more.
+  auto products = [&](int ks) {
     Frag bh[XT], bl[XT];
-    if constexpr (!WIDE) {
 #pragma unroll
-      for (int t = 0; t < XT; ++t) {
-        bh[t] = sh.alpha[ks][t][0][lane];
-        bl[t] = sh.alpha[ks][t][1][lane];
-      }
+    for (int t = 0; t < XT; ++t) {
+      bh[t] = sh.alpha[ks][t][0][lane];
+      bl[t] = sh.alpha[ks][t][1][lane];
     }
     const Rows r = rows(ks);
-    Frag nr, ni, mr, mi;
+    Frag nr, ni;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       nr.w[i] = pk_mul(r.ih.w[i], r.g[i]);
       ni.w[i] = pk_mul_neg(r.rh.w[i], r.g[i]);
     }
-    if constexpr (WIDE) {
-      const unsigned y_rest = sh.b_rest[y0 + yl];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const unsigned dw = sh.vb.dw[0][8 * ks + 4 * h + i], dl = sh.vb.dw[1][8 * ks + 4 * h + i];
-        mr.w[i] = mul_rest(r.ih.w[i], r.il.w[i], r.g[i], mul_rest(dw, dl, by, y_rest, r.g[i]), nr.w[i]);
-        mi.w[i] = rot90(mr.w[i]);  // (as ni is of nr)
-      }
-    }
 #pragma unroll
     for (int t = 0; t < XT; ++t) {
-      if constexpr (WIDE) {
-        __builtin_amdgcn_sched_barrier(0);
-        bh[t] = sh.alpha[ks][t][0][lane];
-        bl[t] = sh.alpha[ks][t][1][lane];
-      }
-      // small products first, and the step's sum added whole: a chain of products onto the
-      // accumulators would round at the size of the subgrid's sum four times or more
       acc16 cr = mfma(r.rl, bh[t], acc16{0}), ci = mfma(r.il, bh[t], acc16{0});
       cr = mfma(r.rh, bl[t], cr);
       ci = mfma(r.ih, bl[t], ci);
       Frag c;
 #pragma unroll
       for (int i = 0; i < 4; ++i) c.w[i] = pk_mul(bh[t].w[i], bx[t]);
-      if constexpr (WIDE) {
-        const unsigned x_rest = sh.b_rest[t * 32 + col];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bl[t].w[i] = mul_rest(bh[t].w[i], bl[t].w[i], bx[t], x_rest, c.w[i]);
-        cr = mfma(nr, bl[t], cr);
-        ci = mfma(ni, bl[t], ci);
-        cr = mfma(mr, c, cr);
-        ci = mfma(mi, c, ci);
-      }
       cr = mfma(nr, c, cr);
       ci = mfma(ni, c, ci);
-      if constexpr (WIDE) {
-        if (terms > 1) {
-          Frag n2r, n2i;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const unsigned g = pk_mul(r.g[i], pair_of(0.5f));
-            n2r.w[i] = pk_mul(ni.w[i], g);
-            n2i.w[i] = pk_mul_neg(nr.w[i], g);
-            c.w[i] = pk_mul(c.w[i], bx[t]);
-          }
-          cr = mfma(n2r, c, cr);
-          ci = mfma(n2i, c, ci);
-        }
-      }
       cr = mfma(r.rh, bh[t], cr);
       ci = mfma(r.ih, bh[t], ci);
       re[t] += cr;
       im[t] += ci;
+    }
+  };
+  // The same with the first term in split operands and a second one, rows times
+  // (-i 2 pi d_k b(y))^2 / 2 and columns times b(x)^2 (also where a subgrid does not need it: a
+  // branch here, as all rows held at once, spilled a hundred registers at L = 96).  One column
+  // tile at a time and, at L = 96, its real sum before the imaginary one, whose rows are formed
+  // again.
+  auto products_wide = [&](int ks) {
+    Frag rh, rl, n, m, n2;  // rows, and rows times g and g g / 2
+    {
+      const Rows r = rows(ks);
+      const unsigned y_rest = sh.b_rest[y0 + yl];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const unsigned dw = sh.vb.dw[0][8 * ks + 4 * h + i], dl = sh.vb.dw[1][8 * ks + 4 * h + i];
+        rh.w[i] = r.rh.w[i];
+        rl.w[i] = r.rl.w[i];
+        n.w[i] = pk_mul(r.ih.w[i], r.g[i]);
+        m.w[i] = mul_rest(r.ih.w[i], r.il.w[i], r.g[i], mul_rest(dw, dl, by, y_rest, r.g[i]), n.w[i]);
+        n2.w[i] = rot90(pk_mul(n.w[i], pk_mul(r.g[i], pair_of(0.5f))));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < XT; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      const Frag bh = sh.alpha[ks][t][0][lane];
+      Frag bl = sh.alpha[ks][t][1][lane], c, cl, c2;
+      const unsigned x_rest = sh.b_rest[t * 32 + col];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        c.w[i] = pk_mul(bh.w[i], bx[t]);
+        cl.w[i] = mul_rest(bh.w[i], bl.w[i], bx[t], x_rest, c.w[i]);
+        c2.w[i] = pk_mul(c.w[i], bx[t]);
+      }
+      const Frag left[7] = {rl, rh, n, m, n2, n, rh}, right[7] = {bh, bl, cl, c, c2, c, bh};
+      acc16 v = acc16{0}, u = acc16{0};
+      if constexpr (XT < 3) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+          v = mfma(left[k], right[k], v);
+          u = mfma(rot90(left[k]), right[k], u);
+        }
+        re[t] += v;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) v = mfma(left[k], right[k], v);
+        re[t] += v;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+          Frag f = left[k];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(f.w[i]));  // formed here, not held from the tile before
+          u = mfma(rot90(f), right[k], u);
+        }
+      }
+      im[t] += u;
     }
   };
   SubgridDev s = load_uniform(a.sg + gs.sb);
@@ -448,7 +464,10 @@ __attribute__((amdgpu_waves_per_eu(kGridWaves<L>, kGridWaves<L>))) void grid_mat
     __syncthreads();
 
 #pragma unroll 1
-    for (int ks = 0; ks < n8 / 8; ++ks) products(ks, cur.order & kWTerms);
+    for (int ks = 0; ks < n8 / 8; ++ks) {
+      if constexpr (WIDE) products_wide(ks);
+      else products(ks);
+    }
     if (!last) continue;
     // Jones correction of this subgrid, A_p^H S A_q, tapered and added to the group's sum;
     // a pixel's terms are loaded while the one before is computed
