@@ -19,7 +19,7 @@
 // subgrid and polarisation) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
 // forms the products exactly and adds in FP32; the gridder adds eight visibilities' sum at
 // once, the degridder sums the small products apart.  Every phase is formed and reduced to
-// [-1/2, 1/2] turn in FP64; there is no recurrence.  The series' first term takes hi hi
+// [-1/4, 1/4] turn in FP64; there is no recurrence.  The series' first term takes hi hi
 // alone where its largest value, times the taper, is below 1.5e-5 (w_series_order), and
 // otherwise split operands as well; a second term is smaller and takes hi hi.
 //
@@ -44,13 +44,19 @@ namespace {
 
 // exp(2 pi i (u x + w z)) for phases in turns, |u x + w z| < 2^18: the sum is formed onto
 // 1.5 2^20, whose last place is 2^-32 turn, so that the low word of the FP64 result is the
-// phase modulo a turn in fixed point (rounded twice, 2^-33 turn); one rounding to FP32 (2^-26
-// turn), then the transcendental unit's cosine and sine (absolute error at most 1.3e-7, rms
-// 3.5e-8 over [-1/2, 1/2] turn, measured over 2^24 points).
+// phase modulo a turn in fixed point (rounded twice, 2^-33 turn).  Reduced to [-1/4, 1/4] turn
+// (sign changes make up for half a turn), one rounding to FP32 (2^-27 turn), then the
+// transcendental unit's cosine and sine (absolute error at most 1.3e-7, rms 3.5e-8, measured
+// over 2^24 points).  From [-1/2, 1/2] a product of two phasors was 10 % further off, and the
+// visibilities of a few sources 4 % further than the general kernels'; the reduction is 2 % of
+// the kernels' time.
 __device__ __forceinline__ float2 turn_phasor(double u, double x, double w, double z) {
   const double th = fma(u, x, fma(w, z, 1572864.0));
-  const float t = (float)(int)__double_as_longlong(th) * 0x1p-32f;
-  return {__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t)};
+  const unsigned p = (unsigned)__double_as_longlong(th);
+  const unsigned flip = (p ^ (p << 1)) & 0x80000000u;
+  const float t = (float)((int)(p << 1) >> 1) * 0x1p-32f;
+  return {__uint_as_float(__float_as_uint(__builtin_amdgcn_cosf(t)) ^ flip),
+          __uint_as_float(__float_as_uint(__builtin_amdgcn_sinf(t)) ^ flip)};
 }
 
 // Pixels whose Jones matrices are loaded ahead.
