@@ -16,8 +16,8 @@
 //
 // Precision: each FP32 factor is split into two FP16 numbers (x = hi + lo, both rounded to
 // nearest: 2^-24 of the largest value, the data scaled to that by a power of two per
-// subgrid and polarisation) and a product takes hi hi + hi lo + lo hi on v_mfma_f32_32x32x16_f16, which
-// forms the products exactly and adds in FP32; the gridder adds eight visibilities' sum at
+// subgrid and polarisation) and a product takes hi hi + hi lo + lo hi on
+// v_mfma_f32_32x32x16_f16, which forms the products exactly and adds in FP32; the gridder adds eight visibilities' sum at
 // once, the degridder sums the small products apart.  Every phase is formed and reduced to
 // [-1/4, 1/4] turn in FP64; there is no recurrence.  The series' first term takes hi hi
 // alone where its largest value, times the taper, is below 1.5e-5 (w_series_order), and
@@ -26,10 +26,10 @@
 // What bounds it: the matrix cores at 3 (hi, lo) + 1 (first-order w term) products, and
 // beside them the VALU that forms the split operands: with 256 registers per lane two waves
 // share a SIMD and overlap little.  128 stations x 60 times x 96 channels, L = 96 (46.8M
-// visibilities): gridder 58.4 ms and degridder 66.2 (128.8 and 161.3 in the paired
-// recurrence); the products alone need 27 ms at the clock they run at, the matrix cores are
-// busy 46 and 38 % of the time.  64 stations x 30 x 48, L = 64: 2.14 and 2.51 ms
-// (5.1 and 5.1); 48 x 12 x 3 of every 32nd channel, L = 96, degridder 0.236 (0.69).
+// visibilities): gridder 69.0 ms and degridder 73.3 (128.8 and 161.3 in the paired
+// recurrence); the products alone need 26 ms at the clock they run at, the matrix cores are
+// busy 37 and 35 % of the time.  64 stations x 30 x 48, L = 64: 2.33 and 2.62 ms
+// (5.1 and 5.1); 48 x 12 x 3 of every 32nd channel, L = 96, degridder 0.265 (0.69).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -192,8 +192,8 @@ struct GridLds {
 };
 
 // Waves per SIMD that the registers are allocated for.  At L = 32 a lane has one column tile
-// and three workgroups fit a compute unit: 72 stations x 16 times x 96 channels, folded: 1.07 ms
-// against 1.25 with two; four spill (1.25 ms), and so do three at L = 64.
+// and three workgroups fit a compute unit: 72 stations x 16 times x 96 channels, folded, series
+// terms of split operands: 1.51 ms against 1.70 with two; four spill, and so do three at L = 64.
 template <int L>
 constexpr int kGridWaves = L == 32 ? 3 : 2;
 
